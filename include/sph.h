@@ -119,7 +119,8 @@ typedef struct {
   int32_t precision;       /* FP64, or FP32 pair sums with FP64 positions/integration/metric  */
   int32_t max_neighbours;  /* exact-list capacity per particle (0: 512); candidate lists hold  */
                            /*   twice as many                                                  */
-  int32_t cell_div;        /* cells per smoothing diameter of the finest level (0: 1)          */
+  int32_t cell_div;        /* FP32: cells per smoothing diameter of the finest level (0: 1);    */
+                           /*   without effect in FP64, whose list build has no cells          */
   double tile_cut;         /* a 64-particle tile is cut where the Morton curve jumps farther  */
                            /*   than tile_cut smoothing lengths (0: 10)                        */
   double skin;             /* relative Verlet skin s: candidate lists hold every b with       */
@@ -187,9 +188,8 @@ sph_status sph_set_params(sph_ctx* ctx, const sph_params* params);
 /* Neighbour search set-up (the summation runs over particles within the support radius,
  * section "Solid SPH Equations").  If the candidate lists are stale (first call, new n or
  * parameters, skin 0, or a particle moved or grew past the skin bound since the last build):
- * permute all state arrays along a global Morton curve, sort particles into a multi-level cell
- * grid (levels by h) and build candidate lists { b != a : |x_a - x_b| < (1 + skin)(h_a + h_b) }
- * per tile of at most 64 consecutive particles.  The exact sets
+ * permute all state arrays along a global Morton curve and build candidate lists, which contain
+ * { b != a : |x_a - x_b| < (1 + skin)(h_a + h_b) }, per tile of at most 64 consecutive particles.  The exact sets
  * N(a) = { b != a : |x_a - x_b|^2 < (h_a + h_b)^2 }, evaluated in FP64 without contraction,
  * are extracted from the candidates by sph_density.  With skin > 0 this call waits for the
  * one-word drift test on the device before deciding. */

@@ -153,7 +153,7 @@ const char* sph_status_string(sph_status s) {
 void sph_destroy(sph_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
-  void* bufs[] = {c->grid, c->keys, c->vals, c->cell_se, c->pos_sorted, c->sort.keys_alt, c->sort.vals_alt,
+  void* bufs[] = {c->grid, c->keys, c->vals, c->cell_se, c->pos_sorted, c->sub_box, c->tile_box, c->super_box, c->sort.keys_alt, c->sort.vals_alt,
                   c->sort.hist, c->sort.rowtot, c->sort.partial, c->sort.scan_bsum, c->tile_u, c->tile_start, c->tile_cnt, c->tile_uoff,
                   c->tile_usize, c->stress_tiles, c->tile_st, c->nbr16, c->nbr_count, c->nbr_count_sl, c->nbr16s, c->nbr_count_s, c->pos_build, c->drift_flag,
                   c->pos4, c->fv, c->fa, c->sig, c->pos4f, c->fvf,
@@ -207,6 +207,8 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
   c->sort.max_blocks = (int)((cap + 4095) / 4096);
   if ((e = dalloc(&c->grid, 1)) || (e = dalloc(&c->keys, cap)) || (e = dalloc(&c->vals, cap)) ||
       (e = dalloc(&c->cell_se, c->max_cells)) || (e = dalloc(&c->pos_sorted, cap)) ||
+      (e = dalloc(&c->sub_box, capw / 8 + capw + 8)) || (e = dalloc(&c->tile_box, capw)) ||
+      (e = dalloc(&c->super_box, capw / 64 + 1)) ||
       (e = dalloc(&c->sort.keys_alt, cap)) || (e = dalloc(&c->sort.vals_alt, cap)) ||
       (e = dalloc(&c->sort.hist, (size_t)256 * c->sort.max_blocks)) || (e = dalloc(&c->sort.rowtot, 256)) ||
       (e = dalloc(&c->sort.partial, (size_t)8 * 1024)) ||

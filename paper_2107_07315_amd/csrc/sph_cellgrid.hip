@@ -1,0 +1,729 @@
+// Candidate-list build on a multi-level cell grid, for the FP32 pair sums.
+//
+// Particles are binned into up to four levels by h (factor 2 per level), each with its own uniform
+// grid (cell size 2 hmax_l / cell_div) addressed by Morton codes.  A tile searches every level l
+// within h_a + hmax_l and skips cells whose box lies farther away.
+// Why FP32 runs keep this build while FP64 runs take the box search of sph_cells.hip: the order of
+// a tile's union decides which of a target's lanes adds which term, and when, and an FP32 sum's
+// rounding with it.  In a star near equilibrium the accelerations are small differences of large
+// pair terms, and a rounding difference moves a few particles to the next FP32 position in the steps
+// that follow: taken from the other build's order, ten steps of the 2M-particle star differ by
+// 2.5e-5 in the accelerations (both orders are equally far from the FP64 values), a perfect lattice
+// by 2e-3.  With this build FP32 runs reproduce earlier results bit for bit.
+#include "sph_internal.h"
+
+namespace {
+
+constexpr int kB = 256;
+
+__device__ __forceinline__ int particle_level(double h, const GridInfo& g) {
+  double ratio = h / g.hmin;
+  int l = 0;
+  while (l < g.nlev - 1 && ratio >= (double)(2 << l)) ++l;
+  return l;
+}
+
+// The same test against the skin-widened support (1 + s)(h_a + h_b); s1 = 1 + s.  With s = 0 it
+// is bit-identical to neighbour_test.
+__device__ __forceinline__ bool candidate_test(double dx, double dy, double dz, double ha, double hb, double s1) {
+#pragma clang fp contract(off)
+  double r2 = (dx * dx + dy * dy) + dz * dz;
+  double H = (ha + hb) * s1;
+  return r2 < H * H;
+}
+
+// Per level: largest h and the bounding box of the level's particles (a tile's search at a level
+// is clipped to that box, which keeps large-h tiles from enumerating the empty fine cells of
+// levels that only occupy the core).
+__global__ __launch_bounds__(kB) void k_level_hmax(const double4* __restrict__ pos4, int64_t n, GridInfo* g) {
+  __shared__ unsigned long long m[SPH_MAX_LEV];
+  __shared__ unsigned long long blo[SPH_MAX_LEV][3], bhi[SPH_MAX_LEV][3];
+  if (threadIdx.x < SPH_MAX_LEV) {
+    m[threadIdx.x] = 0ull;
+    for (int d = 0; d < 3; ++d) {
+      blo[threadIdx.x][d] = ~0ull;
+      bhi[threadIdx.x][d] = 0ull;
+    }
+  }
+  __syncthreads();
+  GridInfo G = *g;
+  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < n;
+       a += (int64_t)gridDim.x * blockDim.x) {
+    const double4 q = pos4[a];
+    const int l = particle_level(q.w, G);
+    atomicMax(&m[l], (unsigned long long)__double_as_longlong(q.w));
+    const double c[3] = {q.x, q.y, q.z};
+    for (int d = 0; d < 3; ++d) {
+      const unsigned long long e = enc_double(c[d]);
+      atomicMin(&blo[l][d], e);
+      atomicMax(&bhi[l][d], e);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < SPH_MAX_LEV && m[threadIdx.x]) {
+    const int l = threadIdx.x;
+    atomicMax(&g->hlev_bits[l], m[l]);
+    for (int d = 0; d < 3; ++d) {
+      atomicMin(&g->lev_lo[l][d], blo[l][d]);
+      atomicMax(&g->lev_hi[l][d], bhi[l][d]);
+    }
+  }
+}
+
+__global__ void k_grid_setup2(GridInfo* g, int cell_div, int64_t max_cells, DevStatus* st) {
+  double hi[3];
+  for (int d = 0; d < 3; ++d) hi[d] = g->periodic ? g->box : dec_double(g->enc_hi[d]);
+  double grow = 1.0;
+  for (int attempt = 0; attempt < 64; ++attempt) {
+    uint64_t total = 0;
+    bool ok = true;
+    for (int l = 0; l < g->nlev; ++l) {
+      double hl = __longlong_as_double((long long)g->hlev_bits[l]);
+      if (!(hl > 0.0)) hl = g->hmin * (double)(1 << l);
+      g->hlev[l] = hl;
+      double c = 2.0 * hl / (double)cell_div * grow;
+      int bmax = 0;
+      for (int d = 0; d < 3; ++d) {
+        int dim;
+        if (g->periodic) {
+          dim = (int)floor(g->box / c);
+          if (dim < 1) dim = 1;
+        } else {
+          double ext = hi[d] - g->lo[d];
+          dim = (int)floor(ext / c) + 1;
+        }
+        if (dim > 1024) ok = false;
+        g->dims[l][d] = dim;
+        int b = 0;
+        while ((1 << b) < dim) ++b;
+        bmax = b > bmax ? b : bmax;
+      }
+      g->cell[l] = g->periodic ? 0.0 : c;   // periodic: per-dimension sizes below
+      g->bits[l] = bmax;
+      g->base[l] = (uint32_t)total;
+      total += 1ull << (3 * bmax);
+    }
+    if (ok && total <= (uint64_t)max_cells) {
+      g->base[g->nlev] = (uint32_t)total;
+      if (g->periodic)
+        for (int l = 0; l < g->nlev; ++l) g->cell[l] = g->box / (double)g->dims[l][0];
+      return;
+    }
+    grow *= 1.25;
+  }
+  // No grid fits: fall back to a single cell (every key 0, memory-safe) and report the error.
+  latch_error(st, SPH_E_ARG, -1);
+  g->nlev = 1;
+  g->cell[0] = 1e300;
+  g->dims[0][0] = g->dims[0][1] = g->dims[0][2] = 1;
+  g->bits[0] = 0;
+  g->base[0] = 0;
+  g->base[1] = 1;
+}
+
+__device__ __forceinline__ int cell_coord(double x, double lo, double c, int dim) {
+  int k = (int)floor((x - lo) / c);
+  return k < 0 ? 0 : (k > dim - 1 ? dim - 1 : k);
+}
+
+__global__ __launch_bounds__(kB) void k_keys(const double4* __restrict__ pos4, int64_t n,
+                                             const GridInfo* __restrict__ gp, uint32_t* __restrict__ keys,
+                                             uint32_t* __restrict__ vals) {
+  int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (a >= n) return;
+  const GridInfo& g = *gp;
+  double4 p = pos4[a];
+  int l = particle_level(p.w, g);
+  double c = g.cell[l];
+  uint32_t ix = (uint32_t)cell_coord(p.x, g.lo[0], c, g.dims[l][0]);
+  uint32_t iy = (uint32_t)cell_coord(p.y, g.lo[1], c, g.dims[l][1]);
+  uint32_t iz = (uint32_t)cell_coord(p.z, g.lo[2], c, g.dims[l][2]);
+  keys[a] = g.base[l] + (spread3(ix) | (spread3(iy) << 1) | (spread3(iz) << 2));
+  vals[a] = (uint32_t)a;
+}
+
+// Clears the cells in use (base[nlev] entries) to empty ranges.
+__global__ __launch_bounds__(kB) void k_cells_clear(int2* __restrict__ se, const GridInfo* __restrict__ gp) {
+  const int64_t total = gp->base[gp->nlev];
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
+    se[i] = make_int2(0, 0);
+}
+
+__global__ __launch_bounds__(kB) void k_cell_ranges(const uint32_t* __restrict__ keys, int64_t n,
+                                                    int2* __restrict__ se) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  uint32_t k = keys[i];
+  if (i == 0 || keys[i - 1] != k) se[k].x = (int32_t)i;
+  if (i == n - 1 || keys[i + 1] != k) se[k].y = (int32_t)(i + 1);
+}
+
+// Positions and h in the cell-sorted order (candidate gathers of the build).
+__global__ __launch_bounds__(kB) void k_gather_pos(const double4* __restrict__ src, const uint32_t* __restrict__ perm,
+                                                   int64_t n, double4* __restrict__ dst) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) dst[i] = src[perm[i]];
+}
+
+struct BuildArgs {
+  const double4* __restrict__ pos4;
+  int64_t n;
+  const GridInfo* __restrict__ grid;
+  const uint32_t* __restrict__ perm;   // cell-sorted position -> particle index
+  const double4* __restrict__ pos_sorted;
+  const int2* __restrict__ cell_se;
+  const int32_t* __restrict__ tile_start;
+  const int32_t* __restrict__ tile_cnt;
+  const uint32_t* __restrict__ tile_uoff;
+  int64_t capw, upool;
+  int cap, ucap;
+  int32_t* __restrict__ tile_u;
+  int32_t* __restrict__ tile_usize;
+  uint16_t* __restrict__ nbr16;     // candidate slot lists
+  int32_t* __restrict__ count;       // candidates per particle
+  int lanes;                         // slots per particle (lanes per target of the pair passes)
+  int cap_sl;                        // entries a slot holds
+  DevStatus* status;
+};
+
+__device__ __forceinline__ double wave_min_d(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
+  return v;
+}
+__device__ __forceinline__ double wave_max_d(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+// min / max over aligned groups of 8 lanes
+__device__ __forceinline__ double grp8_min(double v) {
+  for (int off = 1; off < 8; off <<= 1) v = fmin(v, __shfl_xor(v, off, 64));
+  return v;
+}
+__device__ __forceinline__ double grp8_max(double v) {
+  for (int off = 1; off < 8; off <<= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+__device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v) {
+  for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off, 64);
+  return v;
+}
+
+struct TileState {
+  int64_t a;
+  int32_t a32;               // a as a 32-bit index (candidate indices are 32-bit), -1 if not valid
+  bool valid;
+  unsigned long long vmask;  // the wave's valid lanes
+  double xa, ya, za, ha;
+  double hs;                 // ha (1 + skin)(1 + 2^-40), the candidate test's scaled h
+  int usize, cnt, ucap;
+  int32_t* U;
+  uint16_t* row;             // the lane's staging row in LDS (8 entries of each of the L slots)
+  uint4* slot0;              // group 0 of the lane's first slot
+  int64_t gstride;           // groups between consecutive groups of one slot (capw * lanes)
+};
+
+// Candidate k of a particle goes to its slot k % L, as entry k / L (L = lanes per target of the
+// pair passes): each lane of the density pass then walks one contiguous slot list.  The lane's
+// LDS row holds 8 L consecutive candidates in arrival order (candidate k at k mod 8 L, so entry p
+// of slot s of the row's group sits at p L + s); when the row is full every slot has a complete
+// group of 8, and the row is stored as L groups (group g of slot s at g * capw * L + s), each
+// gathered from the row by byte permutes.  A row holds group g = k / (8 L) of every slot.
+template <int L>
+__device__ __forceinline__ void store_row_groups(const TileState& T, int g, int nslots) {
+  uint32_t D[4 * L];
+  __builtin_memcpy(D, T.row, sizeof(D));
+#pragma unroll
+  for (int s = 0; s < L; ++s) {
+    if (s >= nslots) break;
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (L == 1) {
+        w[k] = D[k];
+      } else {
+        const int i0 = 2 * k * L + s, i1 = (2 * k + 1) * L + s;   // entries 2k, 2k+1 of slot s
+        const uint32_t sel = ((i0 & 1) ? 0x0302u : 0x0100u) | ((i1 & 1) ? 0x07060000u : 0x05040000u);
+        w[k] = __builtin_amdgcn_perm(D[i1 >> 1], D[i0 >> 1], sel);
+      }
+    }
+    T.slot0[(int64_t)g * T.gstride + s] = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+template <int L>
+__device__ __forceinline__ void append_candidate(const BuildArgs& B, TileState& T, int loc) {
+  const unsigned k = (unsigned)T.cnt;
+  const uint16_t v = (uint16_t)loc;
+  __builtin_memcpy(T.row + (k & (8 * L - 1)), &v, sizeof(v));
+  ++T.cnt;
+  if ((k & (8 * L - 1)) == 8 * L - 1 && (int)(k / (8 * L)) * 8 < B.cap_sl) store_row_groups<L>(T, (int)(k / (8 * L)), L);
+}
+
+// candidate test (skin-widened, FP64) of every lane's target against batch candidates cb[0..nb),
+// nb <= 64; NB > 0 fixes nb at compile time (full batches).  The test is
+// r^2 < (h_a' + h_b')^2 with h' = h (1 + skin)(1 + 2^-40) (T.hs, cb[j].w) and r^2 by FMA: the
+// factor 1 + 2^-40 exceeds the few ulp by which this rounding can differ from the exact decision
+// of the density pass, so the candidates always contain every pair that test can accept (with a
+// positive skin the rebuild test's own margin of 1e-9 is larger still).
+// Candidates are taken one at a time: the wave's ballot decides at once whether candidate j joins
+// the union (as its next member), and the lanes that hit it append that local index, so the
+// lists come out ascending in local index and U in candidate order.
+template <int L, int NB, bool PER>
+__device__ __forceinline__ void run_batch(const BuildArgs& B, TileState& T, const double4* cb, const int32_t* cbi,
+                                          int nb, double box) {
+  const int lane = threadIdx.x;
+  unsigned long long um = 0ull;   // the batch's union members (wave-uniform)
+  int nm = 0;
+  // the lane's decision (hit) and the wave's mask of it, the mask from the compares themselves
+  // (ballot of the combined flag would first widen it to a vector register)
+  struct Hit { bool hit; unsigned long long m; };
+  auto test = [&](const double4& pb, int32_t bj) -> Hit {
+    const double dx = min_image(T.xa - pb.x, (int)PER, box), dy = min_image(T.ya - pb.y, (int)PER, box),
+                 dz = min_image(T.za - pb.z, (int)PER, box);
+    const double H = T.hs + pb.w;
+    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx)), H2 = H * H;
+    return Hit{T.valid && bj != T.a32 && r2 < H2,
+               __builtin_amdgcn_fcmp(r2, H2, 4 /* ordered less than */) &
+                   __builtin_amdgcn_uicmp(bj, T.a32, 33 /* not equal */) & T.vmask};
+  };
+  auto take = [&](int j, const Hit& t) {
+    const bool hit = t.hit;
+    if (t.m) {
+      um |= 1ull << j;
+      int loc = T.usize + nm;
+      ++nm;
+      loc = loc < T.ucap ? loc : T.ucap - 1;   // union overflow: keep reads in range, error latched
+      if (hit) append_candidate<L>(B, T, loc);
+    }
+  };
+  if constexpr (NB > 0) {
+    // the next candidate's record is read from LDS while this one is tested and appended
+    double4 nx = cb[0];
+    int32_t nbi = cbi[0];
+#pragma unroll 1
+    for (int jb = 0; jb < NB; jb += 8) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const double4 pb = nx;
+        const int32_t bj = nbi;
+        if (jb + k + 1 < NB) {
+          nx = cb[jb + k + 1];
+          nbi = cbi[jb + k + 1];
+        }
+        take(jb + k, test(pb, bj));
+      }
+    }
+  } else {
+    for (int j = 0; j < nb; ++j) take(j, test(cb[j], cbi[j]));
+  }
+  if (!um) return;
+  const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+  if ((um >> lane) & 1ull) {
+    const int loc = T.usize + __popcll(um & lt);
+    if (loc < T.ucap) T.U[loc] = cbi[lane];
+  }
+  T.usize += nm;
+}
+
+// Geometry of one tile, shared by the cost and build kernels: whole-tile box and max h
+// (wave-uniform), and in LDS the sub-boxes of the 8 groups of 8 consecutive particles with their
+// own max h.  Candidates and cells are tested against the sub-boxes, which stays tight where a
+// tile mixes small and large h (a candidate within (h_a + h_b)(1 + skin) of a particle a is that
+// close to a's sub-box).
+struct TileGeom {
+  double lo[3], hi[3], hmx;
+};
+
+__device__ __forceinline__ void tile_geometry(const double4 pa, bool valid, TileGeom& G, double (*sub)[8]) {
+  const int lane = threadIdx.x;
+  const double big = 1e300;
+  const double q[3] = {pa.x, pa.y, pa.z};
+  for (int d = 0; d < 3; ++d) {
+    G.lo[d] = wave_min_d(valid ? q[d] : big);
+    G.hi[d] = wave_max_d(valid ? q[d] : -big);
+  }
+  G.hmx = wave_max_d(valid ? pa.w : 0.0);
+  double gl[3], gh[3];
+  for (int d = 0; d < 3; ++d) {
+    gl[d] = grp8_min(valid ? q[d] : big);
+    gh[d] = grp8_max(valid ? q[d] : -big);
+  }
+  const double gx = grp8_max(valid ? pa.w : 0.0);
+  __syncthreads();
+  if ((lane & 7) == 0) {
+    for (int d = 0; d < 3; ++d) {
+      sub[lane >> 3][d] = 0.5 * (gl[d] + gh[d]);
+      sub[lane >> 3][3 + d] = 0.5 * (gh[d] - gl[d]);
+    }
+    sub[lane >> 3][6] = gx;
+  }
+  __syncthreads();
+}
+
+// Cells of level l that can hold candidates of the tile: the tile box widened by
+// (hmx + hlev[l])(1 + skin), clipped to the cells that hold the level's particles.
+struct LevelBox {
+  int lo3[3], ext[3];
+  bool wrap[3];
+  int64_t total;
+  double c;
+  uint32_t base;
+};
+
+template <bool PER>
+__device__ __forceinline__ bool level_box(const GridInfo& g, int l, const TileGeom& G, double s1, LevelBox& L) {
+  if (!g.hlev_bits[l]) return false;   // no particles at this level
+  L.c = g.cell[l];
+  L.base = g.base[l];
+  const double R = (G.hmx + g.hlev[l]) * s1 * (1.0 + 1e-9);
+  for (int d = 0; d < 3; ++d) {
+    const int dim = g.dims[l][d];
+    int l0 = (int)floor((G.lo[d] - R - g.lo[d]) / L.c);
+    int h0 = (int)floor((G.hi[d] + R - g.lo[d]) / L.c);
+    L.wrap[d] = false;
+    if (PER) {
+      if (h0 - l0 + 1 >= dim) { l0 = 0; h0 = dim - 1; }
+      else L.wrap[d] = true;
+    } else {
+      const int b0 = cell_coord(dec_double(g.lev_lo[l][d]), g.lo[d], L.c, dim);
+      const int b1 = cell_coord(dec_double(g.lev_hi[l][d]), g.lo[d], L.c, dim);
+      l0 = l0 < b0 ? b0 : l0;
+      h0 = h0 > b1 ? b1 : h0;
+    }
+    L.lo3[d] = l0;
+    L.ext[d] = h0 >= l0 ? h0 - l0 + 1 : 0;
+  }
+  L.total = (int64_t)L.ext[0] * L.ext[1] * L.ext[2];
+  return L.total > 0;
+}
+
+// Particle range [s, e) of the cell with linear index j of the level box (empty if the cell is
+// farther than (hmax_g + hlev[l])(1 + skin) from every sub-box).  UNR: sub-boxes tested per
+// unrolled step (their LDS reads issued together; more registers).
+template <bool PER, int UNR>
+__device__ __forceinline__ void cell_range(const GridInfo& g, int l, const LevelBox& L, int64_t j, double s1,
+                                           const double (*sub)[8], const int2* __restrict__ cell_se, int& s, int& e) {
+  s = e = 0;
+  if (j >= L.total) return;
+  // the box holds at most 2^30 cells (10 bits per axis), so 32-bit index arithmetic suffices
+  const unsigned jj = (unsigned)j, e0 = (unsigned)L.ext[0], e1 = (unsigned)L.ext[1];
+  const unsigned j1 = jj / e0;
+  const int kk[3] = {L.lo3[0] + (int)(jj - j1 * e0), L.lo3[1] + (int)(j1 % e1), L.lo3[2] + (int)(j1 / e1)};
+  int cc[3];
+  double b0[3], b1[3];
+  bool gapd[3];
+  for (int d = 0; d < 3; ++d) {
+    gapd[d] = !PER || L.wrap[d];
+    b0[d] = g.lo[d] + kk[d] * L.c;
+    b1[d] = b0[d] + L.c;
+    const int dim = g.dims[l][d];
+    cc[d] = L.wrap[d] ? ((kk[d] % dim) + dim) % dim : kk[d];
+  }
+  bool need = false;
+#pragma unroll UNR
+  for (int gi = 0; gi < 8; ++gi) {
+    double gap2 = 0.0;
+    for (int d = 0; d < 3; ++d) {
+      const double gd = fmax(0.0, fmax(b0[d] - (sub[gi][d] + sub[gi][3 + d]), (sub[gi][d] - sub[gi][3 + d]) - b1[d]));
+      gap2 += gapd[d] ? gd * gd : 0.0;
+    }
+    const double Rg = (sub[gi][6] + g.hlev[l]) * s1 * (1.0 + 1e-9);
+    need |= gap2 < Rg * Rg && sub[gi][6] > 0.0;
+  }
+  if (need) {
+    const uint32_t key = L.base + (spread3((uint32_t)cc[0]) | (spread3((uint32_t)cc[1]) << 1) |
+                                   (spread3((uint32_t)cc[2]) << 2));
+    const int2 se = cell_se[key];
+    s = se.x;
+    e = se.y;
+  }
+}
+
+// Cost estimate of each tile: the number of particles in the cells its build would gather.
+template <bool PER>
+__global__ __launch_bounds__(64) void k_tile_cost(const double4* __restrict__ pos4, const GridInfo* __restrict__ gp,
+                                                  const int32_t* __restrict__ tile_start,
+                                                  const int32_t* __restrict__ tile_cnt, const int2* __restrict__ cell_se,
+                                                  int32_t* __restrict__ cost) {
+  __shared__ double sub[8][8];
+  const int lane = threadIdx.x;
+  const GridInfo& g = *gp;
+  const double s1 = 1.0 + g.skin;
+  const int64_t ntiles = g.ntiles;
+  for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
+    const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
+    if (t >= ntiles) break;
+    const bool valid = lane < tile_cnt[t];
+    const double4 pa = valid ? pos4[tile_start[t] + lane] : make_double4(0.0, 0.0, 0.0, 0.0);
+    TileGeom G;
+    tile_geometry(pa, valid, G, sub);
+    int64_t tot = 0;
+    for (int l = 0; l < g.nlev; ++l) {
+      LevelBox L;
+      if (!level_box<PER>(g, l, G, s1, L)) continue;
+      for (int64_t q = 0; q < L.total; q += 64) {
+        int s, e;
+        cell_range<PER, 4>(g, l, L, q + lane, s1, sub, cell_se, s, e);
+        tot += e - s;
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
+    if (lane == 0) cost[t] = (int32_t)(tot < 0x7fffffff ? tot : 0x7fffffff);
+    __syncthreads();
+  }
+}
+
+// Splits expensive tiles: a particle also starts a tile at every 16th (cost > kSplit16 / cdiv) or
+// 8th (cost > kSplit8 / cdiv) position of its tile.  The cost counts the particles of the cells a
+// build gathers, which shrinks with finer cells (cdiv cells per smoothing diameter).  Reads the
+// tile of p from the scan of the old flags.
+constexpr int32_t kSplit16 = 12000, kSplit8 = 40000;
+__global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
+                                                   int64_t n, const int32_t* __restrict__ tile_start,
+                                                   const int32_t* __restrict__ cost, int cdiv) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  const uint32_t f = flag[p];
+  const int64_t t = (int64_t)idx[p] + f - 1;
+  const int32_t c = cost[t];
+  const int64_t off = p - tile_start[t];
+  const int size = c > kSplit8 / cdiv ? 8 : (c > kSplit16 / cdiv ? 16 : 64);
+  flag[p] = (f || (off % size) == 0) ? 1u : 0u;
+}
+
+// Tile neighbour lists.  Each tile is handled by one wavefront (one lane per target), in three
+// latency-friendly phases per block of 64 candidate cells:
+//  1. the 64 lanes take 64 cells of the level box at once, cull them against the sub-boxes and
+//     load their particle ranges;
+//  2. the wave gathers the cells' particles 64 at a time (a wave-wide prefix sum maps lanes to
+//     (cell, offset)), pre-tests each against the sub-boxes and appends survivors to an LDS batch;
+//  3. per batch of 64 candidates every lane runs the skin-widened FP64 test against all of them,
+//     building a 64-bit hit mask; the OR of the masks gives the batch's new union members (in
+//     candidate order) and each lane appends the local indices of its hits.
+// Tile t is particles [tile_start[t], tile_start[t] + tile_cnt[t]) of the array order (at most 64).
+// Candidates enter batches in a fixed order (level, cell, cell-sorted position), so U and the
+// lists are deterministic and each list is ascending in local index.
+template <bool PER, int NL>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_build_tiles(BuildArgs B) {
+  __shared__ int32_t c_s[64], c_o[64];
+  __shared__ double sub[8][8];   // per group of 8 tile particles: centre xyz, half-width xyz, max h
+  __shared__ double4 tp[16];     // the particles of a small tile (its exact pre-filter)
+  __shared__ double4 cb[128];
+  __shared__ int32_t cbi[128];
+  __shared__ __align__(16) uint16_t crow[64][8 * NL];   // per lane: staging of the candidate lists
+  const int lane = threadIdx.x;
+  const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const GridInfo& g = *B.grid;
+  const double box = g.box;
+  const double s1 = 1.0 + g.skin;
+  const double s1w = s1 * (1.0 + 0x1p-40);   // the batch test's widened factor
+  const int64_t ntiles = g.ntiles;
+  for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
+    const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
+    if (t >= ntiles) break;
+    const int32_t tcnt = B.tile_cnt[t];
+    const int64_t p = (int64_t)B.tile_start[t] + lane;
+    TileState T;
+    T.valid = lane < tcnt;
+    T.a = T.valid ? p : -1;
+    T.a32 = (int32_t)T.a;
+    T.vmask = __builtin_amdgcn_ballot_w64(T.valid);
+    const double4 pa = T.valid ? B.pos4[T.a] : make_double4(0.0, 0.0, 0.0, 0.0);
+    T.xa = pa.x; T.ya = pa.y; T.za = pa.z; T.ha = pa.w; T.hs = pa.w * s1w;
+    TileGeom G;
+    tile_geometry(pa, T.valid, G, sub);
+    if (lane < 16) tp[lane] = pa;
+    // small tiles (split because they are expensive) pre-filter candidates exactly against
+    // their own particles: far fewer batches, each of which would use only tcnt lanes
+    const bool small = tcnt <= 16;
+    const uint32_t uoff = B.tile_uoff[t];
+    T.ucap = (int)((int64_t)tcnt * B.cap < B.ucap ? (int64_t)tcnt * B.cap : B.ucap);
+    if ((int64_t)uoff + T.ucap > B.upool) {
+      T.ucap = 0;
+      if (lane == 0) latch_error(B.status, SPH_E_NGB_CAPACITY, -1);
+    }
+    T.U = B.tile_u + uoff;
+    T.usize = 0; T.cnt = 0;
+    T.row = crow[lane];
+    T.slot0 = reinterpret_cast<uint4*>(B.nbr16) + (T.valid ? p : 0) * NL;
+    T.gstride = B.capw * NL;
+    int pend = 0;   // candidates waiting in cb (wave-uniform)
+    for (int l = 0; l < g.nlev; ++l) {
+      LevelBox L;
+      if (!level_box<PER>(g, l, G, s1, L)) continue;
+      for (int64_t q = 0; q < L.total; q += 64) {
+        // phase 1: 64 cells at once; lanes take the block's cells in bit-reversed order so that
+        // consecutive union members come from all over the neighbourhood and every target's
+        // neighbours spread evenly over the LDS chunks of the pair passes
+        int s, e;
+        cell_range<PER, 2>(g, l, L, q + (int64_t)(__brev((unsigned)lane) >> 26), s1, sub, B.cell_se, s, e);
+        // wave prefix sum of the cells' particle counts
+        const int cntc = e - s;
+        int inc = cntc;
+        for (int off = 1; off < 64; off <<= 1) {
+          const int o = __shfl_up(inc, off, 64);
+          if (lane >= off) inc += o;
+        }
+        const int Tc = __shfl(inc, 63, 64);
+        __syncthreads();
+        c_s[lane] = s;
+        c_o[lane] = inc - cntc;
+        __syncthreads();
+        // phase 2: gather candidates, 4 rounds of 64 per pass (loads of all 4 issued together),
+        // pre-test against the sub-boxes (small tiles: against their particles) and append the
+        // survivors to the batch in slot order
+        for (int q0 = 0; q0 < Tc; q0 += 256) {
+          double4 pbu[4];
+          int32_t bu[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int slot = q0 + 64 * u + lane;
+            pbu[u] = make_double4(0.0, 0.0, 0.0, 0.0);
+            bu[u] = -1;
+            if (slot < Tc) {
+              int lo_i = 0, hi_i = 63;   // last cell with c_o <= slot
+              while (lo_i < hi_i) {
+                const int mid = (lo_i + hi_i + 1) >> 1;
+                if (c_o[mid] <= slot) lo_i = mid;
+                else hi_i = mid - 1;
+              }
+              const int32_t sp = c_s[lo_i] + (slot - c_o[lo_i]);
+              bu[u] = (int32_t)B.perm[sp];
+              pbu[u] = B.pos_sorted[sp];
+            }
+          }
+          // pre-test of the 4 rounds: each sub-box (particle) is read from LDS once for all 4
+          bool pass[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) pass[u] = false;
+          if (small) {
+            for (int k = 0; k < tcnt; ++k) {
+              const double4 q = tp[k];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const double4 pb = pbu[u];
+                pass[u] |= candidate_test(min_image(q.x - pb.x, (int)PER, box), min_image(q.y - pb.y, (int)PER, box),
+                                          min_image(q.z - pb.z, (int)PER, box), q.w, pb.w, s1);
+              }
+            }
+          } else {
+#pragma unroll 1
+            for (int gi = 0; gi < 8; ++gi) {
+              const double cx = sub[gi][0], cy = sub[gi][1], cz = sub[gi][2];
+              const double wx = sub[gi][3], wy = sub[gi][4], wz = sub[gi][5], hg = sub[gi][6];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const double4 pb = pbu[u];
+                const double ex = fmax(0.0, fabs(min_image(pb.x - cx, (int)PER, box)) - wx);
+                const double ey = fmax(0.0, fabs(min_image(pb.y - cy, (int)PER, box)) - wy);
+                const double ez = fmax(0.0, fabs(min_image(pb.z - cz, (int)PER, box)) - wz);
+                const double Rb = (hg + pb.w) * s1 * (1.0 + 1e-9);
+                pass[u] |= ex * ex + ey * ey + ez * ez < Rb * Rb && hg > 0.0;
+              }
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (q0 + 64 * u >= Tc) break;
+            const double4 pb = pbu[u];
+            pass[u] = pass[u] && bu[u] >= 0;
+            const unsigned long long m = __ballot(pass[u]);
+            if (pass[u]) {
+              const int k = pend + __popcll(m & lt);
+              cb[k] = make_double4(pb.x, pb.y, pb.z, pb.w * s1w);
+              cbi[k] = bu[u];
+            }
+            pend += __popcll(m);
+            __syncthreads();
+            if (pend >= 64) {   // phase 3 on a full batch
+              run_batch<NL, 64, PER>(B, T, cb, cbi, 64, box);
+              const int rest = pend - 64;
+              double4 mv = make_double4(0.0, 0.0, 0.0, 0.0);
+              int32_t mi = 0;
+              if (lane < rest) { mv = cb[64 + lane]; mi = cbi[64 + lane]; }
+              __syncthreads();
+              if (lane < rest) { cb[lane] = mv; cbi[lane] = mi; }
+              pend = rest;
+              __syncthreads();
+            }
+          }
+        }
+      }
+    }
+    if (pend > 0) run_batch<NL, 0, PER>(B, T, cb, cbi, pend, box);
+    __syncthreads();
+    if (T.valid && T.cnt <= B.cap && (T.cnt & (8 * NL - 1))) {
+      // the partly filled last row: slots s < r hold a partial last group g (a slot's count is at
+      // most that of slot 0, so the capacity test of slot 0 covers them all)
+      const int r = T.cnt & (8 * NL - 1), g = T.cnt / (8 * NL);
+      if ((T.cnt + NL - 1) / NL <= B.cap_sl) store_row_groups<NL>(T, g, r < NL ? r : NL);
+    }
+    if (T.valid) B.count[p] = T.cnt < B.cap ? T.cnt : B.cap;
+    if (lane == 0) B.tile_usize[t] = T.usize < T.ucap ? T.usize : T.ucap;
+    if (T.usize > T.ucap || T.cnt > B.cap) latch_error(B.status, SPH_E_NGB_CAPACITY, (int)(T.valid ? T.a : -1));
+  }
+}
+
+// Cells per smoothing diameter of the finest level (default 1: cells of 2 hmax_l).  Measured on
+// the 2M-particle star, 1 against 2 takes a list build from 6.2 to 5.3 ms (8x fewer cells to
+// cull, at 1.5x more particles to pre-test) and the FP32 step from 1.335 to 1.288 ms.
+static int cell_div_of(const sph_params& p) { return p.cell_div > 0 ? p.cell_div : 1; }
+
+template <bool PER>
+static void launch_build_per(const BuildArgs& B, dim3 grid, hipStream_t s) {
+  if (B.lanes == 1)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_build_tiles<PER, 1>), grid, dim3(64), 0, s, B);
+  else if (B.lanes == 2)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_build_tiles<PER, 2>), grid, dim3(64), 0, s, B);
+  else
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_build_tiles<PER, 4>), grid, dim3(64), 0, s, B);
+}
+static void launch_build(const BuildArgs& B, bool per, dim3 grid, hipStream_t s) {
+  if (per) launch_build_per<true>(B, grid, s);
+  else launch_build_per<false>(B, grid, s);
+}
+
+}  // namespace
+
+// Grid, cell-sorted order and cell ranges of the current pos4 (overwrites keys and vals).
+sph_status grid_prepare(sph_ctx* c, int64_t n) {
+  hipStream_t s = c->stream;
+  const unsigned nb = grid_for(n, kB), nred = nb < 1024 ? nb : 1024;
+  sph_status e;
+  hipLaunchKernelGGL(k_level_hmax, dim3(nred), dim3(kB), 0, s, c->pos4, n, c->grid);
+  hipLaunchKernelGGL(k_grid_setup2, dim3(1), dim3(1), 0, s, c->grid, cell_div_of(c->p),
+                     c->max_cells, c->status);
+  hipLaunchKernelGGL(k_keys, dim3(nb), dim3(kB), 0, s, c->pos4, n, c->grid, c->keys, c->vals);
+  if ((e = sph_sort_pairs(c, c->keys, c->vals, n))) return e;
+  hipLaunchKernelGGL(k_cells_clear, dim3(2048), dim3(kB), 0, s, c->cell_se, c->grid);
+  hipLaunchKernelGGL(k_cell_ranges, dim3(nb), dim3(kB), 0, s, c->keys, n, c->cell_se);
+  hipLaunchKernelGGL(k_gather_pos, dim3(nb), dim3(kB), 0, s, c->pos4, c->vals, n, c->pos_sorted);
+  HIP_TRY(hipGetLastError());
+  return SPH_OK;
+}
+
+// Marks the starts of the tiles that the cost estimate splits off in flag (idx: its scan so far).
+sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles) {
+  if (c->p.periodic)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<true>), dim3(tiles), dim3(64), 0, c->stream, c->pos4, c->grid,
+                       c->tile_start, c->tile_cnt, c->cell_se, c->tile_usize);
+  else
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<false>), dim3(tiles), dim3(64), 0, c->stream, c->pos4, c->grid,
+                       c->tile_start, c->tile_cnt, c->cell_se, c->tile_usize);
+  hipLaunchKernelGGL(k_tile_split, dim3(grid_for(n, kB)), dim3(kB), 0, c->stream, flag, idx, n, c->tile_start,
+                     c->tile_usize, cell_div_of(c->p));
+  HIP_TRY(hipGetLastError());
+  return SPH_OK;
+}
+
+sph_status grid_build_lists(sph_ctx* c, int64_t n, unsigned tiles) {
+  BuildArgs B;
+  B.pos4 = c->pos4; B.n = n; B.grid = c->grid; B.perm = c->vals; B.pos_sorted = c->pos_sorted;
+  B.cell_se = c->cell_se; B.capw = c->capw; B.cap = c->cap_s; B.ucap = c->ucap;
+  B.lanes = pass_lanes(c->p); B.cap_sl = cand_slot_capacity(c->cap_s, B.lanes);
+  B.tile_start = c->tile_start; B.tile_cnt = c->tile_cnt; B.tile_uoff = c->tile_uoff; B.upool = c->upool;
+  B.tile_u = c->tile_u; B.tile_usize = c->tile_usize; B.nbr16 = c->nbr16s; B.count = c->nbr_count_s;
+  B.status = c->status;
+  launch_build(B, c->p.periodic != 0, dim3(tiles), c->stream);
+  HIP_TRY(hipGetLastError());
+  return SPH_OK;
+}

@@ -1,14 +1,14 @@
-// Cell build and neighbour lists.
+// Candidate-list build.
 //
 // The paper's sums run over "particles within the support radius" (section "Solid SPH
 // Equations"); with support h_a + h_b the neighbour set is
 //   N(a) = { b != a : |x_a - x_b|^2 < (h_a + h_b)^2 }.
-// Smoothing lengths in a star vary about tenfold from the centre to the surface, so particles
-// are binned into up to four levels by h (factor 2 per level), each with its own uniform grid
-// (cell size 2 hmax_l / cell_div).  A particle searches every level l within h_a + hmax_l and
-// skips cells whose box lies farther away.  Cells are addressed by Morton codes so that the
-// sorted particle order is spatially compact.  The list build writes exact FP64 lists that all
-// later passes read, grouped in tiles of 64 particles (see k_build_tiles).
+// The particle arrays are kept along a global Morton curve and cut into tiles of at most 64
+// consecutive particles.  Neighbours are found through bounding boxes over that order: one box per
+// 8 consecutive particles of a tile, one per tile, one per 64 tiles, each with its largest h, so a
+// search adapts to the tenfold range of smoothing lengths by itself (no grid, no second sort).
+// k_build_tiles descends the boxes for every tile and tests what is left on the matrix cores.  FP32
+// runs take the lists of a cell grid instead (sph_cellgrid.hip, which says why).
 #include <stddef.h>
 #include <string.h>
 
@@ -112,132 +112,13 @@ __global__ __launch_bounds__(64) void k_grid_setup1(GridInfo* g, const unsigned 
   int L = 1;
   while (L < SPH_MAX_LEV && g->hmax >= g->hmin * (double)(1 << L)) ++L;
   g->nlev = L;
-}
-
-// Per level: largest h and the bounding box of the level's particles (a tile's search at a level
-// is clipped to that box, which keeps large-h tiles from enumerating the empty fine cells of
-// levels that only occupy the core).
-__global__ __launch_bounds__(kB) void k_level_hmax(const double4* __restrict__ pos4, int64_t n, GridInfo* g) {
-  __shared__ unsigned long long m[SPH_MAX_LEV];
-  __shared__ unsigned long long blo[SPH_MAX_LEV][3], bhi[SPH_MAX_LEV][3];
-  if (threadIdx.x < SPH_MAX_LEV) {
-    m[threadIdx.x] = 0ull;
+  // origin of the FP32 bounding boxes; a set wider than 2^32 smallest smoothing lengths is refused
+  for (int d = 0; d < 3; ++d) g->org[d] = isfinite(g->lo[d]) ? g->lo[d] : 0.0;
+  if (!periodic)
     for (int d = 0; d < 3; ++d) {
-      blo[threadIdx.x][d] = ~0ull;
-      bhi[threadIdx.x][d] = 0ull;
+      const double ext = dec_double(g->enc_hi[d]) - g->lo[d];
+      if (ext > 0x1p32 * g->hmin) latch_error(st, SPH_E_ARG, -1);
     }
-  }
-  __syncthreads();
-  GridInfo G = *g;
-  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < n;
-       a += (int64_t)gridDim.x * blockDim.x) {
-    const double4 q = pos4[a];
-    const int l = particle_level(q.w, G);
-    atomicMax(&m[l], (unsigned long long)__double_as_longlong(q.w));
-    const double c[3] = {q.x, q.y, q.z};
-    for (int d = 0; d < 3; ++d) {
-      const unsigned long long e = enc_double(c[d]);
-      atomicMin(&blo[l][d], e);
-      atomicMax(&bhi[l][d], e);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < SPH_MAX_LEV && m[threadIdx.x]) {
-    const int l = threadIdx.x;
-    atomicMax(&g->hlev_bits[l], m[l]);
-    for (int d = 0; d < 3; ++d) {
-      atomicMin(&g->lev_lo[l][d], blo[l][d]);
-      atomicMax(&g->lev_hi[l][d], bhi[l][d]);
-    }
-  }
-}
-
-__global__ void k_grid_setup2(GridInfo* g, int cell_div, int64_t max_cells, DevStatus* st) {
-  double hi[3];
-  for (int d = 0; d < 3; ++d) hi[d] = g->periodic ? g->box : dec_double(g->enc_hi[d]);
-  double grow = 1.0;
-  for (int attempt = 0; attempt < 64; ++attempt) {
-    uint64_t total = 0;
-    bool ok = true;
-    for (int l = 0; l < g->nlev; ++l) {
-      double hl = __longlong_as_double((long long)g->hlev_bits[l]);
-      if (!(hl > 0.0)) hl = g->hmin * (double)(1 << l);
-      g->hlev[l] = hl;
-      double c = 2.0 * hl / (double)cell_div * grow;
-      int bmax = 0;
-      for (int d = 0; d < 3; ++d) {
-        int dim;
-        if (g->periodic) {
-          dim = (int)floor(g->box / c);
-          if (dim < 1) dim = 1;
-        } else {
-          double ext = hi[d] - g->lo[d];
-          dim = (int)floor(ext / c) + 1;
-        }
-        if (dim > 1024) ok = false;
-        g->dims[l][d] = dim;
-        int b = 0;
-        while ((1 << b) < dim) ++b;
-        bmax = b > bmax ? b : bmax;
-      }
-      g->cell[l] = g->periodic ? 0.0 : c;   // periodic: per-dimension sizes below
-      g->bits[l] = bmax;
-      g->base[l] = (uint32_t)total;
-      total += 1ull << (3 * bmax);
-    }
-    if (ok && total <= (uint64_t)max_cells) {
-      g->base[g->nlev] = (uint32_t)total;
-      if (g->periodic)
-        for (int l = 0; l < g->nlev; ++l) g->cell[l] = g->box / (double)g->dims[l][0];
-      return;
-    }
-    grow *= 1.25;
-  }
-  // No grid fits: fall back to a single cell (every key 0, memory-safe) and report the error.
-  latch_error(st, SPH_E_ARG, -1);
-  g->nlev = 1;
-  g->cell[0] = 1e300;
-  g->dims[0][0] = g->dims[0][1] = g->dims[0][2] = 1;
-  g->bits[0] = 0;
-  g->base[0] = 0;
-  g->base[1] = 1;
-}
-
-__device__ __forceinline__ int cell_coord(double x, double lo, double c, int dim) {
-  int k = (int)floor((x - lo) / c);
-  return k < 0 ? 0 : (k > dim - 1 ? dim - 1 : k);
-}
-
-__global__ __launch_bounds__(kB) void k_keys(const double4* __restrict__ pos4, int64_t n,
-                                             const GridInfo* __restrict__ gp, uint32_t* __restrict__ keys,
-                                             uint32_t* __restrict__ vals) {
-  int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= n) return;
-  const GridInfo& g = *gp;
-  double4 p = pos4[a];
-  int l = particle_level(p.w, g);
-  double c = g.cell[l];
-  uint32_t ix = (uint32_t)cell_coord(p.x, g.lo[0], c, g.dims[l][0]);
-  uint32_t iy = (uint32_t)cell_coord(p.y, g.lo[1], c, g.dims[l][1]);
-  uint32_t iz = (uint32_t)cell_coord(p.z, g.lo[2], c, g.dims[l][2]);
-  keys[a] = g.base[l] + (spread3(ix) | (spread3(iy) << 1) | (spread3(iz) << 2));
-  vals[a] = (uint32_t)a;
-}
-
-// Clears the cells in use (base[nlev] entries) to empty ranges.
-__global__ __launch_bounds__(kB) void k_cells_clear(int2* __restrict__ se, const GridInfo* __restrict__ gp) {
-  const int64_t total = gp->base[gp->nlev];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
-    se[i] = make_int2(0, 0);
-}
-
-__global__ __launch_bounds__(kB) void k_cell_ranges(const uint32_t* __restrict__ keys, int64_t n,
-                                                    int2* __restrict__ se) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint32_t k = keys[i];
-  if (i == 0 || keys[i - 1] != k) se[k].x = (int32_t)i;
-  if (i == n - 1 || keys[i + 1] != k) se[k].y = (int32_t)(i + 1);
 }
 
 template <typename T>
@@ -284,7 +165,7 @@ __global__ __launch_bounds__(kB) void k_pack_pos(const double* __restrict__ x, c
 
 // Global Morton key of a 1024^3 grid over the bounding box: the particle arrays are kept in this
 // order (re-sorted every few steps), so any 64 consecutive particles form a compact tile whatever
-// the local density; the per-level cell tables index the particles through a permutation.
+// the local density.
 __global__ __launch_bounds__(kB) void k_gkeys(const double4* __restrict__ pos4, int64_t n,
                                               const GridInfo* __restrict__ gp, uint32_t* __restrict__ keys,
                                               uint32_t* __restrict__ vals) {
@@ -314,25 +195,22 @@ __global__ __launch_bounds__(kB) void k_gkeys(const double4* __restrict__ pos4, 
 // that spans the boundary could be that large.  Cutting where 2^(k+1) fine cells exceed 4 h keeps
 // every tile inside a region about 4 smoothing lengths across, in dense and sparse parts alike
 // (the factor is the tile_cut parameter).
+__device__ __forceinline__ double morton_jump(const GridInfo& g, const uint32_t* __restrict__ gkeys, int64_t p) {
+  double ext = 0.0;
+  for (int d = 0; d < 3; ++d) {
+    const double e = g.periodic ? g.box : dec_double(g.enc_hi[d]) - g.lo[d];
+    ext = e > ext ? e : ext;
+  }
+  const uint32_t x = gkeys[p] ^ gkeys[p - 1];
+  const int lvl = x ? (31 - __clz(x)) / 3 : -1;
+  return lvl >= 0 ? (double)(2 << lvl) * (ext / 1024.0) : 0.0;
+}
 __global__ __launch_bounds__(kB) void k_tile_flags(const uint32_t* __restrict__ gkeys, const double4* __restrict__ pos4,
                                                    int64_t n, const GridInfo* __restrict__ gp, double cut,
                                                    uint32_t* __restrict__ flag) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
-  bool start = (p & 63) == 0;
-  if (!start) {
-    const GridInfo& g = *gp;
-    double ext = 0.0;
-    for (int d = 0; d < 3; ++d) {
-      const double e = g.periodic ? g.box : dec_double(g.enc_hi[d]) - g.lo[d];
-      ext = e > ext ? e : ext;
-    }
-    const double fine = ext / 1024.0;
-    const uint32_t x = gkeys[p] ^ gkeys[p - 1];
-    const int lvl = x ? (31 - __clz(x)) / 3 : -1;
-    start = lvl >= 0 && (double)(2 << lvl) * fine > cut * pos4[p].w;
-  }
-  flag[p] = start ? 1u : 0u;
+  flag[p] = ((p & 63) == 0 || morton_jump(*gp, gkeys, p) > cut * pos4[p].w) ? 1u : 0u;
 }
 
 // Work list of the stress pass: the tiles that hold a particle of type 1 (crust).  Breaking only
@@ -413,27 +291,208 @@ __global__ __launch_bounds__(kB) void k_tile_len(const GridInfo* __restrict__ gp
   ub[t] = v;
 }
 
-// Tile neighbour lists.  Each tile is handled by one wavefront (one lane per target), in three
-// latency-friendly phases per block of 64 candidate cells:
-//  1. the 64 lanes enumerate 64 cells of the search box at once, cull them against the tile's
-//     bounding box and look up their particle ranges (parallel loads);
-//  2. the wave gathers the cells' particles 64 at a time (a wave-wide prefix sum maps lanes to
-//     (cell, offset)), pre-tests each against the tile box and appends survivors to an LDS batch;
-//  3. per batch of 64 candidates every lane runs the exact FP64 test against all of them,
-//     building a 64-bit hit mask; the OR of the masks gives the batch's new union members (in
-//     candidate order) and each lane appends the local indices of its hits.
-// Tile t is particles [tile_start[t], tile_start[t] + tile_cnt[t]) of the array order (at most 64).
-// Candidates enter batches in a fixed order (level, cell, cell-sorted position), so U and the
-// lists are deterministic and each list is ascending in local index.
+// ---- bounding boxes ----------------------------------------------------------------------------
+__device__ __forceinline__ double wave_min_d(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
+  return v;
+}
+// min / max over aligned groups of NL lanes
+template <int NL>
+__device__ __forceinline__ double grp_min(double v) {
+  for (int off = 1; off < NL; off <<= 1) v = fmin(v, __shfl_xor(v, off, 64));
+  return v;
+}
+template <int NL>
+__device__ __forceinline__ double grp_max(double v) {
+  for (int off = 1; off < NL; off <<= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+__device__ __forceinline__ float round_up(double v) { return (float)v * (1.0f + 0x1p-21f) + 1e-37f; }
+
+// Box of the NL lanes of a group: q = position relative to the origin, h, in = the lane holds a
+// particle with finite values.  The half-width is taken about the FP32-rounded centre and rounded
+// up, so the box holds every particle exactly.
+template <int NL>
+__device__ __forceinline__ Box group_box(const double q[3], double h, bool in) {
+  Box B;
+  const double big = 1e300;
+  float c[3], w[3];
+  const bool any = grp_max<NL>(in ? 1.0 : 0.0) > 0.0;
+  for (int d = 0; d < 3; ++d) {
+    const double lo = grp_min<NL>(in ? q[d] : big), hi = grp_max<NL>(in ? q[d] : -big);
+    c[d] = any ? (float)(0.5 * (lo + hi)) : 0.f;
+    w[d] = any ? round_up(fmax(hi - (double)c[d], (double)c[d] - lo)) : 0.f;
+  }
+  const float hm = any ? round_up(grp_max<NL>(in ? h : 0.0)) : -1.f;
+  B.c = make_float4(c[0], c[1], c[2], hm);
+  B.w = make_float4(w[0], w[1], w[2], 0.f);
+  return B;
+}
+
+// Whether particles of the two boxes can lie within (h_a + h_b) s1 of each other (s1 widened by
+// 1e-5, far above the FP32 rounding of the test; with a periodic box the centres' distance is the
+// minimum image, itself widened by its rounding).
+template <bool PER>
+__device__ __forceinline__ bool boxes_near(const float4& ac, const float4& aw, const float4& bc, const float4& bw,
+                                           float s1, float box) {
+  float dx = fabsf(ac.x - bc.x), dy = fabsf(ac.y - bc.y), dz = fabsf(ac.z - bc.z);
+  if constexpr (PER) {
+    const float e = box * 0x1p-21f;
+    dx = fminf(dx, box - dx) - e;
+    dy = fminf(dy, box - dy) - e;
+    dz = fminf(dz, box - dz) - e;
+  }
+  const float gx = fmaxf(0.f, dx - (aw.x + bw.x)), gy = fmaxf(0.f, dy - (aw.y + bw.y)), gz = fmaxf(0.f, dz - (aw.z + bw.z));
+  const float R = (ac.w + bc.w) * s1;
+  return gx * gx + gy * gy + gz * gz < R * R && bc.w > 0.f;
+}
+
+// Boxes of each tile and of its runs of 8 particles (one wave a tile).
+__global__ __launch_bounds__(64) void k_tile_boxes(const GridInfo* __restrict__ gp, const double4* __restrict__ pos4,
+                                                   const int32_t* __restrict__ tile_start,
+                                                   const int32_t* __restrict__ tile_cnt, Box* __restrict__ tile_box,
+                                                   Box* __restrict__ sub_box) {
+  const int lane = threadIdx.x;
+  const GridInfo& g = *gp;
+  const int64_t ntiles = g.ntiles;
+  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int32_t ts = tile_start[t], tc = tile_cnt[t];
+    const double4 p = lane < tc ? pos4[ts + lane] : make_double4(0.0, 0.0, 0.0, 0.0);
+    const double q[3] = {p.x - g.org[0], p.y - g.org[1], p.z - g.org[2]};
+    const bool in = lane < tc && isfinite(q[0]) && isfinite(q[1]) && isfinite(q[2]) && isfinite(p.w);
+    const Box sb = group_box<8>(q, p.w, in), tb = group_box<64>(q, p.w, in);
+    if ((lane & 7) == 0 && lane < tc) sub_box[(ts >> 3) + t + (lane >> 3)] = sb;
+    if (lane == 0) tile_box[t] = tb;
+  }
+}
+
+// Box of each run of 64 tiles (one wave a run).
+__global__ __launch_bounds__(64) void k_super_boxes(const GridInfo* __restrict__ gp, const Box* __restrict__ tile_box,
+                                                    Box* __restrict__ super_box) {
+  const int lane = threadIdx.x;
+  const int64_t ntiles = gp->ntiles, ns = (ntiles + 63) / 64;
+  for (int64_t s = blockIdx.x; s < ns; s += gridDim.x) {
+    const int64_t t = s * 64 + lane;
+    Box b;
+    b.c.w = -1.f;
+    if (t < ntiles) b = tile_box[t];
+    const bool in = b.c.w > 0.f;
+    // the union of the tiles' boxes, in FP64 from their FP32 corners
+    const float bc[3] = {b.c.x, b.c.y, b.c.z}, bw[3] = {b.w.x, b.w.y, b.w.z};
+    float c[3], w[3];
+    const bool any = __ballot(in) != 0ull;
+    for (int d = 0; d < 3; ++d) {
+      const double lo = grp_min<64>(in ? (double)bc[d] - (double)bw[d] : 1e300);
+      const double hi = grp_max<64>(in ? (double)bc[d] + (double)bw[d] : -1e300);
+      c[d] = any ? (float)(0.5 * (lo + hi)) : 0.f;
+      w[d] = any ? round_up(fmax(hi - (double)c[d], (double)c[d] - lo)) : 0.f;
+    }
+    const float hm = (float)grp_max<64>(in ? (double)b.c.w : -1.0);
+    if (lane == 0) super_box[s] = Box{make_float4(c[0], c[1], c[2], hm), make_float4(w[0], w[1], w[2], 0.f)};
+  }
+}
+
+// Cost estimate of each tile: the particles of the tiles near it.
+template <bool PER>
+__global__ __launch_bounds__(64) void k_tile_cost(const GridInfo* __restrict__ gp, const int32_t* __restrict__ tile_cnt,
+                                                  const Box* __restrict__ tile_box, const Box* __restrict__ super_box,
+                                                  int32_t* __restrict__ cost) {
+  const int lane = threadIdx.x;
+  const GridInfo& g = *gp;
+  const float s1 = (float)(1.0 + g.skin) * (1.0f + 1e-5f), box = (float)g.box;
+  const int64_t ntiles = g.ntiles, ns = (ntiles + 63) / 64;
+  for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
+    const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
+    if (t >= ntiles) break;
+    const Box own = tile_box[t];
+    int64_t tot = 0;
+    for (int64_t s0 = 0; s0 < ns; s0 += 64) {
+      bool near = false;
+      if (s0 + lane < ns) {
+        const Box b = super_box[s0 + lane];
+        near = boxes_near<PER>(own.c, own.w, b.c, b.w, s1, box);
+      }
+      unsigned long long m = __ballot(near);
+      while (m) {
+        const int64_t u = (s0 + __builtin_ctzll(m)) * 64 + lane;
+        m &= m - 1;
+        if (u < ntiles) {
+          const Box b = tile_box[u];
+          if (boxes_near<PER>(own.c, own.w, b.c, b.w, s1, box)) tot += tile_cnt[u];
+        }
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
+    if (lane == 0) cost[t] = (int32_t)(tot < 0x7fffffff ? tot : 0x7fffffff);
+  }
+}
+
+// Splits expensive tiles: a particle also starts a tile where the curve jumps farther than 4 (cost >
+// kSplit4) or 2 (cost > kSplit2) of the smaller smoothing lengths at the jump, and at every 32nd
+// position of the dearer ones.  A tile that spans such a jump near the surface, where h varies
+// tenfold, is wide against its smallest h and would test thousands of runs in one wave, which the
+// whole build then waits for.  On the 1M-particle star (mean cost 5700) 16.6k tiles become 18.1k
+// and the dearest tests 107 batches of 64 candidates (2700 without the split; 36 on average);
+// cutting every tile above 8000 at 4 h costs 15% more tiles, which the pair passes pay for at
+// every evaluation.  Sets of at most kSplitSmall particles (1100 tiles, about one a SIMD) take half
+// the thresholds: there more tiles run side by side, and the dearest tile is the build's time.  Reads
+// the tile of p from the scan of the old flags.
+constexpr int32_t kSplit4 = 12000, kSplit2 = 18000, kSplitSmall = 65536;
+__global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
+                                                   int64_t n, const int32_t* __restrict__ tile_start,
+                                                   const int32_t* __restrict__ cost, const uint32_t* __restrict__ gkeys,
+                                                   const double4* __restrict__ pos4, const GridInfo* __restrict__ gp) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  const uint32_t f = flag[p];
+  if (f) return;
+  const int64_t t = (int64_t)idx[p] - 1;
+  const int32_t c = cost[t];
+  const int32_t half = n <= kSplitSmall ? 2 : 1;
+  if (c <= kSplit4 / half) return;
+  const bool dear = c > kSplit2 / half;
+  // p > 0: particle 0 starts a tile
+  if ((dear && ((p - tile_start[t]) & 31) == 0) ||
+      morton_jump(*gp, gkeys, p) > (dear ? 2.0 : 4.0) * fmin(pos4[p].w, pos4[p - 1].w))
+    flag[p] = 1u;
+}
+
+// ---- candidate lists ---------------------------------------------------------------------------
+// One wave builds the lists of one tile (lane = target).  It descends the boxes: the runs of 64
+// tiles near its own box, their tiles, and those tiles' runs of 8 particles, tested against the
+// runs of its own tile.  Eight runs that pass form a batch of 64 candidates (lane = candidate),
+// which is tested against the 64 targets on the matrix cores:
+//   r^2 - (h_a' + h_b')^2 = -2 x_a.x_b - 2 h_a' h_b' + w_a + w_b,  w = |x|^2 - h'^2
+// (h' = (1 + skin) h, x relative to the tile's centre).  Each of the four components and w goes in
+// as two FP16 parts (hi = f16(v), lo = f16(v - hi)); hi.hi, hi.lo and lo.hi of four components and
+// the parts of the two w are 16 products, so one v_mfma_f32_32x32x16_f16 takes a block of 32 x 32
+// pairs and four take the batch (128 of the SIMD's cycles; 10 FP64 operations a pair on the vector
+// ALUs are 2560).  The sign bits are shifted into one 64-bit mask of hits per target, one v_alignbit
+// per 64 pairs.
+// The lists only have to contain the exact sets (the density pass takes the exact FP64 decision), so
+// each w is lowered by kListBand (|x|^2 + h'^2), more than the test can be off: with M = |x_a|^2 +
+// |x_b|^2 + h_a'^2 + h_b'^2 the parts leave out at most 2^-22 of a value, the product lo.lo 2^-22 of
+// hi.hi, and the FP32 inputs and the accumulation 40 2^-24 M, in all below 16 2^-22 M against the
+// band's 32 2^-22 M (a widening of H by 3e-5).  Lengths are scaled so that the tile's reach is 100.
+// In a tile so wide that the band would lengthen its lists (centre-to-corner above 8 of its smallest
+// h) every hit is tested again from the FP32 coordinates' differences; a batch with a candidate
+// beyond FP16's range, and a periodic box less than twice the tile's reach across, take the test
+// pair by pair in FP64.
+// A candidate hit by any target joins the union, as its next member, and each target appends the
+// local indices of its hits to its list, ascending.
+// Bound by instruction issue (about 490 vector instructions a batch, half of them the appends, and
+// their latency: 4 waves a SIMD) and, over the launch, by its dearest tiles.  Measured against a
+// cell grid of two smoothing lengths with an FP64 test of every candidate by every lane: 1M-particle
+// snapshot 3.34 -> 0.80 ms, 2M-particle star in a run 3.19 -> 1.32 ms (FP64 skin 0.08) and
+// 3.44 -> 1.4 ms (skin 0.14), 15k-particle star 0.38 -> 0.145 ms.
 struct BuildArgs {
   const double4* __restrict__ pos4;
-  int64_t n;
   const GridInfo* __restrict__ grid;
-  const uint32_t* __restrict__ perm;   // cell-sorted position -> particle index
-  const double4* __restrict__ pos_sorted;
-  const int2* __restrict__ cell_se;
   const int32_t* __restrict__ tile_start;
   const int32_t* __restrict__ tile_cnt;
+  const Box* __restrict__ tile_box;
+  const Box* __restrict__ sub_box;
+  const Box* __restrict__ super_box;
   const uint32_t* __restrict__ tile_uoff;
   int64_t capw, upool;
   int cap, ucap;
@@ -446,480 +505,398 @@ struct BuildArgs {
   DevStatus* status;
 };
 
-__device__ __forceinline__ double wave_min_d(double v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
-  return v;
-}
-__device__ __forceinline__ double wave_max_d(double v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
-}
-// min / max over aligned groups of 8 lanes
-__device__ __forceinline__ double grp8_min(double v) {
-  for (int off = 1; off < 8; off <<= 1) v = fmin(v, __shfl_xor(v, off, 64));
-  return v;
-}
-__device__ __forceinline__ double grp8_max(double v) {
-  for (int off = 1; off < 8; off <<= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
-}
-__device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v) {
-  for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off, 64);
-  return v;
-}
+constexpr float kListBand = 0x1p-17f;
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-struct TileState {
-  int64_t a;
-  int32_t a32;               // a as a 32-bit index (candidate indices are 32-bit), -1 if not valid
-  bool valid;
-  unsigned long long vmask;  // the wave's valid lanes
-  double xa, ya, za, ha;
-  double hs;                 // ha (1 + skin)(1 + 2^-40), the candidate test's scaled h
-  int usize, cnt, ucap;
-  int32_t* U;
-  uint16_t* row;             // the lane's staging row in LDS (8 entries of each of the L slots)
-  uint4* slot0;              // group 0 of the lane's first slot
-  int64_t gstride;           // groups between consecutive groups of one slot (capw * lanes)
-};
+__device__ __forceinline__ uint32_t dpp_or(uint32_t v) {   // OR over the wave, in lane 63
+#define SPH_DPP_OR(ctrl, rows) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, true)
+  SPH_DPP_OR(0x111, 0xf);   // row_shr 1, 2, 4, 8
+  SPH_DPP_OR(0x112, 0xf);
+  SPH_DPP_OR(0x114, 0xf);
+  SPH_DPP_OR(0x118, 0xf);
+  SPH_DPP_OR(0x142, 0xa);   // row_bcast 15, 31
+  SPH_DPP_OR(0x143, 0xc);
+#undef SPH_DPP_OR
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)dpp_or(v), 63); }
 
-// Candidate k of a particle goes to its slot k % L, as entry k / L (L = lanes per target of the
-// pair passes): each lane of the density pass then walks one contiguous slot list.  The lane's
-// LDS row holds 8 L consecutive candidates in arrival order (candidate k at k mod 8 L, so entry p
-// of slot s of the row's group sits at p L + s); when the row is full every slot has a complete
-// group of 8, and the row is stored as L groups (group g of slot s at g * capw * L + s), each
-// gathered from the row by byte permutes.  A row holds group g = k / (8 L) of every slot.
-template <int L>
-__device__ __forceinline__ void store_row_groups(const TileState& T, int g, int nslots) {
-  uint32_t D[4 * L];
-  __builtin_memcpy(D, T.row, sizeof(D));
+// exchanges the upper 32 lanes of a with the lower 32 lanes of b
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+// The operands of both 32-wide blocks from one particle per lane: 16 FP16 components k, of which
+// lane l < 32 of a block's operand holds 0..7 of the block's particle l and lane l >= 32 holds 8..15
+// of particle l - 32.  TARGET: the target's side (B), else the candidate's (A).
+template <bool TARGET>
+__device__ __forceinline__ void lift_operands(float x, float y, float z, float h, float w, f16x8 op[2]) {
+  const float s = TARGET ? 1.f : -2.f;
+  const float v[5] = {s * x, s * y, s * z, s * h, w};
+  _Float16 hi[5], lo[5];
 #pragma unroll
-  for (int s = 0; s < L; ++s) {
-    if (s >= nslots) break;
-    uint32_t w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if constexpr (L == 1) {
-        w[k] = D[k];
-      } else {
-        const int i0 = 2 * k * L + s, i1 = (2 * k + 1) * L + s;   // entries 2k, 2k+1 of slot s
-        const uint32_t sel = ((i0 & 1) ? 0x0302u : 0x0100u) | ((i1 & 1) ? 0x07060000u : 0x05040000u);
-        w[k] = __builtin_amdgcn_perm(D[i1 >> 1], D[i0 >> 1], sel);
-      }
-    }
-    T.slot0[(int64_t)g * T.gstride + s] = make_uint4(w[0], w[1], w[2], w[3]);
+  for (int d = 0; d < 5; ++d) {
+    hi[d] = (_Float16)v[d];
+    lo[d] = (_Float16)(v[d] - (float)hi[d]);
   }
-}
-template <int L>
-__device__ __forceinline__ void append_candidate(const BuildArgs& B, TileState& T, int loc) {
-  const unsigned k = (unsigned)T.cnt;
-  const uint16_t v = (uint16_t)loc;
-  __builtin_memcpy(T.row + (k & (8 * L - 1)), &v, sizeof(v));
-  ++T.cnt;
-  if ((k & (8 * L - 1)) == 8 * L - 1 && (int)(k / (8 * L)) * 8 < B.cap_sl) store_row_groups<L>(T, (int)(k / (8 * L)), L);
+  const _Float16 one = (_Float16)1.f;
+  _Float16 k[16];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {   // candidate (hi, hi, lo) by target (hi, lo, hi)
+    k[3 * d] = hi[d];
+    k[3 * d + 1] = TARGET ? lo[d] : hi[d];
+    k[3 * d + 2] = TARGET ? hi[d] : lo[d];
+  }
+  k[12] = TARGET ? one : hi[4];
+  k[13] = TARGET ? one : lo[4];
+  k[14] = TARGET ? hi[4] : one;
+  k[15] = TARGET ? lo[4] : one;
+  uint32_t a[4], b[4];
+  __builtin_memcpy(a, k, sizeof(a));
+  __builtin_memcpy(b, k + 8, sizeof(b));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) swap32(a[i], b[i]);
+  __builtin_memcpy(&op[0], a, sizeof(a));
+  __builtin_memcpy(&op[1], b, sizeof(b));
 }
 
-// candidate test (skin-widened, FP64) of every lane's target against batch candidates cb[0..nb),
-// nb <= 64; NB > 0 fixes nb at compile time (full batches).  The test is
-// r^2 < (h_a' + h_b')^2 with h' = h (1 + skin)(1 + 2^-40) (T.hs, cb[j].w) and r^2 by FMA: the
-// factor 1 + 2^-40 exceeds the few ulp by which this rounding can differ from the exact decision
-// of the density pass, so the candidates always contain every pair that test can accept (with a
-// positive skin the rebuild test's own margin of 1e-9 is larger still).
-// Candidates are taken one at a time: the wave's ballot decides at once whether candidate j joins
-// the union (as its next member), and the lanes that hit it append that local index, so the
-// lists come out ascending in local index and U in candidate order.
-template <int L, int NB, bool PER>
-__device__ __forceinline__ void run_batch(const BuildArgs& B, TileState& T, const double4* cb, const int32_t* cbi,
-                                          int nb, double box) {
-  const int lane = threadIdx.x;
-  unsigned long long um = 0ull;   // the batch's union members (wave-uniform)
-  int nm = 0;
-  // the lane's decision (hit) and the wave's mask of it, the mask from the compares themselves
-  // (ballot of the combined flag would first widen it to a vector register)
-  struct Hit { bool hit; unsigned long long m; };
-  auto test = [&](const double4& pb, int32_t bj) -> Hit {
-    const double dx = min_image(T.xa - pb.x, (int)PER, box), dy = min_image(T.ya - pb.y, (int)PER, box),
-                 dz = min_image(T.za - pb.z, (int)PER, box);
-    const double H = T.hs + pb.w;
-    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx)), H2 = H * H;
-    return Hit{T.valid && bj != T.a32 && r2 < H2,
-               __builtin_amdgcn_fcmp(r2, H2, 4 /* ordered less than */) &
-                   __builtin_amdgcn_uicmp(bj, T.a32, 33 /* not equal */) & T.vmask};
-  };
-  auto take = [&](int j, const Hit& t) {
-    const bool hit = t.hit;
-    if (t.m) {
-      um |= 1ull << j;
-      int loc = T.usize + nm;
-      ++nm;
-      loc = loc < T.ucap ? loc : T.ucap - 1;   // union overflow: keep reads in range, error latched
-      if (hit) append_candidate<L>(B, T, loc);
-    }
-  };
-  if constexpr (NB > 0) {
-    // the next candidate's record is read from LDS while this one is tested and appended
-    double4 nx = cb[0];
-    int32_t nbi = cbi[0];
-#pragma unroll 1
-    for (int jb = 0; jb < NB; jb += 8) {
+// A target's list in the making.  Candidate k of a particle goes to its slot k % L, as entry k / L
+// (L = lanes per target of the pair passes).  Hits wait in the lane's LDS ring of 64 entries in
+// arrival order; 8 L of them are one group of 8 entries of every slot, gathered from the ring by
+// byte permutes and stored as L 16-byte groups (group g of slot s at g * capw * L + s).
+constexpr int kRing = 64, kRingRow = 72;   // ring entries, and the padded row (16-byte aligned)
+template <int L>
+struct ListOut {
+  uint16_t* ring;
+  uint4* slot0;       // group 0 of the target's first slot
+  int64_t gstride;    // groups between consecutive groups of one slot (capw * L)
+  int cap_sl;
+  int cnt, stored;    // hits so far, groups stored
+  __device__ __forceinline__ void store_group(int nslots) {
+    uint32_t D[4 * L];
+    __builtin_memcpy(D, __builtin_assume_aligned(ring + ((8 * L * stored) & (kRing - 1)), 16), sizeof(D));
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const double4 pb = nx;
-        const int32_t bj = nbi;
-        if (jb + k + 1 < NB) {
-          nx = cb[jb + k + 1];
-          nbi = cbi[jb + k + 1];
+    for (int s = 0; s < L; ++s) {
+      if (s >= nslots) break;
+      uint32_t w[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (L == 1) {
+          w[k] = D[k];
+        } else {
+          const int i0 = 2 * k * L + s, i1 = (2 * k + 1) * L + s;   // entries 2k, 2k + 1 of slot s
+          const uint32_t sel = ((i0 & 1) ? 0x0302u : 0x0100u) | ((i1 & 1) ? 0x07060000u : 0x05040000u);
+          w[k] = __builtin_amdgcn_perm(D[i1 >> 1], D[i0 >> 1], sel);
         }
-        take(jb + k, test(pb, bj));
       }
+      if (stored * 8 < cap_sl) slot0[(int64_t)stored * gstride + s] = make_uint4(w[0], w[1], w[2], w[3]);
     }
-  } else {
-    for (int j = 0; j < nb; ++j) take(j, test(cb[j], cbi[j]));
+    ++stored;
   }
-  if (!um) return;
-  const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-  if ((um >> lane) & 1ull) {
-    const int loc = T.usize + __popcll(um & lt);
-    if (loc < T.ucap) T.U[loc] = cbi[lane];
+  // room for `more` entries in every lane's ring (the wave's complete groups are stored if not)
+  __device__ __forceinline__ void make_room(int more) {
+    if (__ballot(cnt - 8 * L * stored + more > kRing))
+      while (cnt - 8 * L * stored >= 8 * L) store_group(L);
   }
-  T.usize += nm;
-}
-
-// Geometry of one tile, shared by the cost and build kernels: whole-tile box and max h
-// (wave-uniform), and in LDS the sub-boxes of the 8 groups of 8 consecutive particles with their
-// own max h.  Candidates and cells are tested against the sub-boxes, which stays tight where a
-// tile mixes small and large h (a candidate within (h_a + h_b)(1 + skin) of a particle a is that
-// close to a's sub-box).
-struct TileGeom {
-  double lo[3], hi[3], hmx;
-};
-
-__device__ __forceinline__ void tile_geometry(const double4 pa, bool valid, TileGeom& G, double (*sub)[8]) {
-  const int lane = threadIdx.x;
-  const double big = 1e300;
-  const double q[3] = {pa.x, pa.y, pa.z};
-  for (int d = 0; d < 3; ++d) {
-    G.lo[d] = wave_min_d(valid ? q[d] : big);
-    G.hi[d] = wave_max_d(valid ? q[d] : -big);
+  // the lowest hit left in m, entry k: bit b is union member base + (members of um below b)
+  __device__ __forceinline__ void put(uint32_t& m, uint32_t um, int base, int last, int k) {
+    const int b = __builtin_ctz(m);
+    m &= m - 1;
+    int loc = base + __builtin_popcount(um & ((1u << b) - 1u));
+    loc = loc < last ? loc : last;   // union overflow: keep reads in range, error latched
+    const uint16_t v = (uint16_t)loc;
+    __builtin_memcpy(ring + (k & (kRing - 1)), &v, sizeof(v));
   }
-  G.hmx = wave_max_d(valid ? pa.w : 0.0);
-  double gl[3], gh[3];
-  for (int d = 0; d < 3; ++d) {
-    gl[d] = grp8_min(valid ? q[d] : big);
-    gh[d] = grp8_max(valid ? q[d] : -big);
-  }
-  const double gx = grp8_max(valid ? pa.w : 0.0);
-  __syncthreads();
-  if ((lane & 7) == 0) {
-    for (int d = 0; d < 3; ++d) {
-      sub[lane >> 3][d] = 0.5 * (gl[d] + gh[d]);
-      sub[lane >> 3][3 + d] = 0.5 * (gh[d] - gl[d]);
-    }
-    sub[lane >> 3][6] = gx;
-  }
-  __syncthreads();
-}
-
-// Cells of level l that can hold candidates of the tile: the tile box widened by
-// (hmx + hlev[l])(1 + skin), clipped to the cells that hold the level's particles.
-struct LevelBox {
-  int lo3[3], ext[3];
-  bool wrap[3];
-  int64_t total;
-  double c;
-  uint32_t base;
-};
-
-template <bool PER>
-__device__ __forceinline__ bool level_box(const GridInfo& g, int l, const TileGeom& G, double s1, LevelBox& L) {
-  if (!g.hlev_bits[l]) return false;   // no particles at this level
-  L.c = g.cell[l];
-  L.base = g.base[l];
-  const double R = (G.hmx + g.hlev[l]) * s1 * (1.0 + 1e-9);
-  for (int d = 0; d < 3; ++d) {
-    const int dim = g.dims[l][d];
-    int l0 = (int)floor((G.lo[d] - R - g.lo[d]) / L.c);
-    int h0 = (int)floor((G.hi[d] + R - g.lo[d]) / L.c);
-    L.wrap[d] = false;
-    if (PER) {
-      if (h0 - l0 + 1 >= dim) { l0 = 0; h0 = dim - 1; }
-      else L.wrap[d] = true;
+  // the hits of a batch: words m0 (members from base of u0) and m1 (after them, of u1); both words
+  // advance together where the ring holds them
+  __device__ __forceinline__ void append(uint32_t m0, uint32_t m1, uint32_t u0, uint32_t u1, int base, int last) {
+    const int n0 = __builtin_popcount(m0), nn = n0 + __builtin_popcount(m1), base1 = base + __builtin_popcount(u0);
+    make_room(nn);
+    if (!__ballot(cnt - 8 * L * stored + nn > kRing)) {
+      int k = cnt;
+      while (m0 | m1) {
+        if (m0) put(m0, u0, base, last, k);
+        if (m1) put(m1, u1, base1, last, k + n0);
+        ++k;
+      }
     } else {
-      const int b0 = cell_coord(dec_double(g.lev_lo[l][d]), g.lo[d], L.c, dim);
-      const int b1 = cell_coord(dec_double(g.lev_hi[l][d]), g.lo[d], L.c, dim);
-      l0 = l0 < b0 ? b0 : l0;
-      h0 = h0 > b1 ? b1 : h0;
+      make_room(n0);
+      for (int k = cnt; m0; ++k) put(m0, u0, base, last, k);
+      cnt += n0;
+      make_room(nn - n0);
+      for (int k = cnt; m1; ++k) put(m1, u1, base1, last, k);
+      cnt -= n0;
     }
-    L.lo3[d] = l0;
-    L.ext[d] = h0 >= l0 ? h0 - l0 + 1 : 0;
+    cnt += nn;
   }
-  L.total = (int64_t)L.ext[0] * L.ext[1] * L.ext[2];
-  return L.total > 0;
-}
+};
 
-// Particle range [s, e) of the cell with linear index j of the level box (empty if the cell is
-// farther than (hmax_g + hlev[l])(1 + skin) from every sub-box).  UNR: sub-boxes tested per
-// unrolled step (their LDS reads issued together; more registers).
-template <bool PER, int UNR>
-__device__ __forceinline__ void cell_range(const GridInfo& g, int l, const LevelBox& L, int64_t j, double s1,
-                                           const double (*sub)[8], const int2* __restrict__ cell_se, int& s, int& e) {
-  s = e = 0;
-  if (j >= L.total) return;
-  // the box holds at most 2^30 cells (10 bits per axis), so 32-bit index arithmetic suffices
-  const unsigned jj = (unsigned)j, e0 = (unsigned)L.ext[0], e1 = (unsigned)L.ext[1];
-  const unsigned j1 = jj / e0;
-  const int kk[3] = {L.lo3[0] + (int)(jj - j1 * e0), L.lo3[1] + (int)(j1 % e1), L.lo3[2] + (int)(j1 / e1)};
-  int cc[3];
-  double b0[3], b1[3];
-  bool gapd[3];
-  for (int d = 0; d < 3; ++d) {
-    gapd[d] = !PER || L.wrap[d];
-    b0[d] = g.lo[d] + kk[d] * L.c;
-    b1[d] = b0[d] + L.c;
-    const int dim = g.dims[l][d];
-    cc[d] = L.wrap[d] ? ((kk[d] % dim) + dim) % dim : kk[d];
-  }
-  bool need = false;
-#pragma unroll UNR
-  for (int gi = 0; gi < 8; ++gi) {
-    double gap2 = 0.0;
-    for (int d = 0; d < 3; ++d) {
-      const double gd = fmax(0.0, fmax(b0[d] - (sub[gi][d] + sub[gi][3 + d]), (sub[gi][d] - sub[gi][3 + d]) - b1[d]));
-      gap2 += gapd[d] ? gd * gd : 0.0;
-    }
-    const double Rg = (sub[gi][6] + g.hlev[l]) * s1 * (1.0 + 1e-9);
-    need |= gap2 < Rg * Rg && sub[gi][6] > 0.0;
-  }
-  if (need) {
-    const uint32_t key = L.base + (spread3((uint32_t)cc[0]) | (spread3((uint32_t)cc[1]) << 1) |
-                                   (spread3((uint32_t)cc[2]) << 2));
-    const int2 se = cell_se[key];
-    s = se.x;
-    e = se.y;
-  }
-}
-
-// Cost estimate of each tile: the number of particles in the cells its build would gather.
-template <bool PER>
-__global__ __launch_bounds__(64) void k_tile_cost(const double4* __restrict__ pos4, const GridInfo* __restrict__ gp,
-                                                  const int32_t* __restrict__ tile_start,
-                                                  const int32_t* __restrict__ tile_cnt, const int2* __restrict__ cell_se,
-                                                  int32_t* __restrict__ cost) {
-  __shared__ double sub[8][8];
-  const int lane = threadIdx.x;
-  const GridInfo& g = *gp;
-  const double s1 = 1.0 + g.skin;
-  const int64_t ntiles = g.ntiles;
-  for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
-    const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
-    if (t >= ntiles) break;
-    const bool valid = lane < tile_cnt[t];
-    const double4 pa = valid ? pos4[tile_start[t] + lane] : make_double4(0.0, 0.0, 0.0, 0.0);
-    TileGeom G;
-    tile_geometry(pa, valid, G, sub);
-    int64_t tot = 0;
-    for (int l = 0; l < g.nlev; ++l) {
-      LevelBox L;
-      if (!level_box<PER>(g, l, G, s1, L)) continue;
-      for (int64_t q = 0; q < L.total; q += 64) {
-        int s, e;
-        cell_range<PER, 4>(g, l, L, q + lane, s1, sub, cell_se, s, e);
-        tot += e - s;
-      }
-    }
-    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
-    if (lane == 0) cost[t] = (int32_t)(tot < 0x7fffffff ? tot : 0x7fffffff);
-    __syncthreads();
-  }
-}
-
-// Splits expensive tiles: a particle also starts a tile at every 16th (cost > kSplit16 / cdiv) or
-// 8th (cost > kSplit8 / cdiv) position of its tile.  The cost counts the particles of the cells a
-// build gathers, which shrinks with finer cells (cdiv cells per smoothing diameter).  Reads the
-// tile of p from the scan of the old flags.
-constexpr int32_t kSplit16 = 12000, kSplit8 = 40000;
-__global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
-                                                   int64_t n, const int32_t* __restrict__ tile_start,
-                                                   const int32_t* __restrict__ cost, int cdiv) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const uint32_t f = flag[p];
-  const int64_t t = (int64_t)idx[p] + f - 1;
-  const int32_t c = cost[t];
-  const int64_t off = p - tile_start[t];
-  const int size = c > kSplit8 / cdiv ? 8 : (c > kSplit16 / cdiv ? 16 : 64);
-  flag[p] = (f || (off % size) == 0) ? 1u : 0u;
-}
-
-// Tile neighbour lists.  Each tile is handled by one wavefront (one lane per target), in three
-// latency-friendly phases per block of 64 candidate cells:
-//  1. the 64 lanes take 64 cells of the level box at once, cull them against the sub-boxes and
-//     load their particle ranges;
-//  2. the wave gathers the cells' particles 64 at a time (a wave-wide prefix sum maps lanes to
-//     (cell, offset)), pre-tests each against the sub-boxes and appends survivors to an LDS batch;
-//  3. per batch of 64 candidates every lane runs the skin-widened FP64 test against all of them,
-//     building a 64-bit hit mask; the OR of the masks gives the batch's new union members (in
-//     candidate order) and each lane appends the local indices of its hits.
-// Tile t is particles [tile_start[t], tile_start[t] + tile_cnt[t]) of the array order (at most 64).
-// Candidates enter batches in a fixed order (level, cell, cell-sorted position), so U and the
-// lists are deterministic and each list is ascending in local index.
+constexpr int kRuns = 304;   // near runs collected before they are tested (12.5 KB of LDS: 13 waves a CU)
 template <bool PER, int NL>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_build_tiles(BuildArgs B) {
-  __shared__ int32_t c_s[64], c_o[64];
-  __shared__ double sub[8][8];   // per group of 8 tile particles: centre xyz, half-width xyz, max h
-  __shared__ double4 tp[16];     // the particles of a small tile (its exact pre-filter)
-  __shared__ double4 cb[128];
-  __shared__ int32_t cbi[128];
-  __shared__ __align__(16) uint16_t crow[64][8 * NL];   // per lane: staging of the candidate lists
+  __shared__ int32_t q_tile[128];        // ring: near tiles waiting for their runs to be tested
+  __shared__ int32_t q_run[kRuns];       // near runs: first particle ...
+  __shared__ uint8_t q_len[kRuns];       //   ... and length
+  __shared__ float4 own_c[8], own_w[8];  // the tile's own runs
+  __shared__ float4 cand[64];            // a batch's scaled coordinates, by bit of the masks (wide tiles)
+  uint32_t* self = reinterpret_cast<uint32_t*>(cand);   // then its candidate that is the lane's own particle
+  __shared__ __align__(16) uint16_t ring[64 * kRingRow];
   const int lane = threadIdx.x;
-  const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   const GridInfo& g = *B.grid;
-  const double box = g.box;
-  const double s1 = 1.0 + g.skin;
-  const double s1w = s1 * (1.0 + 0x1p-40);   // the batch test's widened factor
-  const int64_t ntiles = g.ntiles;
+  const double box = g.box, s1 = 1.0 + g.skin;
+  const float s1f = (float)s1 * (1.0f + 1e-5f), boxf = (float)box;
+  const int64_t ntiles = g.ntiles, ns = (ntiles + 63) / 64;
+  const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+  // candidate lane c of a batch is bit cbit of word cword of the masks (the order in which the
+  // products' rows come out)
+  const int cword = (lane >> 2) & 1, cbit = 16 * (lane >> 5) + 4 * ((lane >> 3) & 3) + (lane & 3);
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
     const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
     if (t >= ntiles) break;
-    const int32_t tcnt = B.tile_cnt[t];
-    const int64_t p = (int64_t)B.tile_start[t] + lane;
-    TileState T;
-    T.valid = lane < tcnt;
-    T.a = T.valid ? p : -1;
-    T.a32 = (int32_t)T.a;
-    T.vmask = __builtin_amdgcn_ballot_w64(T.valid);
-    const double4 pa = T.valid ? B.pos4[T.a] : make_double4(0.0, 0.0, 0.0, 0.0);
-    T.xa = pa.x; T.ya = pa.y; T.za = pa.z; T.ha = pa.w; T.hs = pa.w * s1w;
-    TileGeom G;
-    tile_geometry(pa, T.valid, G, sub);
-    if (lane < 16) tp[lane] = pa;
-    // small tiles (split because they are expensive) pre-filter candidates exactly against
-    // their own particles: far fewer batches, each of which would use only tcnt lanes
-    const bool small = tcnt <= 16;
+    const int32_t ts = B.tile_start[t], tcnt = B.tile_cnt[t];
+    const bool valid = lane < tcnt;
+    const int32_t a = ts + lane;
+    const double4 pa = valid ? B.pos4[a] : make_double4(0.0, 0.0, 0.0, 0.0);
+    const Box own = B.tile_box[t];
+    const int nown = (tcnt + 7) >> 3;
+    __syncthreads();
+    if (lane < nown) {
+      const Box b = B.sub_box[(ts >> 3) + t + lane];
+      own_c[lane] = b.c;
+      own_w[lane] = b.w;
+    }
+    __syncthreads();
     const uint32_t uoff = B.tile_uoff[t];
-    T.ucap = (int)((int64_t)tcnt * B.cap < B.ucap ? (int64_t)tcnt * B.cap : B.ucap);
-    if ((int64_t)uoff + T.ucap > B.upool) {
-      T.ucap = 0;
+    int ucap = (int)((int64_t)tcnt * B.cap < B.ucap ? (int64_t)tcnt * B.cap : B.ucap);
+    if ((int64_t)uoff + ucap > B.upool) {
+      ucap = 0;
       if (lane == 0) latch_error(B.status, SPH_E_NGB_CAPACITY, -1);
     }
-    T.U = B.tile_u + uoff;
-    T.usize = 0; T.cnt = 0;
-    T.row = crow[lane];
-    T.slot0 = reinterpret_cast<uint4*>(B.nbr16) + (T.valid ? p : 0) * NL;
-    T.gstride = B.capw * NL;
-    int pend = 0;   // candidates waiting in cb (wave-uniform)
-    for (int l = 0; l < g.nlev; ++l) {
-      LevelBox L;
-      if (!level_box<PER>(g, l, G, s1, L)) continue;
-      for (int64_t q = 0; q < L.total; q += 64) {
-        // phase 1: 64 cells at once; lanes take the block's cells in bit-reversed order so that
-        // consecutive union members come from all over the neighbourhood and every target's
-        // neighbours spread evenly over the LDS chunks of the pair passes
-        int s, e;
-        cell_range<PER, 2>(g, l, L, q + (int64_t)(__brev((unsigned)lane) >> 26), s1, sub, B.cell_se, s, e);
-        // wave prefix sum of the cells' particle counts
-        const int cntc = e - s;
-        int inc = cntc;
-        for (int off = 1; off < 64; off <<= 1) {
-          const int o = __shfl_up(inc, off, 64);
-          if (lane >= off) inc += o;
+    int32_t* U = B.tile_u + uoff;
+    const double c0 = g.org[0] + own.c.x, c1 = g.org[1] + own.c.y, c2 = g.org[2] + own.c.z;
+    const float rt2 = own.w.x * own.w.x + own.w.y * own.w.y + own.w.z * own.w.z;
+    const float sc = 100.f / (sqrtf(rt2) + 2.f * own.c.w * s1f + 1e-30f);
+    const float reach = (sqrtf(rt2) + own.c.w * s1f) * sc * (1.f + 1e-5f);
+    // scaled components; a lane without a (finite) particle, or with one out of every target's reach,
+    // never hits (w beyond any -h'^2); returns |x|^2 + h'^2, which must stay below kListMax in FP16
+    auto lift = [&](const double4& p, bool in, float& x, float& y, float& z, float& h, float& w) -> float {
+      x = (float)min_image(p.x - c0, (int)PER, box) * sc;
+      y = (float)min_image(p.y - c1, (int)PER, box) * sc;
+      z = (float)min_image(p.z - c2, (int)PER, box) * sc;
+      h = (float)(p.w * s1) * sc;
+      const float r2 = x * x + y * y + z * z, h2 = h * h, far = reach + h;
+      w = (r2 - h2) - kListBand * (r2 + h2);
+      if (!(in && r2 < far * far && h2 < 1e30f)) {   // (NaN fails too)
+        x = y = z = h = 0.f;
+        w = 60000.f;
+        return 0.f;
+      }
+      return r2 + h2;
+    };
+    constexpr float kListMax = 3e4f;
+    f16x8 T[2];
+    const float hmn = (float)wave_min_d(valid ? pa.w : 1e300);
+    const bool wide = rt2 > 64.f * hmn * hmn;
+    bool by_pair = false;
+    float tx, ty, tz, th;
+    {
+      float w;
+      const float m = lift(pa, valid, tx, ty, tz, th, w);
+      lift_operands<true>(tx, ty, tz, th, w, T);
+      by_pair = __ballot(m > kListMax) != 0ull;
+    }
+    if (PER) by_pair = by_pair || fmaxf(own.w.x, fmaxf(own.w.y, own.w.z)) + (own.c.w + (float)g.hmax) * s1f > 0.499f * boxf;
+    ListOut<NL> out;
+    out.ring = ring + kRingRow * lane;
+    out.slot0 = reinterpret_cast<uint4*>(B.nbr16) + (valid ? (int64_t)a : 0) * NL;
+    out.gstride = B.capw * NL;
+    out.cap_sl = B.cap_sl;
+    out.cnt = out.stored = 0;
+    int usize = 0;
+    // candidate of batch k of nb: its runs are k, k + nb, ... of those collected, lane / 8 the run and
+    // lane % 8 the particle.  A batch is thus spread over the whole neighbourhood and a target's hits
+    // come evenly from all batches (with neighbouring runs in one batch a target near them hits most
+    // of it, and the wave waits for the target with the most hits: 0.94 against 0.80 ms).
+    auto fetch = [&](int k, int nb, int nr, double4& pb) -> int32_t {
+      const int q = k + nb * (lane >> 3), r = lane & 7;
+      const bool in = k < nb && q < nr && r < (int)q_len[q < kRuns ? q : 0];
+      const int32_t b = in ? q_run[q] + r : -1;
+      pb = in ? B.pos4[b] : make_double4(0.0, 0.0, 0.0, 0.0);
+      return b;
+    };
+    auto batch = [&](int32_t b, const double4& pb) {
+      const bool in = b >= 0;
+      uint32_t m0, m1;
+      float x, y, z, h, w;
+      const float mag = lift(pb, in, x, y, z, h, w);
+      if (!by_pair && !__ballot(mag > kListMax)) {
+        f16x8 C[2];
+        lift_operands<false>(x, y, z, h, w, C);
+        uint32_t q[2];
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+          const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          const f32x16 D0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(C[0], T[tb], zero, 0, 0, 0);
+          const f32x16 D1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(C[1], T[tb], zero, 0, 0, 0);
+          uint32_t q0 = 0u, q1 = 0u;
+#pragma unroll
+          for (int e = 15; e >= 0; --e) {
+            q0 = __builtin_amdgcn_alignbit(q0, __float_as_uint(D0[e]), 31u);
+            q1 = __builtin_amdgcn_alignbit(q1, __float_as_uint(D1[e]), 31u);
+          }
+          q[tb] = q0 | (q1 << 16);
         }
-        const int Tc = __shfl(inc, 63, 64);
-        __syncthreads();
-        c_s[lane] = s;
-        c_o[lane] = inc - cntc;
-        __syncthreads();
-        // phase 2: gather candidates, 4 rounds of 64 per pass (loads of all 4 issued together),
-        // pre-test against the sub-boxes (small tiles: against their particles) and append the
-        // survivors to the batch in slot order
-        for (int q0 = 0; q0 < Tc; q0 += 256) {
-          double4 pbu[4];
-          int32_t bu[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int slot = q0 + 64 * u + lane;
-            pbu[u] = make_double4(0.0, 0.0, 0.0, 0.0);
-            bu[u] = -1;
-            if (slot < Tc) {
-              int lo_i = 0, hi_i = 63;   // last cell with c_o <= slot
-              while (lo_i < hi_i) {
-                const int mid = (lo_i + hi_i + 1) >> 1;
-                if (c_o[mid] <= slot) lo_i = mid;
-                else hi_i = mid - 1;
-              }
-              const int32_t sp = c_s[lo_i] + (slot - c_o[lo_i]);
-              bu[u] = (int32_t)B.perm[sp];
-              pbu[u] = B.pos_sorted[sp];
+        // lane l < 32 holds rows 8 i + j (upper lanes: 8 i + 4 + j) of targets l and 32 + l: each
+        // lane receives both halves of its own target
+        m0 = q[0];
+        m1 = q[1];
+        swap32(m0, m1);
+        if (wide && __ballot((m0 | m1) != 0u)) {
+          __syncthreads();
+          cand[32 * cword + cbit] = make_float4(x, y, z, h);
+          __syncthreads();
+          // coordinates rounded to FP32 (their differences to 2^-22 |x|, |x| < 2 sqrt(kListMax)): the
+          // support widened by 1e-5 and 1e-4 of the scaled unit holds every pair of the exact test
+          auto again = [&](uint32_t m, int word) -> uint32_t {
+            uint32_t keep = 0u;
+            while (m) {
+              const int b = __builtin_ctz(m);
+              m &= m - 1;
+              const float4 c = cand[32 * word + b];
+              const float dx = tx - c.x, dy = ty - c.y, dz = tz - c.z, H = (th + c.w) * (1.f + 1e-5f) + 2e-4f;
+              keep |= (dx * dx + dy * dy + dz * dz < H * H ? 1u : 0u) << b;
             }
-          }
-          // pre-test of the 4 rounds: each sub-box (particle) is read from LDS once for all 4
-          bool pass[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) pass[u] = false;
-          if (small) {
-            for (int k = 0; k < tcnt; ++k) {
-              const double4 q = tp[k];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const double4 pb = pbu[u];
-                pass[u] |= candidate_test(min_image(q.x - pb.x, (int)PER, box), min_image(q.y - pb.y, (int)PER, box),
-                                          min_image(q.z - pb.z, (int)PER, box), q.w, pb.w, s1);
-              }
-            }
-          } else {
-#pragma unroll 1
-            for (int gi = 0; gi < 8; ++gi) {
-              const double cx = sub[gi][0], cy = sub[gi][1], cz = sub[gi][2];
-              const double wx = sub[gi][3], wy = sub[gi][4], wz = sub[gi][5], hg = sub[gi][6];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const double4 pb = pbu[u];
-                const double ex = fmax(0.0, fabs(min_image(pb.x - cx, (int)PER, box)) - wx);
-                const double ey = fmax(0.0, fabs(min_image(pb.y - cy, (int)PER, box)) - wy);
-                const double ez = fmax(0.0, fabs(min_image(pb.z - cz, (int)PER, box)) - wz);
-                const double Rb = (hg + pb.w) * s1 * (1.0 + 1e-9);
-                pass[u] |= ex * ex + ey * ey + ez * ez < Rb * Rb && hg > 0.0;
-              }
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (q0 + 64 * u >= Tc) break;
-            const double4 pb = pbu[u];
-            pass[u] = pass[u] && bu[u] >= 0;
-            const unsigned long long m = __ballot(pass[u]);
-            if (pass[u]) {
-              const int k = pend + __popcll(m & lt);
-              cb[k] = make_double4(pb.x, pb.y, pb.z, pb.w * s1w);
-              cbi[k] = bu[u];
-            }
-            pend += __popcll(m);
-            __syncthreads();
-            if (pend >= 64) {   // phase 3 on a full batch
-              run_batch<NL, 64, PER>(B, T, cb, cbi, 64, box);
-              const int rest = pend - 64;
-              double4 mv = make_double4(0.0, 0.0, 0.0, 0.0);
-              int32_t mi = 0;
-              if (lane < rest) { mv = cb[64 + lane]; mi = cbi[64 + lane]; }
-              __syncthreads();
-              if (lane < rest) { cb[lane] = mv; cbi[lane] = mi; }
-              pend = rest;
-              __syncthreads();
-            }
-          }
+            return keep;
+          };
+          m0 = again(m0, 0);
+          m1 = again(m1, 1);
+        }
+      } else {
+        m0 = m1 = 0u;
+        for (int j = 0; j < 64; ++j) {
+          const double4 q = make_double4(__shfl(in ? pb.x : __builtin_nan(""), j, 64), __shfl(pb.y, j, 64),
+                                         __shfl(pb.z, j, 64), __shfl(pb.w, j, 64));
+          const double dx = min_image(pa.x - q.x, (int)PER, box), dy = min_image(pa.y - q.y, (int)PER, box),
+                       dz = min_image(pa.z - q.z, (int)PER, box);
+          const double H = (pa.w + q.w) * s1 * (1.0 + 0x1p-40);
+          const uint32_t bit = (valid && dx * dx + dy * dy + dz * dz < H * H ? 1u : 0u)
+                               << (16 * (j >> 5) + 4 * ((j >> 3) & 3) + (j & 3));
+          if ((j >> 2) & 1) m1 |= bit;
+          else m0 |= bit;
         }
       }
+      // a particle is not its own neighbour
+      const int ta = b - ts;   // the target this candidate is, if it is of the tile
+      if (__ballot(in && ta >= 0 && ta < tcnt)) {
+        __syncthreads();
+        self[lane] = 64u;
+        __syncthreads();
+        if (in && ta >= 0 && ta < tcnt) self[ta] = (uint32_t)(32 * cword + cbit);
+        __syncthreads();
+        const uint32_t sb = self[lane];
+        if (sb < 32u) m0 &= ~(1u << sb);
+        else if (sb < 64u) m1 &= ~(1u << (sb - 32u));
+      }
+      const uint32_t u0 = wave_or(m0), u1 = wave_or(m1);   // the batch's union members
+      if (!(u0 | u1)) return;
+      const int n0 = __builtin_popcount(u0);
+      {
+        const uint32_t uw = cword ? u1 : u0;
+        const int loc = usize + (cword ? n0 : 0) + __builtin_popcount(uw & ((1u << cbit) - 1u));
+        if (((uw >> cbit) & 1u) && loc < ucap) U[loc] = b;
+      }
+      const int last = ucap > 0 ? ucap - 1 : 0;
+      out.append(m0, m1, u0, u1, usize, last);
+      usize += n0 + __builtin_popcount(u1);
+    };
+    int nt = 0, ht = 0, nr = 0;      // tiles waiting (and the ring's head), runs collected (wave-uniform)
+    int64_t s0 = -64;                // first of the current 64 runs of 64 tiles, and those near
+    unsigned long long sm = 0ull;
+    bool more = true;
+    for (;;) {
+      if (nr > kRuns - 64 || (!more && nt == 0 && nr > 0)) {   // the batches of the collected runs
+        const int nb = (nr + 7) >> 3;
+        __syncthreads();
+        double4 p0;
+        int32_t b0 = fetch(0, nb, nr, p0);
+#pragma unroll 1
+        for (int k = 0; k < nb; ++k) {   // the next batch's loads are in flight
+          double4 p1;
+          const int32_t b1 = fetch(k + 1, nb, nr, p1);
+          batch(b0, p0);
+          p0 = p1;
+          b0 = b1;
+        }
+        nr = 0;
+        __syncthreads();
+        continue;
+      }
+      if (nt >= 8 || (!more && nt > 0)) {   // the runs of 8 tiles, against the tile's own runs
+        const int k = nt < 8 ? nt : 8;
+        const int gi = lane >> 3, r = lane & 7;
+        bool near = false;
+        int32_t first = 0, len = 0;
+        if (gi < k) {
+          const int32_t u = q_tile[(ht + gi) & 127];
+          first = B.tile_start[u] + 8 * r;
+          len = B.tile_cnt[u] - 8 * r;
+          len = len < 8 ? len : 8;
+          if (len > 0) {
+            const Box b = B.sub_box[((first - 8 * r) >> 3) + u + r];
+            for (int o = 0; o < nown; ++o) near = near || boxes_near<PER>(own_c[o], own_w[o], b.c, b.w, s1f, boxf);
+          }
+        }
+        const unsigned long long m = __ballot(near);
+        if (near) {
+          const int k2 = nr + __popcll(m & lt);
+          q_run[k2] = first;
+          q_len[k2] = (uint8_t)len;
+        }
+        nr += __popcll(m);
+        nt -= k;
+        ht += k;
+        __syncthreads();
+        continue;
+      }
+      if (sm) {   // the tiles of the next near run of 64
+        const int64_t u = (s0 + __builtin_ctzll(sm)) * 64 + lane;
+        sm &= sm - 1;
+        bool near = false;
+        if (u < ntiles) {
+          const Box b = B.tile_box[u];
+          near = boxes_near<PER>(own.c, own.w, b.c, b.w, s1f, boxf);
+        }
+        const unsigned long long m = __ballot(near);
+        if (near) q_tile[(ht + nt + __popcll(m & lt)) & 127] = (int32_t)u;
+        nt += __popcll(m);
+        __syncthreads();
+        continue;
+      }
+      if (!more) break;
+      s0 += 64;
+      if (s0 >= ns) {
+        more = false;
+        continue;
+      }
+      bool near = false;
+      if (s0 + lane < ns) {
+        const Box b = B.super_box[s0 + lane];
+        near = boxes_near<PER>(own.c, own.w, b.c, b.w, s1f, boxf);
+      }
+      sm = __ballot(near);
     }
-    if (pend > 0) run_batch<NL, 0, PER>(B, T, cb, cbi, pend, box);
-    __syncthreads();
-    if (T.valid && T.cnt <= B.cap && (T.cnt & (8 * NL - 1))) {
-      // the partly filled last row: slots s < r hold a partial last group g (a slot's count is at
-      // most that of slot 0, so the capacity test of slot 0 covers them all)
-      const int r = T.cnt & (8 * NL - 1), g = T.cnt / (8 * NL);
-      if ((T.cnt + NL - 1) / NL <= B.cap_sl) store_row_groups<NL>(T, g, r < NL ? r : NL);
+    // what is left in the rings: whole groups, then a partly filled last one (slots s < r of it
+    // hold entries; a slot's count is at most that of slot 0, whose capacity covers them all)
+    if (valid && out.cnt <= B.cap) {
+      while (out.cnt - 8 * NL * out.stored >= 8 * NL) out.store_group(NL);
+      const int r = out.cnt - 8 * NL * out.stored;
+      if (r > 0) out.store_group(r < NL ? r : NL);
     }
-    if (T.valid) B.count[p] = T.cnt < B.cap ? T.cnt : B.cap;
-    if (lane == 0) B.tile_usize[t] = T.usize < T.ucap ? T.usize : T.ucap;
-    if (T.usize > T.ucap || T.cnt > B.cap) latch_error(B.status, SPH_E_NGB_CAPACITY, (int)(T.valid ? T.a : -1));
+    if (valid) B.count[a] = out.cnt < B.cap ? out.cnt : B.cap;
+    if (lane == 0) B.tile_usize[t] = usize < ucap ? usize : ucap;
+    if (usize > ucap || out.cnt > B.cap) latch_error(B.status, SPH_E_NGB_CAPACITY, valid ? a : -1);
   }
 }
 
@@ -1007,11 +984,6 @@ static sph_status ensure_pool(sph_ctx* c) {
   return SPH_OK;
 }
 
-// Cells per smoothing diameter of the finest level (default 1: cells of 2 hmax_l).  Measured on
-// the 2M-particle star, 1 against 2 takes a list build from 6.2 to 5.3 ms (8x fewer cells to
-// cull, at 1.5x more particles to pre-test) and the FP32 step from 1.335 to 1.288 ms.
-static int cell_div_of(const sph_params& p) { return p.cell_div > 0 ? p.cell_div : 1; }
-
 static unsigned tile_grid(int64_t cap_tiles) {
   return (unsigned)(cap_tiles < 65536 ? cap_tiles : 65536);
 }
@@ -1068,35 +1040,37 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
     hipLaunchKernelGGL(k_pack_pos, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, st->h,
                        (const int32_t*)nullptr, (const StarInfo*)nullptr, n, c->pos4, (float4*)nullptr);
   }
-  // tile starts along the Morton order (the keys are overwritten by the cell sort below)
+  // tile table: Morton cuts, then tiles with many particles near them are split
   uint32_t* flag = reinterpret_cast<uint32_t*>(c->tmp);
   uint32_t* idx = flag + c->capw;
   hipLaunchKernelGGL(k_tile_flags, dim3(nb), dim3(kB), 0, s, c->keys, c->pos4, n, c->grid,
                      tile_cut_of(c->p), flag);
-  hipLaunchKernelGGL(k_level_hmax, dim3(nred), dim3(kB), 0, s, c->pos4, n, c->grid);
-  hipLaunchKernelGGL(k_grid_setup2, dim3(1), dim3(1), 0, s, c->grid, cell_div_of(c->p),
-                     c->max_cells, c->status);
-  hipLaunchKernelGGL(k_keys, dim3(nb), dim3(kB), 0, s, c->pos4, n, c->grid, c->keys, c->vals);
-  if ((e = sph_sort_pairs(c, c->keys, c->vals, n))) return e;
-  hipLaunchKernelGGL(k_cells_clear, dim3(2048), dim3(kB), 0, s, c->cell_se, c->grid);
-  hipLaunchKernelGGL(k_cell_ranges, dim3(nb), dim3(kB), 0, s, c->keys, n, c->cell_se);
-  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gather<double4>), dim3(nb), dim3(kB), 0, s, c->pos4, c->vals, n, c->pos_sorted);
-  // tile table: Morton cuts, then tiles whose candidate cells hold many particles are split
   const bool per = c->p.periodic != 0;
+  // FP32 pair sums keep the order of the cell grid's lists (see sph_cellgrid.hip)
+  const bool cells = c->p.precision == SPH_FP32;
+  const dim3 tgrid(tile_grid(c->cap_tiles));
+  if (cells && (e = grid_prepare(c, n))) return e;
   for (int pass = 0; pass < 2; ++pass) {
     if ((e = sph_scan_u32(c, flag, idx, n, &c->grid->ntiles))) return e;
     hipLaunchKernelGGL(k_tile_fill, dim3(nb), dim3(kB), 0, s, flag, idx, n, c->tile_start);
     hipLaunchKernelGGL(k_tile_len, dim3(grid_for(c->cap_tiles, kB)), dim3(kB), 0, s, c->grid, n, c->cap_tiles,
                        c->tile_start, c->tile_cnt, c->cap_s, c->ucap, c->tile_uoff);
+    if (cells) {
+      if (pass == 0 && (e = grid_split_tiles(c, n, flag, idx, tgrid.x))) return e;
+      continue;
+    }
+    hipLaunchKernelGGL(k_tile_boxes, tgrid, dim3(64), 0, s, c->grid, c->pos4, c->tile_start, c->tile_cnt, c->tile_box,
+                       c->sub_box);
+    hipLaunchKernelGGL(k_super_boxes, dim3((tgrid.x + 63) / 64), dim3(64), 0, s, c->grid, c->tile_box, c->super_box);
     if (pass == 1) break;
     if (per)
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<true>), dim3(tile_grid(c->cap_tiles)), dim3(64), 0, s, c->pos4,
-                         c->grid, c->tile_start, c->tile_cnt, c->cell_se, c->tile_usize);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<true>), tgrid, dim3(64), 0, s, c->grid, c->tile_cnt, c->tile_box,
+                         c->super_box, c->tile_usize);
     else
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<false>), dim3(tile_grid(c->cap_tiles)), dim3(64), 0, s, c->pos4,
-                         c->grid, c->tile_start, c->tile_cnt, c->cell_se, c->tile_usize);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<false>), tgrid, dim3(64), 0, s, c->grid, c->tile_cnt, c->tile_box,
+                         c->super_box, c->tile_usize);
     hipLaunchKernelGGL(k_tile_split, dim3(nb), dim3(kB), 0, s, flag, idx, n, c->tile_start, c->tile_usize,
-                       cell_div_of(c->p));
+                       c->keys, c->pos4, c->grid);
   }
   if ((e = sph_scan_u32(c, c->tile_uoff, c->tile_uoff, c->cap_tiles, &c->grid->upool_used))) return e;
   // stress-pass work list (tiles with a type-1 particle), read back with the pool size
@@ -1106,14 +1080,18 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   hipLaunchKernelGGL(k_stress_list, dim3(grid_for(c->cap_tiles, kB)), dim3(kB), 0, s, flag, idx, c->cap_tiles,
                      c->stress_tiles);
   if ((e = ensure_pool(c))) return e;
-  BuildArgs B;
-  B.pos4 = c->pos4; B.n = n; B.grid = c->grid; B.perm = c->vals; B.pos_sorted = c->pos_sorted;
-  B.cell_se = c->cell_se; B.capw = c->capw; B.cap = c->cap_s; B.ucap = c->ucap;
-  B.lanes = pass_lanes(c->p); B.cap_sl = cand_slot_capacity(c->cap_s, B.lanes);
-  B.tile_start = c->tile_start; B.tile_cnt = c->tile_cnt; B.tile_uoff = c->tile_uoff; B.upool = c->upool;
-  B.tile_u = c->tile_u; B.tile_usize = c->tile_usize; B.nbr16 = c->nbr16s; B.count = c->nbr_count_s;
-  B.status = c->status;
-  launch_build(B, per, dim3(tile_grid(c->cap_tiles)), s);
+  if (cells) {
+    if ((e = grid_build_lists(c, n, tgrid.x))) return e;
+  } else {
+    BuildArgs B;
+    B.pos4 = c->pos4; B.grid = c->grid; B.tile_box = c->tile_box; B.sub_box = c->sub_box; B.super_box = c->super_box;
+    B.capw = c->capw; B.cap = c->cap_s; B.ucap = c->ucap;
+    B.lanes = pass_lanes(c->p); B.cap_sl = cand_slot_capacity(c->cap_s, B.lanes);
+    B.tile_start = c->tile_start; B.tile_cnt = c->tile_cnt; B.tile_uoff = c->tile_uoff; B.upool = c->upool;
+    B.tile_u = c->tile_u; B.tile_usize = c->tile_usize; B.nbr16 = c->nbr16s; B.count = c->nbr_count_s;
+    B.status = c->status;
+    launch_build(B, per, tgrid, s);
+  }
   hipLaunchKernelGGL(k_tile_union_type, dim3(tile_grid(c->cap_tiles)), dim3(64), 0, s, c->grid, c->tile_start,
                      c->tile_cnt, c->tile_uoff, c->tile_usize, c->tile_u, st->type, c->tile_st);
   HIP_TRY(hipGetLastError());

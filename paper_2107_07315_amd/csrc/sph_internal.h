@@ -8,19 +8,21 @@
 
 #include "../../include/sph.h"
 
-#define SPH_MAX_LEV 4
 #define SPH_PI 3.14159265358979323846
 
-// Multi-level cell grid.  Particles are binned into levels by smoothing length
+// Global state of a list build: bounding box and h range of the particles, the skin in force, the
+// sizes of the tile table, and the multi-level cell grid of the FP32 runs: particles are binned into levels by smoothing length
 // (level l holds h in [hmin 2^l, hmin 2^(l+1)), the top level takes the rest); each level has
 // its own uniform grid whose cells are addressed by a Morton code inside a per-level block of
 // 2^(3 bits) entries starting at base[l].  All fields are computed on the device.
+#define SPH_MAX_LEV 4
 struct GridInfo {
   unsigned long long enc_lo[3], enc_hi[3];   // order-preserving encodings for atomics
   unsigned long long enc_hmin, enc_hmax;
   unsigned long long hlev_bits[SPH_MAX_LEV]; // max h per level (positive-double bits)
   unsigned long long lev_lo[SPH_MAX_LEV][3], lev_hi[SPH_MAX_LEV][3];  // per-level bounding boxes (encoded)
   double lo[3];
+  double org[3];        // origin of the FP32 bounding boxes (lo where finite)
   double hmin, hmax;
   double hlev[SPH_MAX_LEV];
   double cell[SPH_MAX_LEV];
@@ -34,6 +36,12 @@ struct GridInfo {
   uint32_t ntiles;      // tiles of the current array order (written on the device)
   uint32_t upool_used;  // union-pool entries reserved by the tiles
   uint32_t nstress;     // tiles holding a particle of type 1 (the stress pass's work list)
+};
+
+// Bounding box of a run of particles, relative to GridInfo::org, in FP32 rounded outward:
+// c = centre and largest h (negative: no particle), w = half-widths.
+struct Box {
+  float4 c, w;
 };
 
 // Per-star parameters of an ensemble (centre of the star's background, particle mass and
@@ -73,13 +81,6 @@ __device__ __forceinline__ uint32_t spread3(uint32_t v) {  // 10 bits -> every t
   return v;
 }
 
-__device__ __forceinline__ int particle_level(double h, const GridInfo& g) {
-  double ratio = h / g.hmin;
-  int l = 0;
-  while (l < g.nlev - 1 && ratio >= (double)(2 << l)) ++l;
-  return l;
-}
-
 // ---- geometry ---------------------------------------------------------------------------------
 template <typename R>
 __device__ __forceinline__ R min_image(R d, int periodic, R box) {
@@ -103,15 +104,6 @@ __device__ __forceinline__ bool neighbour_test(double dx, double dy, double dz, 
 __device__ __forceinline__ double pair_r2(double dx, double dy, double dz) {
 #pragma clang fp contract(off)
   return (dx * dx + dy * dy) + dz * dz;
-}
-
-// The same test against the skin-widened support (1 + s)(h_a + h_b); s1 = 1 + s.  With s = 0 it
-// is bit-identical to neighbour_test.
-__device__ __forceinline__ bool candidate_test(double dx, double dy, double dz, double ha, double hb, double s1) {
-#pragma clang fp contract(off)
-  double r2 = (dx * dx + dy * dy) + dz * dz;
-  double H = (ha + hb) * s1;
-  return r2 < H * H;
 }
 
 // Verlet-skin test: candidate lists built at positions/h `b` with skin s stay a superset of the
@@ -315,10 +307,15 @@ struct sph_ctx {
   double4* pos_build;   // x, y, z, h at the last candidate-list build
   // grid and sort
   GridInfo* grid;       // device
-  uint32_t *keys, *vals;  // cell-sorted keys and permutation (sorted position -> particle index)
+  uint32_t *keys, *vals;  // Morton keys and the permutation that sorts them
+  // cell grid (FP32 runs)
   int2* cell_se;        // per cell [start, end) in the cell-sorted order; cleared at every build
   int64_t max_cells;
-  double4* pos_sorted;  // x, y, z, h in the cell-sorted order (candidate gathers of the build)
+  double4* pos_sorted;  // x, y, z, h in the cell-sorted order
+  // boxes (FP64 runs)
+  Box* sub_box;         // per 8 consecutive particles of a tile, at (tile_start >> 3) + tile + k
+  Box* tile_box;
+  Box* super_box;       // per 64 consecutive tiles
   SortScratch sort;
   // tile neighbour lists: tile t = particles [tile_start[t], tile_start[t] + tile_cnt[t]) of the
   // array order (at most 64; the array is kept along the global Morton curve); U_t = tile_u +
@@ -407,6 +404,10 @@ sph_status sph_sort_pairs(sph_ctx* c, uint32_t* keys, uint32_t* vals, int64_t n)
 // outputs_recomputed: the outputs (D, rho, P, c_s, accelerations, du/dt, dS/dt) are recomputed
 // before they are next read, so they are not reordered
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed);
+// the cell grid of the FP32 runs: its tables, the tiles it splits, and the lists
+sph_status grid_prepare(sph_ctx* c, int64_t n);
+sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles);
+sph_status grid_build_lists(sph_ctx* c, int64_t n, unsigned tiles);
 sph_status launch_drift_check(sph_ctx* c, sph_state* st);
 sph_status launch_flag_clear(sph_ctx* c);
 sph_status launch_density(sph_ctx* c, sph_state* st);   // pair loop
