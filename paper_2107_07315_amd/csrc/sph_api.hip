@@ -157,7 +157,7 @@ void sph_destroy(sph_ctx* c) {
                   c->sort.hist, c->sort.rowtot, c->sort.partial, c->sort.scan_bsum, c->tile_u, c->tile_start, c->tile_cnt, c->tile_uoff,
                   c->tile_usize, c->stress_tiles, c->tile_st, c->nbr16, c->nbr_count, c->nbr_count_sl, c->nbr16s, c->nbr_count_s, c->pos_build, c->drift_flag,
                   c->pos4, c->fv, c->fa, c->sig, c->pos4f, c->fvf,
-                  c->faf, c->sigf, c->mu, c->Y0, c->B, c->sdot, c->tovf, c->half, c->tmp, c->stars, c->status,
+                  c->faf, c->sigf, c->mu, c->Y0, c->B, c->sdot, c->tovf, c->half, c->half_alt, c->tmp, c->stars, c->status,
                   c->dsum, c->dDdt, c->xcoef, c->dtw, c->dtpart, c->eos_list, c->eos_list_n};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -210,13 +210,13 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
       (e = dalloc(&c->sub_box, capw / 8 + capw + 8)) || (e = dalloc(&c->tile_box, capw)) ||
       (e = dalloc(&c->super_box, capw / 64 + 1)) ||
       (e = dalloc(&c->sort.keys_alt, cap)) || (e = dalloc(&c->sort.vals_alt, cap)) ||
-      (e = dalloc(&c->sort.hist, (size_t)256 * c->sort.max_blocks)) || (e = dalloc(&c->sort.rowtot, 256)) ||
+      (e = dalloc(&c->sort.hist, (size_t)256 * (c->sort.max_blocks > 128 ? c->sort.max_blocks : 128))) || (e = dalloc(&c->sort.rowtot, 256)) ||
       (e = dalloc(&c->sort.partial, (size_t)8 * 1024)) ||
       (e = dalloc(&c->tile_u, (size_t)c->upool)) || (e = dalloc(&c->tile_usize, c->cap_tiles)) ||
       (e = dalloc(&c->tile_start, c->cap_tiles)) || (e = dalloc(&c->tile_cnt, c->cap_tiles)) ||
       (e = dalloc(&c->stress_tiles, c->cap_tiles)) || (e = dalloc(&c->tile_st, c->cap_tiles)) ||
       (e = dalloc(&c->tile_uoff, c->cap_tiles)) ||
-      (e = dalloc(&c->sort.scan_bsum, c->sort.scan_cap + 1)) ||
+      (e = dalloc(&c->sort.scan_bsum, 2 * c->sort.scan_cap)) ||
       (e = dalloc(&c->nbr16, (size_t)capw * slot_entries_max(c->cap))) || (e = dalloc(&c->nbr_count, capw)) ||
       (e = dalloc(&c->nbr_count_sl, (size_t)capw * 4)) ||
       (e = dalloc(&c->nbr16s, (size_t)capw * (c->cap_s + 32))) || (e = dalloc(&c->nbr_count_s, capw)) ||
@@ -226,7 +226,8 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
       (e = dalloc(&c->faf, cap)) || (e = dalloc(&c->sigf, 6 * cap)) || (e = dalloc(&c->mu, cap)) ||
       (e = dalloc(&c->Y0, cap)) || (e = dalloc(&c->B, cap)) || (e = dalloc(&c->sdot, cap)) ||
       (e = dalloc(&c->tovf, cap)) ||
-      (e = dalloc(&c->half, SPH_HALF_FIELDS * cap)) || (e = dalloc(&c->tmp, capw)) || (e = dalloc(&c->status, 1)) ||
+      (e = dalloc(&c->half, SPH_HALF_FIELDS * cap)) ||
+      (e = dalloc(&c->half_alt, SPH_HALF_FIELDS * cap)) || (e = dalloc(&c->tmp, capw)) || (e = dalloc(&c->status, 1)) ||
       (e = dalloc(&c->dsum, cap)) || (e = dalloc(&c->dDdt, cap)) || (e = dalloc(&c->xcoef, 5 * cap)) ||
       (e = dalloc(&c->dtw, 8)) || (e = dalloc(&c->dtpart, 65536 + 4096)) || (e = dalloc(&c->eos_list, cap)) ||
       (e = dalloc(&c->eos_list_n, 1))) {

@@ -35,38 +35,64 @@ __device__ __forceinline__ bool candidate_test(double dx, double dy, double dz, 
 // Per level: largest h and the bounding box of the level's particles (a tile's search at a level
 // is clipped to that box, which keeps large-h tiles from enumerating the empty fine cells of
 // levels that only occupy the core).
+// Each thread keeps the extremes of its particles per level in registers, a wave combines them by
+// shuffles and one lane a block and level adds them to the grid with atomics (an LDS atomic for each
+// particle's seven values took 57 us at 1M particles).
 __global__ __launch_bounds__(kB) void k_level_hmax(const double4* __restrict__ pos4, int64_t n, GridInfo* g) {
-  __shared__ unsigned long long m[SPH_MAX_LEV];
-  __shared__ unsigned long long blo[SPH_MAX_LEV][3], bhi[SPH_MAX_LEV][3];
-  if (threadIdx.x < SPH_MAX_LEV) {
-    m[threadIdx.x] = 0ull;
-    for (int d = 0; d < 3; ++d) {
-      blo[threadIdx.x][d] = ~0ull;
-      bhi[threadIdx.x][d] = 0ull;
-    }
-  }
-  __syncthreads();
-  GridInfo G = *g;
-  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < n;
-       a += (int64_t)gridDim.x * blockDim.x) {
+  __shared__ unsigned long long red[kB / 64][SPH_MAX_LEV][7];
+  const GridInfo& G = *g;
+  const int nlev = G.nlev;
+  unsigned long long m[SPH_MAX_LEV][7];   // max h bits, low corner, high corner (encoded)
+#pragma unroll
+  for (int l = 0; l < SPH_MAX_LEV; ++l)
+#pragma unroll
+    for (int k = 0; k < 7; ++k) m[l][k] = k >= 1 && k < 4 ? ~0ull : 0ull;
+  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < n; a += (int64_t)gridDim.x * blockDim.x) {
     const double4 q = pos4[a];
-    const int l = particle_level(q.w, G);
-    atomicMax(&m[l], (unsigned long long)__double_as_longlong(q.w));
-    const double c[3] = {q.x, q.y, q.z};
-    for (int d = 0; d < 3; ++d) {
-      const unsigned long long e = enc_double(c[d]);
-      atomicMin(&blo[l][d], e);
-      atomicMax(&bhi[l][d], e);
+    const int lev = particle_level(q.w, G);
+    const unsigned long long hb = (unsigned long long)__double_as_longlong(q.w);
+    const unsigned long long e[3] = {enc_double(q.x), enc_double(q.y), enc_double(q.z)};
+#pragma unroll
+    for (int l = 0; l < SPH_MAX_LEV; ++l) {
+      if (l != lev) continue;
+      m[l][0] = hb > m[l][0] ? hb : m[l][0];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        m[l][1 + d] = e[d] < m[l][1 + d] ? e[d] : m[l][1 + d];
+        m[l][4 + d] = e[d] > m[l][4 + d] ? e[d] : m[l][4 + d];
+      }
+    }
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int l = 0; l < SPH_MAX_LEV; ++l) {
+    if (l >= nlev) break;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      unsigned long long v = m[l][k];
+      const bool lo = k >= 1 && k < 4;
+      for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(v, off, 64);
+        v = lo ? (o < v ? o : v) : (o > v ? o : v);
+      }
+      if (lane == 0) red[wave][l][k] = v;
     }
   }
   __syncthreads();
-  if (threadIdx.x < SPH_MAX_LEV && m[threadIdx.x]) {
-    const int l = threadIdx.x;
-    atomicMax(&g->hlev_bits[l], m[l]);
-    for (int d = 0; d < 3; ++d) {
-      atomicMin(&g->lev_lo[l][d], blo[l][d]);
-      atomicMax(&g->lev_hi[l][d], bhi[l][d]);
-    }
+  if ((int)threadIdx.x >= nlev * 7) return;
+  const int l = threadIdx.x / 7, k = threadIdx.x % 7;
+  const bool lo = k >= 1 && k < 4;
+  unsigned long long v = red[0][l][k];
+  for (int w = 1; w < kB / 64; ++w) {
+    const unsigned long long o = red[w][l][k];
+    v = lo ? (o < v ? o : v) : (o > v ? o : v);
+  }
+  if (k == 0) {
+    if (v) atomicMax(&g->hlev_bits[l], v);
+  } else if (lo) {
+    if (v != ~0ull) atomicMin(&g->lev_lo[l][k - 1], v);
+  } else if (v) {
+    atomicMax(&g->lev_hi[l][k - 4], v);
   }
 }
 
@@ -479,15 +505,28 @@ __global__ __launch_bounds__(64) void k_tile_cost(const double4* __restrict__ po
 constexpr int32_t kSplit16 = 12000, kSplit8 = 40000;
 __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
                                                    int64_t n, const int32_t* __restrict__ tile_start,
-                                                   const int32_t* __restrict__ cost, int cdiv) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const uint32_t f = flag[p];
-  const int64_t t = (int64_t)idx[p] + f - 1;
-  const int32_t c = cost[t];
-  const int64_t off = p - tile_start[t];
-  const int size = c > kSplit8 / cdiv ? 8 : (c > kSplit16 / cdiv ? 16 : 64);
-  flag[p] = (f || (off % size) == 0) ? 1u : 0u;
+                                                   const int32_t* __restrict__ cost, int cdiv,
+                                                   uint32_t* __restrict__ bsum) {
+  __shared__ uint32_t tot;
+  const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+  if (threadIdx.x == 0) tot = 0u;
+  __syncthreads();
+  uint32_t v = 0u;
+  for (int k = 0; k < 4; ++k) {
+    const int64_t p = p0 + k;
+    if (p >= n) break;
+    const uint32_t f = flag[p];
+    const int64_t t = (int64_t)idx[p] + f - 1;
+    const int32_t c = cost[t];
+    const int64_t off = p - tile_start[t];
+    const int size = c > kSplit8 / cdiv ? 8 : (c > kSplit16 / cdiv ? 16 : 64);
+    const uint32_t g = (f || (off % size) == 0) ? 1u : 0u;
+    flag[p] = g;
+    v += g;
+  }
+  atomicAdd(&tot, v);
+  __syncthreads();
+  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;   // starts per block of 1024 particles
 }
 
 // Tile neighbour lists.  Each tile is handled by one wavefront (one lane per target), in three
@@ -687,7 +726,7 @@ static void launch_build(const BuildArgs& B, bool per, dim3 grid, hipStream_t s)
 // Grid, cell-sorted order and cell ranges of the current pos4 (overwrites keys and vals).
 sph_status grid_prepare(sph_ctx* c, int64_t n) {
   hipStream_t s = c->stream;
-  const unsigned nb = grid_for(n, kB), nred = nb < 1024 ? nb : 1024;
+  const unsigned nb = grid_for(n, kB), nred = nb < 512 ? nb : 512;
   sph_status e;
   hipLaunchKernelGGL(k_level_hmax, dim3(nred), dim3(kB), 0, s, c->pos4, n, c->grid);
   hipLaunchKernelGGL(k_grid_setup2, dim3(1), dim3(1), 0, s, c->grid, cell_div_of(c->p),
@@ -701,16 +740,17 @@ sph_status grid_prepare(sph_ctx* c, int64_t n) {
   return SPH_OK;
 }
 
-// Marks the starts of the tiles that the cost estimate splits off in flag (idx: its scan so far).
-sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles) {
+// Marks the starts of the tiles that the cost estimate splits off in flag (idx: its scan so far);
+// bsum: the starts per block of 1024 particles.
+sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles, uint32_t* bsum) {
   if (c->p.periodic)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<true>), dim3(tiles), dim3(64), 0, c->stream, c->pos4, c->grid,
                        c->tile_start, c->tile_cnt, c->cell_se, c->tile_usize);
   else
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<false>), dim3(tiles), dim3(64), 0, c->stream, c->pos4, c->grid,
                        c->tile_start, c->tile_cnt, c->cell_se, c->tile_usize);
-  hipLaunchKernelGGL(k_tile_split, dim3(grid_for(n, kB)), dim3(kB), 0, c->stream, flag, idx, n, c->tile_start,
-                     c->tile_usize, cell_div_of(c->p));
+  hipLaunchKernelGGL(k_tile_split, dim3(grid_for(n, 1024)), dim3(kB), 0, c->stream, flag, idx, n, c->tile_start,
+                     c->tile_usize, cell_div_of(c->p), bsum);
   HIP_TRY(hipGetLastError());
   return SPH_OK;
 }

@@ -36,20 +36,20 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
 }
 
 // Bounding box and h range: one partial per block (8 encoded values), reduced in set-up.
-__global__ __launch_bounds__(kB) void k_bounds(const double4* __restrict__ pos4, int64_t n,
+__global__ __launch_bounds__(kB) void k_bounds(const double* __restrict__ x, const double* __restrict__ y,
+                                               const double* __restrict__ z, const double* __restrict__ h, int64_t n,
                                                unsigned long long* __restrict__ partial) {
   __shared__ unsigned long long red[4][8];
   unsigned long long v[8] = {~0ull, ~0ull, ~0ull, 0ull, 0ull, 0ull, ~0ull, 0ull};  // lo xyz, hi xyz, hmin, hmax
   for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < n;
        a += (int64_t)gridDim.x * blockDim.x) {
-    double4 p = pos4[a];
-    double q[3] = {p.x, p.y, p.z};
+    double q[3] = {x[a], y[a], z[a]};
     for (int d = 0; d < 3; ++d) {
       unsigned long long e = enc_double(q[d]);
       v[d] = e < v[d] ? e : v[d];
       v[3 + d] = e > v[3 + d] ? e : v[3 + d];
     }
-    unsigned long long e = enc_double(p.w);
+    unsigned long long e = enc_double(h[a]);
     v[6] = e < v[6] ? e : v[6];
     v[7] = e > v[7] ? e : v[7];
   }
@@ -121,52 +121,83 @@ __global__ __launch_bounds__(64) void k_grid_setup1(GridInfo* g, const unsigned 
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kB) void k_gather(const T* __restrict__ src, const uint32_t* __restrict__ perm,
-                                               int64_t n, T* __restrict__ dst) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[perm[i]];
-}
-
-// Several arrays of 8-byte elements at once: dst[k][i] = src[k][perm[i]] (gather) or
-// dst[k][i] = src[k][i] (copy) for k < na, the permutation read once per element.
-constexpr int kPermBatch = 16;
+// Reorders the particle arrays: a gather along the permutation into a staging area and a copy back,
+// every array of a batch in one launch each (the permutation is read once per particle, and a list
+// build at 20k particles is a chain of short launches: one pair instead of six took 40 us off it).
+// elem: bytes per element (8, 4 or 1).  crust: an array of type-1 particles only (S, dS/dt), which is 0
+// for the others: their old values are not read.
+constexpr int kPermMax = 48;
 struct PermBatch {
-  const double* src[kPermBatch];
-  double* dst[kPermBatch];
+  void* arr[kPermMax];
+  char* stage[kPermMax];
+  uint8_t elem[kPermMax], crust[kPermMax], back[kPermMax];   // back: copied back from the staging area
   int na;
+  const int8_t* type;       // before the permutation
 };
-template <bool GATHER>
-__global__ __launch_bounds__(kB) void k_permute_batch(PermBatch B, const uint32_t* __restrict__ perm, int64_t n) {
+__global__ __launch_bounds__(kB) void k_permute_gather(PermBatch B, const uint32_t* __restrict__ perm, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int64_t j = GATHER ? (int64_t)perm[i] : i;
-  for (int k = 0; k < B.na; ++k) B.dst[k][i] = B.src[k][j];
+  const int64_t j = (int64_t)perm[i];
+  const bool crust = B.type[j] == 1;
+  for (int k = 0; k < B.na; ++k) {
+    if (B.elem[k] == 8)
+      reinterpret_cast<double*>(B.stage[k])[i] =
+          B.crust[k] && !crust ? 0.0 : reinterpret_cast<const double*>(B.arr[k])[j];
+    else if (B.elem[k] == 4)
+      reinterpret_cast<int32_t*>(B.stage[k])[i] = reinterpret_cast<const int32_t*>(B.arr[k])[j];
+    else
+      reinterpret_cast<int8_t*>(B.stage[k])[i] = reinterpret_cast<const int8_t*>(B.arr[k])[j];
+  }
 }
-
+__global__ __launch_bounds__(kB) void k_permute_copy(PermBatch B, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  for (int k = 0; k < B.na; ++k) {
+    if (!B.back[k]) continue;
+    if (B.elem[k] == 8)
+      reinterpret_cast<double*>(B.arr[k])[i] = reinterpret_cast<const double*>(B.stage[k])[i];
+    else if (B.elem[k] == 4)
+      reinterpret_cast<int32_t*>(B.arr[k])[i] = reinterpret_cast<const int32_t*>(B.stage[k])[i];
+    else
+      reinterpret_cast<int8_t*>(B.arr[k])[i] = reinterpret_cast<const int8_t*>(B.stage[k])[i];
+  }
+}
 
 // pos4: absolute position and h (FP64 pair passes); pos4f: position relative to the
 // particle's star centre and h (FP32 pair passes keep full precision near each star).
+// After a reordering (pos_build != nullptr) it also keeps the positions and h of the build for the
+// skin test and clears the stress rates of the particles that are not of type 1.
 __global__ __launch_bounds__(kB) void k_pack_pos(const double* __restrict__ x, const double* __restrict__ y,
                                                  const double* __restrict__ z, const double* __restrict__ h,
                                                  const int32_t* __restrict__ star,
                                                  const StarInfo* __restrict__ stars, int64_t n,
-                                                 double4* __restrict__ pos4, float4* __restrict__ pos4f) {
+                                                 double4* __restrict__ pos4, float4* __restrict__ pos4f,
+                                                 double4* __restrict__ pos_build, const int8_t* __restrict__ type,
+                                                 double* __restrict__ dSdt, double* __restrict__ sdot) {
   int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= n) return;
   double cx = 0, cy = 0, cz = 0;
-  if (star && stars) {
+  if (pos4f && star && stars) {
     StarInfo s = stars[star[a]];
     cx = s.cx; cy = s.cy; cz = s.cz;
   }
-  pos4[a] = make_double4(x[a], y[a], z[a], h[a]);
-  if (pos4f) pos4f[a] = make_float4((float)(x[a] - cx), (float)(y[a] - cy), (float)(z[a] - cz), (float)(0.5 * h[a]));
+  const double4 q = make_double4(x[a], y[a], z[a], h[a]);
+  pos4[a] = q;
+  if (pos4f) pos4f[a] = make_float4((float)(q.x - cx), (float)(q.y - cy), (float)(q.z - cz), (float)(0.5 * q.w));
+  if (pos_build) {
+    pos_build[a] = q;
+    if (type[a] != 1) {
+      for (int c = 0; c < 6; ++c) dSdt[c * n + a] = 0.0;
+      sdot[a] = 0.0;
+    }
+  }
 }
 
 // Global Morton key of a 1024^3 grid over the bounding box: the particle arrays are kept in this
 // order (re-sorted every few steps), so any 64 consecutive particles form a compact tile whatever
 // the local density.
-__global__ __launch_bounds__(kB) void k_gkeys(const double4* __restrict__ pos4, int64_t n,
+__global__ __launch_bounds__(kB) void k_gkeys(const double* __restrict__ x, const double* __restrict__ y,
+                                              const double* __restrict__ z, int64_t n,
                                               const GridInfo* __restrict__ gp, uint32_t* __restrict__ keys,
                                               uint32_t* __restrict__ vals) {
   const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -178,9 +209,8 @@ __global__ __launch_bounds__(kB) void k_gkeys(const double4* __restrict__ pos4, 
     ext = e > ext ? e : ext;
   }
   const double sc = ext > 0.0 ? 1024.0 / ext : 0.0;
-  const double4 p = pos4[a];
   uint32_t k3[3];
-  const double q[3] = {p.x, p.y, p.z};
+  const double q[3] = {x[a], y[a], z[a]};
   for (int d = 0; d < 3; ++d) {
     int k = (int)floor((q[d] - g.lo[d]) * sc);
     k3[d] = (uint32_t)(k < 0 ? 0 : (k > 1023 ? 1023 : k));
@@ -205,31 +235,137 @@ __device__ __forceinline__ double morton_jump(const GridInfo& g, const uint32_t*
   const int lvl = x ? (31 - __clz(x)) / 3 : -1;
   return lvl >= 0 ? (double)(2 << lvl) * (ext / 1024.0) : 0.0;
 }
-__global__ __launch_bounds__(kB) void k_tile_flags(const uint32_t* __restrict__ gkeys, const double4* __restrict__ pos4,
-                                                   int64_t n, const GridInfo* __restrict__ gp, double cut,
-                                                   uint32_t* __restrict__ flag) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  flag[p] = ((p & 63) == 0 || morton_jump(*gp, gkeys, p) > cut * pos4[p].w) ? 1u : 0u;
+// Block-wide sums and exclusive scans over 1024 elements a block, 4 consecutive ones a thread
+// (256 threads): a count per block, scanned by k_scan_rows, then each element's index.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+  const int lane = threadIdx.x & 63;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(v, off, 64);
+    if (lane >= off) v += o;
+  }
+  return v;
+}
+__device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t& total) {
+  __shared__ uint32_t wsum[4];
+  const int wave = threadIdx.x >> 6;
+  const uint32_t inc = wave_inclusive_scan(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 63) wsum[wave] = inc;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += wsum[w];
+  total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  return before + inc - v;
 }
 
-// Work list of the stress pass: the tiles that hold a particle of type 1 (crust).  Breaking only
-// removes particles from the stressed set and type never changes, so the list stays a superset
-// until the next build.  Every other particle is of type 0, carries no deviatoric stress and has
-// zero stress rates, which k_zero_fluid_rates sets once per build (the kicks then skip the stress
-// arrays of type-0 particles; the rates of type-1 particles are written by the pass).
-__global__ __launch_bounds__(kB) void k_stress_flags(const GridInfo* __restrict__ gp, int64_t cap_tiles,
-                                                     const int32_t* __restrict__ tile_start,
-                                                     const int32_t* __restrict__ tile_cnt,
-                                                     const int8_t* __restrict__ type, uint32_t* __restrict__ flag) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= cap_tiles) return;
-  uint32_t f = 0u;
-  if (t < (int64_t)gp->ntiles) {
-    const int32_t s = tile_start[t], e = s + tile_cnt[t];
-    for (int32_t q = s; q < e; ++q) f |= type[q] == 1 ? 1u : 0u;
+// Start flags of the first cut, and their count per block.
+__global__ __launch_bounds__(kB) void k_tile_flags(const uint32_t* __restrict__ gkeys, const double* __restrict__ h,
+                                                   int64_t n, const GridInfo* __restrict__ gp, double cut,
+                                                   uint32_t* __restrict__ flag, uint32_t* __restrict__ bsum) {
+  const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+  uint32_t v = 0u;
+  for (int k = 0; k < 4; ++k) {
+    const int64_t p = p0 + k;
+    if (p >= n) break;
+    const uint32_t f = ((p & 63) == 0 || morton_jump(*gp, gkeys, p) > cut * h[p]) ? 1u : 0u;
+    flag[p] = f;
+    v += f;
   }
-  flag[t] = f;
+  uint32_t tot;
+  block_exclusive(v, tot);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+}
+
+// The index of each particle's flag (tiles started before it) and the tiles' first particles.
+__global__ __launch_bounds__(kB) void k_tile_starts(const uint32_t* __restrict__ flag, const uint32_t* __restrict__ boff,
+                                                    int64_t n, uint32_t* __restrict__ idx,
+                                                    int32_t* __restrict__ tile_start) {
+  const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+  uint32_t f[4], v = 0u, tot;
+  for (int k = 0; k < 4; ++k) {
+    f[k] = p0 + k < n ? flag[p0 + k] : 0u;
+    v += f[k];
+  }
+  uint32_t e = block_exclusive(v, tot) + boff[blockIdx.x];
+  for (int k = 0; k < 4; ++k) {
+    if (p0 + k >= n) break;
+    idx[p0 + k] = e;
+    if (f[k]) tile_start[e] = (int32_t)(p0 + k);
+    e += f[k];
+  }
+}
+
+__device__ __forceinline__ int32_t tile_length(const int32_t* __restrict__ tile_start, int64_t t, int64_t nt, int64_t n) {
+  return (int32_t)((t + 1 < nt ? (int64_t)tile_start[t + 1] : n) - tile_start[t]);
+}
+// tile lengths alone (the cell grid's first cut)
+__global__ __launch_bounds__(kB) void k_tile_len(const GridInfo* __restrict__ gp, int64_t n,
+                                                 const int32_t* __restrict__ tile_start, int32_t* __restrict__ tile_cnt) {
+  const int64_t nt = gp->ntiles;
+  for (int64_t t = (int64_t)blockIdx.x * kB + threadIdx.x; t < nt; t += (int64_t)gridDim.x * kB)
+    tile_cnt[t] = tile_length(tile_start, t, nt, n);
+}
+
+// The final tiles: each one's reservation in the union pool, min(ucap, cnt * cap) entries, and
+// whether it holds a particle of type 1 (crust).  Those tiles are the stress pass's work list:
+// breaking only removes particles from the stressed set and type never changes, so the list stays a
+// superset until the next build.  Every other particle is of type 0, carries no deviatoric stress and
+// has zero stress rates, set once per build (the kicks then skip the stress arrays of type-0
+// particles; the rates of type-1 particles are written by the pass).
+// One wave a tile finds the type, then both are summed and scanned 1024 tiles a block.
+__global__ __launch_bounds__(256) void k_tile_crust(const GridInfo* __restrict__ gp, int64_t n,
+                                                    const int32_t* __restrict__ tile_start,
+                                                    const int8_t* __restrict__ type, int32_t* __restrict__ tile_cnt,
+                                                    uint32_t* __restrict__ crust) {
+  const int64_t nt = gp->ntiles;
+  const int lane = threadIdx.x & 63;
+  for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < nt; t += (int64_t)gridDim.x * 4) {
+    const int32_t cnt = tile_length(tile_start, t, nt, n);
+    const unsigned long long m = __ballot(lane < cnt && type[tile_start[t] + lane] == 1);
+    if (lane == 0) {
+      tile_cnt[t] = cnt;
+      crust[t] = m ? 1u : 0u;
+    }
+  }
+}
+__device__ __forceinline__ uint32_t pool_share(int32_t cnt, int cap, int ucap) {
+  const int64_t b = (int64_t)cnt * cap;
+  return (uint32_t)(b < ucap ? b : ucap);
+}
+__global__ __launch_bounds__(kB) void k_tile_sums(const GridInfo* __restrict__ gp, const int32_t* __restrict__ tile_cnt,
+                                                  const uint32_t* __restrict__ crust, int cap, int ucap,
+                                                  uint32_t* __restrict__ bsum, int nb) {
+  const int64_t nt = gp->ntiles, t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+  uint32_t u = 0u, c = 0u, tot;
+  for (int k = 0; k < 4; ++k)
+    if (t0 + k < nt) {
+      u += pool_share(tile_cnt[t0 + k], cap, ucap);
+      c += crust[t0 + k];
+    }
+  block_exclusive(u, tot);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  block_exclusive(c, tot);
+  if (threadIdx.x == 0) bsum[nb + blockIdx.x] = tot;
+}
+__global__ __launch_bounds__(kB) void k_tile_offsets(const GridInfo* __restrict__ gp, const int32_t* __restrict__ tile_cnt,
+                                                     const uint32_t* __restrict__ crust, int cap, int ucap,
+                                                     const uint32_t* __restrict__ boff, int nb,
+                                                     uint32_t* __restrict__ uoff, int32_t* __restrict__ list) {
+  const int64_t nt = gp->ntiles, t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+  uint32_t u[4], c[4], su = 0u, sc = 0u, tot;
+  for (int k = 0; k < 4; ++k) {
+    u[k] = t0 + k < nt ? pool_share(tile_cnt[t0 + k], cap, ucap) : 0u;
+    c[k] = t0 + k < nt ? crust[t0 + k] : 0u;
+    su += u[k];
+    sc += c[k];
+  }
+  uint32_t eu = block_exclusive(su, tot) + boff[blockIdx.x], ec = block_exclusive(sc, tot) + boff[nb + blockIdx.x];
+  for (int k = 0; k < 4; ++k) {
+    if (t0 + k >= nt) break;
+    uoff[t0 + k] = eu;
+    eu += u[k];
+    if (c[k]) list[ec++] = (int32_t)(t0 + k);
+  }
 }
 // Per tile: whether one of its particles or of its union members is of type 1 (one wave a tile).
 __global__ __launch_bounds__(64) void k_tile_union_type(const GridInfo* __restrict__ gp, const int32_t* __restrict__ tile_start,
@@ -249,48 +385,6 @@ __global__ __launch_bounds__(64) void k_tile_union_type(const GridInfo* __restri
     if (lane == 0) flag[t] = m ? 1u : 0u;
   }
 }
-__global__ __launch_bounds__(kB) void k_stress_list(const uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
-                                                    int64_t cap_tiles, int32_t* __restrict__ list) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < cap_tiles && flag[t]) list[idx[t]] = (int32_t)t;
-}
-__global__ __launch_bounds__(kB) void k_zero_fluid_rates(const int8_t* __restrict__ type, int64_t n,
-                                                         double* __restrict__ S, double* __restrict__ dSdt,
-                                                         double* __restrict__ sdot) {
-  const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= n || type[a] == 1) return;
-  for (int c = 0; c < 6; ++c) {
-    S[c * n + a] = 0.0;   // fluid (type 0) carries no deviatoric stress
-    dSdt[c * n + a] = 0.0;
-  }
-  sdot[a] = 0.0;
-}
-
-__global__ __launch_bounds__(kB) void k_tile_fill(const uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
-                                                  int64_t n, int32_t* __restrict__ tile_start) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  if (flag[p]) tile_start[idx[p]] = (int32_t)p;
-}
-
-// tile lengths and each tile's reservation in the union pool: min(ucap, cnt * cap) entries
-__global__ __launch_bounds__(kB) void k_tile_len(const GridInfo* __restrict__ gp, int64_t n, int64_t cap_tiles,
-                                                 const int32_t* __restrict__ tile_start, int32_t* __restrict__ tile_cnt,
-                                                 int cap, int ucap, uint32_t* __restrict__ ub) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= cap_tiles) return;
-  const int64_t nt = gp->ntiles;
-  uint32_t v = 0;
-  if (t < nt) {
-    const int64_t e = t + 1 < nt ? tile_start[t + 1] : n;
-    const int32_t cnt = (int32_t)(e - tile_start[t]);
-    tile_cnt[t] = cnt;
-    const int64_t b = (int64_t)cnt * cap;
-    v = (uint32_t)(b < ucap ? b : ucap);
-  }
-  ub[t] = v;
-}
-
 // ---- bounding boxes ----------------------------------------------------------------------------
 __device__ __forceinline__ double wave_min_d(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
@@ -347,16 +441,22 @@ __device__ __forceinline__ bool boxes_near(const float4& ac, const float4& aw, c
   return gx * gx + gy * gy + gz * gz < R * R && bc.w > 0.f;
 }
 
-// Boxes of each tile and of its runs of 8 particles (one wave a tile).
+// Boxes of each tile and of its runs of 8 particles, and what k_tile_crust finds (one wave a tile).
 __global__ __launch_bounds__(64) void k_tile_boxes(const GridInfo* __restrict__ gp, const double4* __restrict__ pos4,
-                                                   const int32_t* __restrict__ tile_start,
-                                                   const int32_t* __restrict__ tile_cnt, Box* __restrict__ tile_box,
+                                                   int64_t n, const int32_t* __restrict__ tile_start,
+                                                   const int8_t* __restrict__ type, int32_t* __restrict__ tile_cnt,
+                                                   uint32_t* __restrict__ crust, Box* __restrict__ tile_box,
                                                    Box* __restrict__ sub_box) {
   const int lane = threadIdx.x;
   const GridInfo& g = *gp;
   const int64_t ntiles = g.ntiles;
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int32_t ts = tile_start[t], tc = tile_cnt[t];
+    const int32_t ts = tile_start[t], tc = tile_length(tile_start, t, ntiles, n);
+    const unsigned long long cm = __ballot(lane < tc && type[ts + lane] == 1);
+    if (lane == 0) {
+      tile_cnt[t] = tc;
+      crust[t] = cm ? 1u : 0u;
+    }
     const double4 p = lane < tc ? pos4[ts + lane] : make_double4(0.0, 0.0, 0.0, 0.0);
     const double q[3] = {p.x - g.org[0], p.y - g.org[1], p.z - g.org[2]};
     const bool in = lane < tc && isfinite(q[0]) && isfinite(q[1]) && isfinite(q[2]) && isfinite(p.w);
@@ -441,20 +541,29 @@ constexpr int32_t kSplit4 = 12000, kSplit2 = 18000, kSplitSmall = 65536;
 __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
                                                    int64_t n, const int32_t* __restrict__ tile_start,
                                                    const int32_t* __restrict__ cost, const uint32_t* __restrict__ gkeys,
-                                                   const double4* __restrict__ pos4, const GridInfo* __restrict__ gp) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const uint32_t f = flag[p];
-  if (f) return;
-  const int64_t t = (int64_t)idx[p] - 1;
-  const int32_t c = cost[t];
+                                                   const double4* __restrict__ pos4, const GridInfo* __restrict__ gp,
+                                                   uint32_t* __restrict__ bsum) {
+  const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
   const int32_t half = n <= kSplitSmall ? 2 : 1;
-  if (c <= kSplit4 / half) return;
-  const bool dear = c > kSplit2 / half;
-  // p > 0: particle 0 starts a tile
-  if ((dear && ((p - tile_start[t]) & 31) == 0) ||
-      morton_jump(*gp, gkeys, p) > (dear ? 2.0 : 4.0) * fmin(pos4[p].w, pos4[p - 1].w))
-    flag[p] = 1u;
+  uint32_t v = 0u, tot;
+  for (int k = 0; k < 4; ++k) {
+    const int64_t p = p0 + k;
+    if (p >= n) break;
+    bool f = flag[p] != 0u;
+    if (!f) {   // p > 0: particle 0 starts a tile
+      const int64_t t = (int64_t)idx[p] - 1;
+      const int32_t c = cost[t];
+      if (c > kSplit4 / half) {
+        const bool dear = c > kSplit2 / half;
+        f = (dear && ((p - tile_start[t]) & 31) == 0) ||
+            morton_jump(*gp, gkeys, p) > (dear ? 2.0 : 4.0) * fmin(pos4[p].w, pos4[p - 1].w);
+        if (f) flag[p] = 1u;
+      }
+    }
+    v += f ? 1u : 0u;
+  }
+  block_exclusive(v, tot);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
 // ---- candidate lists ---------------------------------------------------------------------------
@@ -919,40 +1028,41 @@ __global__ __launch_bounds__(kB) void k_count_stats(const int32_t* __restrict__ 
   }
 }
 
-// Permutes the 8-byte arrays arr[0, m) in place along c->vals: batches of up to kPermBatch go
-// through a staging area in one gather and one copy launch each.  The staging is the candidate-list
-// buffer, whose lists the build that follows rewrites (c->tmp, one array, where it is smaller).
-static sph_status permute_arrays(sph_ctx* c, double* const* arr, int m, int64_t n) {
-  if (n <= 0) return SPH_OK;
-  const size_t big = (size_t)c->capw * (size_t)(c->cap_s + 32) * sizeof(uint16_t);
-  double* stage = reinterpret_cast<double*>(c->nbr16s);
-  int per = (int)(big / (sizeof(double) * (size_t)n));
-  if (per < 1) { stage = c->tmp; per = 1; }
-  per = per < kPermBatch ? per : kPermBatch;
+// Permutes the state arrays in place along c->vals, as many at a time as the staging area holds: the
+// candidate-list buffer, whose lists the build that follows rewrites (c->tmp, one array, where that
+// is smaller).  type comes last: the crust arrays are gathered with its old order.
+struct PermArray {
+  void* p;
+  int elem;
+  bool crust;
+  void* to;   // gathered there for good (a second buffer), or nullptr: back into p
+};
+static sph_status permute_arrays(sph_ctx* c, const PermArray* A, int m, const int8_t* type, int64_t n) {
+  const size_t big = (size_t)c->capw * (size_t)(c->cap_s + 32) * sizeof(uint16_t), one = ((size_t)n * 8 + 255) & ~(size_t)255;
+  const bool fits = big >= one;
+  char* stage = fits ? reinterpret_cast<char*>(c->nbr16s) : reinterpret_cast<char*>(c->tmp);
+  const size_t room = fits ? big : (size_t)c->capw * 8;
   const unsigned nb = grid_for(n, kB);
-  for (int k0 = 0; k0 < m; k0 += per) {
-    PermBatch G{}, C{};
-    G.na = C.na = (m - k0) < per ? (m - k0) : per;
-    for (int k = 0; k < G.na; ++k) {
-      G.src[k] = arr[k0 + k];
-      G.dst[k] = stage + (int64_t)k * n;
-      C.src[k] = G.dst[k];
-      C.dst[k] = arr[k0 + k];
+  for (int k = 0; k < m;) {
+    PermBatch B{};
+    B.type = type;
+    size_t used = 0;
+    while (k < m && B.na < kPermMax) {
+      const size_t bytes = A[k].to ? 0 : ((size_t)n * A[k].elem + 255) & ~(size_t)255;
+      if (B.na > 0 && used + bytes > room) break;
+      B.arr[B.na] = A[k].p;
+      B.stage[B.na] = A[k].to ? (char*)A[k].to : stage + used;
+      B.back[B.na] = A[k].to ? 0 : 1;
+      B.elem[B.na] = (uint8_t)A[k].elem;
+      B.crust[B.na] = A[k].crust ? 1 : 0;
+      used += bytes;
+      ++B.na;
+      ++k;
     }
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_permute_batch<true>), dim3(nb), dim3(kB), 0, c->stream, G, c->vals, n);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_permute_batch<false>), dim3(nb), dim3(kB), 0, c->stream, C, c->vals, n);
+    hipLaunchKernelGGL(k_permute_gather, dim3(nb), dim3(kB), 0, c->stream, B, c->vals, n);
+    hipLaunchKernelGGL(k_permute_copy, dim3(nb), dim3(kB), 0, c->stream, B, n);
   }
   HIP_TRY(hipGetLastError());
-  return SPH_OK;
-}
-
-template <typename T>
-sph_status permute_array(sph_ctx* c, T* arr, int64_t n) {
-  if (!arr) return SPH_OK;
-  T* tmp = reinterpret_cast<T*>(c->tmp);
-  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gather<T>), dim3(grid_for(n, kB)), dim3(kB), 0, c->stream, arr,
-                     c->vals, n, tmp);
-  HIP_TRY(hipMemcpyAsync(arr, tmp, sizeof(T) * n, hipMemcpyDeviceToDevice, c->stream));
   return SPH_OK;
 }
 
@@ -968,6 +1078,8 @@ static sph_status ensure_pool(sph_ctx* c) {
   HIP_TRY(hipMemcpyAsync(c->drift_host, &c->grid->ntiles, 3 * sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   const uint32_t used = c->drift_host[1];
+  c->ntiles = c->drift_host[0];
+  c->nstress = c->drift_host[2];
   c->stress_heavy = 2ull * c->drift_host[2] > (unsigned long long)c->drift_host[0];
   if ((int64_t)used <= c->upool) return SPH_OK;
   int64_t want = (int64_t)used + (int64_t)used / 4;
@@ -986,6 +1098,14 @@ static sph_status ensure_pool(sph_ctx* c) {
 
 static unsigned tile_grid(int64_t cap_tiles) {
   return (unsigned)(cap_tiles < 65536 ? cap_tiles : 65536);
+}
+// A multiple of the XCD count.  An empty workgroup of the pair passes costs 0.2 ns of dispatch each:
+// 14 us a pass when a grid of 65536 is launched for no tile.
+unsigned tile_launch(const sph_ctx* c) {
+  const unsigned all = tile_grid(c->cap_tiles);
+  if (c->p.graph) return all;
+  const unsigned t = (c->ntiles + SPH_XCD - 1) / SPH_XCD * SPH_XCD;
+  return t < 1 ? SPH_XCD : (t < all ? t : all);
 }
 
 template <bool PER>
@@ -1009,79 +1129,94 @@ static void launch_build(const BuildArgs& B, bool per, dim3 grid, hipStream_t s)
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   const int64_t n = st->n;
   hipStream_t s = c->stream;
-  const unsigned nb = grid_for(n, kB);
+  const unsigned nb = grid_for(n, kB), nb4 = grid_for(n, 1024);
   unsigned nred = nb < 1024 ? nb : 1024;
   sph_status e;
-  hipLaunchKernelGGL(k_pack_pos, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, st->h,
-                     (const int32_t*)nullptr, (const StarInfo*)nullptr, n, c->pos4, (float4*)nullptr);
-  hipLaunchKernelGGL(k_bounds, dim3(nred), dim3(kB), 0, s, c->pos4, n, c->sort.partial);
+  hipLaunchKernelGGL(k_bounds, dim3(nred), dim3(kB), 0, s, st->x, st->y, st->z, st->h, n, c->sort.partial);
   hipLaunchKernelGGL(k_grid_setup1, dim3(1), dim3(64), 0, s, c->grid, c->sort.partial, (int)nred, c->p.periodic,
                      c->p.box, c->p.skin, c->status);
+  hipLaunchKernelGGL(k_gkeys, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, n, c->grid, c->keys, c->vals);
+  if ((e = sph_sort_pairs(c, c->keys, c->vals, n))) return e;
   {
-    hipLaunchKernelGGL(k_gkeys, dim3(nb), dim3(kB), 0, s, c->pos4, n, c->grid, c->keys, c->vals);
-    if ((e = sph_sort_pairs(c, c->keys, c->vals, n))) return e;
-    double* d64[64];
+    PermArray A[64];
     int m = 0;
-    for (double* a : {st->x, st->y, st->z, st->vx, st->vy, st->vz, st->u, st->h}) d64[m++] = a;
-    for (int k = 0; k < 6; ++k) d64[m++] = st->S + k * n;
+    for (double* a : {st->x, st->y, st->z, st->vx, st->vy, st->vz, st->u, st->h}) A[m++] = {a, 8, false, nullptr};
+    for (int k = 0; k < 6; ++k) A[m++] = {st->S + k * n, 8, true, nullptr};
     if (!outputs_recomputed) {
-      for (double* a : {st->D, st->rho, st->P, st->cs, st->ax, st->ay, st->az, st->dudt}) d64[m++] = a;
-      for (int k = 0; k < 6; ++k) d64[m++] = st->dSdt + k * n;
+      for (double* a : {st->D, st->rho, st->P, st->cs, st->ax, st->ay, st->az, st->dudt}) A[m++] = {a, 8, false, nullptr};
+      for (int k = 0; k < 6; ++k) A[m++] = {st->dSdt + k * n, 8, true, nullptr};
     } else {   // state that the next evaluation reads although it is an output
-      if (c->p.density_mode == SPH_DENS_CONTINUITY) d64[m++] = st->D;
-      if (c->p.dtP_mode == SPH_DTP_LAGGED) d64[m++] = st->P;
+      if (c->p.density_mode == SPH_DENS_CONTINUITY) A[m++] = {st->D, 8, false, nullptr};
+      if (c->p.dtP_mode == SPH_DTP_LAGGED) A[m++] = {st->P, 8, false, nullptr};
+      // the step's half-step copies, into their second buffer (outside a step nothing reads them)
+      for (int k = 0; k < SPH_HALF_FIELDS; ++k)
+        if (k < 10 || c->p.density_mode == SPH_DENS_CONTINUITY)
+          A[m++] = {c->half + (int64_t)k * c->capacity, 8, k >= 4 && k < 10, c->half_alt + (int64_t)k * c->capacity};
     }
-    for (int k = 0; k < SPH_HALF_FIELDS; ++k) d64[m++] = c->half + (int64_t)k * c->capacity;
-    if ((e = permute_arrays(c, d64, m, n))) return e;
-    if ((e = permute_array(c, st->type, n))) return e;
-    if ((e = permute_array(c, st->broken, n))) return e;
-    if ((e = permute_array(c, st->id, n))) return e;
-    if ((e = permute_array(c, st->star, n))) return e;
-    hipLaunchKernelGGL(k_pack_pos, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, st->h,
-                       (const int32_t*)nullptr, (const StarInfo*)nullptr, n, c->pos4, (float4*)nullptr);
+    A[m++] = {st->id, 4, false, nullptr};
+    if (st->star) A[m++] = {st->star, 4, false, nullptr};
+    A[m++] = {st->broken, 1, false, nullptr};
+    A[m++] = {st->type, 1, false, nullptr};
+    if ((e = permute_arrays(c, A, m, st->type, n))) return e;
+    if (outputs_recomputed) {
+      double* t = c->half;
+      c->half = c->half_alt;
+      c->half_alt = t;
+      ++c->graph_epoch;   // captured kicks hold the old buffer
+    }
+    hipLaunchKernelGGL(k_pack_pos, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, st->h, st->star, c->stars, n, c->pos4,
+                       c->p.precision == SPH_FP32 ? c->pos4f : nullptr, c->pos_build, st->type, st->dSdt, c->sdot);
   }
   // tile table: Morton cuts, then tiles with many particles near them are split
   uint32_t* flag = reinterpret_cast<uint32_t*>(c->tmp);
   uint32_t* idx = flag + c->capw;
-  hipLaunchKernelGGL(k_tile_flags, dim3(nb), dim3(kB), 0, s, c->keys, c->pos4, n, c->grid,
-                     tile_cut_of(c->p), flag);
+  uint32_t* bsum = c->sort.scan_bsum;
+  hipLaunchKernelGGL(k_tile_flags, dim3(nb4), dim3(kB), 0, s, c->keys, st->h, n, c->grid, tile_cut_of(c->p), flag, bsum);
   const bool per = c->p.periodic != 0;
   // FP32 pair sums keep the order of the cell grid's lists (see sph_cellgrid.hip)
   const bool cells = c->p.precision == SPH_FP32;
   const dim3 tgrid(tile_grid(c->cap_tiles));
-  if (cells && (e = grid_prepare(c, n))) return e;
-  for (int pass = 0; pass < 2; ++pass) {
-    if ((e = sph_scan_u32(c, flag, idx, n, &c->grid->ntiles))) return e;
-    hipLaunchKernelGGL(k_tile_fill, dim3(nb), dim3(kB), 0, s, flag, idx, n, c->tile_start);
-    hipLaunchKernelGGL(k_tile_len, dim3(grid_for(c->cap_tiles, kB)), dim3(kB), 0, s, c->grid, n, c->cap_tiles,
-                       c->tile_start, c->tile_cnt, c->cap_s, c->ucap, c->tile_uoff);
-    if (cells) {
-      if (pass == 0 && (e = grid_split_tiles(c, n, flag, idx, tgrid.x))) return e;
-      continue;
-    }
-    hipLaunchKernelGGL(k_tile_boxes, tgrid, dim3(64), 0, s, c->grid, c->pos4, c->tile_start, c->tile_cnt, c->tile_box,
-                       c->sub_box);
-    hipLaunchKernelGGL(k_super_boxes, dim3((tgrid.x + 63) / 64), dim3(64), 0, s, c->grid, c->tile_box, c->super_box);
-    if (pass == 1) break;
+  auto starts = [&] {
+    sph_scan_rows(c, bsum, (int)nb4, &c->grid->ntiles);
+    hipLaunchKernelGGL(k_tile_starts, dim3(nb4), dim3(kB), 0, s, flag, bsum, n, idx, c->tile_start);
+  };
+  uint32_t* crust = c->tile_st;   // until the build marks the tiles' unions there
+  if (cells) {
+    starts();
+    hipLaunchKernelGGL(k_tile_len, dim3(tgrid.x < 1024 ? tgrid.x : 1024), dim3(kB), 0, s, c->grid, n, c->tile_start,
+                       c->tile_cnt);
+    if ((e = grid_prepare(c, n)) || (e = grid_split_tiles(c, n, flag, idx, tgrid.x, bsum))) return e;
+    starts();
+    hipLaunchKernelGGL(k_tile_crust, dim3(tgrid.x < 16384 ? tgrid.x : 16384), dim3(256), 0, s, c->grid, n, c->tile_start,
+                       st->type, c->tile_cnt, crust);
+  } else {
+    auto boxes = [&] {
+      hipLaunchKernelGGL(k_tile_boxes, tgrid, dim3(64), 0, s, c->grid, c->pos4, n, c->tile_start, st->type, c->tile_cnt,
+                         crust, c->tile_box, c->sub_box);
+      hipLaunchKernelGGL(k_super_boxes, dim3((tgrid.x + 63) / 64), dim3(64), 0, s, c->grid, c->tile_box, c->super_box);
+    };
+    starts();
+    boxes();
     if (per)
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<true>), tgrid, dim3(64), 0, s, c->grid, c->tile_cnt, c->tile_box,
                          c->super_box, c->tile_usize);
     else
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<false>), tgrid, dim3(64), 0, s, c->grid, c->tile_cnt, c->tile_box,
                          c->super_box, c->tile_usize);
-    hipLaunchKernelGGL(k_tile_split, dim3(nb), dim3(kB), 0, s, flag, idx, n, c->tile_start, c->tile_usize,
-                       c->keys, c->pos4, c->grid);
+    hipLaunchKernelGGL(k_tile_split, dim3(nb4), dim3(kB), 0, s, flag, idx, n, c->tile_start, c->tile_usize,
+                       c->keys, c->pos4, c->grid, bsum);
+    starts();
+    boxes();
   }
-  if ((e = sph_scan_u32(c, c->tile_uoff, c->tile_uoff, c->cap_tiles, &c->grid->upool_used))) return e;
-  // stress-pass work list (tiles with a type-1 particle), read back with the pool size
-  hipLaunchKernelGGL(k_stress_flags, dim3(grid_for(c->cap_tiles, kB)), dim3(kB), 0, s, c->grid, c->cap_tiles,
-                     c->tile_start, c->tile_cnt, st->type, flag);
-  if ((e = sph_scan_u32(c, flag, idx, c->cap_tiles, &c->grid->nstress))) return e;
-  hipLaunchKernelGGL(k_stress_list, dim3(grid_for(c->cap_tiles, kB)), dim3(kB), 0, s, flag, idx, c->cap_tiles,
-                     c->stress_tiles);
-  if ((e = ensure_pool(c))) return e;
+  // reservations in the union pool and the stress pass's work list; sizes read back with them
+  hipLaunchKernelGGL(k_tile_sums, dim3(nb4), dim3(kB), 0, s, c->grid, c->tile_cnt, crust, c->cap_s, c->ucap, bsum, (int)nb4);
+  sph_scan_rows(c, bsum, (int)nb4, &c->grid->upool_used, 2);
+  hipLaunchKernelGGL(k_tile_offsets, dim3(nb4), dim3(kB), 0, s, c->grid, c->tile_cnt, crust, c->cap_s, c->ucap, bsum,
+                     (int)nb4, c->tile_uoff, c->stress_tiles);
+  HIP_TRY(hipGetLastError());
+  if ((e = ensure_pool(c))) return e;   // also brings the number of tiles
   if (cells) {
-    if ((e = grid_build_lists(c, n, tgrid.x))) return e;
+    if ((e = grid_build_lists(c, n, tile_launch(c)))) return e;
   } else {
     BuildArgs B;
     B.pos4 = c->pos4; B.grid = c->grid; B.tile_box = c->tile_box; B.sub_box = c->sub_box; B.super_box = c->super_box;
@@ -1090,17 +1225,12 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
     B.tile_start = c->tile_start; B.tile_cnt = c->tile_cnt; B.tile_uoff = c->tile_uoff; B.upool = c->upool;
     B.tile_u = c->tile_u; B.tile_usize = c->tile_usize; B.nbr16 = c->nbr16s; B.count = c->nbr_count_s;
     B.status = c->status;
-    launch_build(B, per, tgrid, s);
+    launch_build(B, per, dim3(tile_launch(c)), s);
   }
-  hipLaunchKernelGGL(k_tile_union_type, dim3(tile_grid(c->cap_tiles)), dim3(64), 0, s, c->grid, c->tile_start,
+  hipLaunchKernelGGL(k_tile_union_type, dim3(tile_launch(c)), dim3(64), 0, s, c->grid, c->tile_start,
                      c->tile_cnt, c->tile_uoff, c->tile_usize, c->tile_u, st->type, c->tile_st);
   HIP_TRY(hipGetLastError());
-  // the zero rates of every type-0 particle
-  hipLaunchKernelGGL(k_zero_fluid_rates, dim3(grid_for(n, kB)), dim3(kB), 0, s, st->type, n, st->S, st->dSdt,
-                     c->sdot);
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(c->pos_build, c->pos4, sizeof(double4) * n, hipMemcpyDeviceToDevice, s));
-  return launch_pack(c, st);
+  return SPH_OK;
 }
 
 // Skin test of the current positions and h against the last build (for sph_build_cells; inside
@@ -1111,12 +1241,16 @@ __global__ __launch_bounds__(kB) void k_drift_check(const double* __restrict__ x
                                                     const GridInfo* __restrict__ gp, uint32_t id,
                                                     uint32_t* __restrict__ flag) {
   const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= n) return;
-  const GridInfo& g = *gp;
-  const double4 b = pb[a];
-  if (skin_exceeded(min_image(x[a] - b.x, g.periodic, g.box), min_image(y[a] - b.y, g.periodic, g.box),
-                    min_image(z[a] - b.z, g.periodic, g.box), h[a], b, g.skin))
-    atomicMax(flag, id);
+  bool out = false;
+  if (a < n) {
+    const GridInfo& g = *gp;
+    const double4 b = pb[a];
+    out = skin_exceeded(min_image(x[a] - b.x, g.periodic, g.box), min_image(y[a] - b.y, g.periodic, g.box),
+                        min_image(z[a] - b.z, g.periodic, g.box), h[a], b, g.skin);
+  }
+  // one plain store a workgroup, all of the same value: after a new snapshot every particle is out, and
+  // an atomic for each took 183 us at 1M particles
+  if (__syncthreads_or(out) && threadIdx.x == 0) *flag = id;
 }
 
 sph_status launch_drift_check(sph_ctx* c, sph_state* st) {
@@ -1130,7 +1264,8 @@ sph_status launch_drift_check(sph_ctx* c, sph_state* st) {
 sph_status launch_pack(sph_ctx* c, sph_state* st) {
   const int64_t n = st->n;
   hipLaunchKernelGGL(k_pack_pos, dim3(grid_for(n, kB)), dim3(kB), 0, c->stream, st->x, st->y, st->z, st->h,
-                     st->star, c->stars, n, c->pos4, c->p.precision == SPH_FP32 ? c->pos4f : nullptr);
+                     st->star, c->stars, n, c->pos4, c->p.precision == SPH_FP32 ? c->pos4f : nullptr, nullptr, nullptr, nullptr,
+                     nullptr);
   HIP_TRY(hipGetLastError());
   return SPH_OK;
 }

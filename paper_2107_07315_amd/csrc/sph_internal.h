@@ -355,7 +355,8 @@ struct sph_ctx {
   double *mu, *Y0, *B, *sdot;
   double4* tovf;        // per particle: fixed-background force coefficients (k_P, B_x, B_y, B_z)
   // half-step copies for kick-drift-kick
-  double* half;         // 10*cap: vx, vy, vz, u, S[6]
+  double* half;         // SPH_HALF_FIELDS * cap: vx, vy, vz, u, S[6], D
+  double* half_alt;     // where a list build inside a step gathers them (the two change places)
   double* tmp;          // permutation staging, 8 bytes * cap
   // ensemble
   StarInfo* stars;      // device, may be null
@@ -389,6 +390,7 @@ struct sph_ctx {
   int32_t* eos_list;    // particles the EoS network serves in the current evaluation (split epilogue)
   int32_t* eos_list_n;
   int eos_blocks;       // blocks of that epilogue that wrote dtpart (0: none)
+  uint32_t ntiles, nstress;   // tiles and stress tiles of the last build
   bool stress_heavy;    // more than half of the tiles hold a type-1 particle (last list build)
   int64_t steps_done;   // steps completed since sph_create (slot bookkeeping of the Courant steps)
   bool adaptive;        // inside an sph_step call with Courant steps
@@ -406,7 +408,8 @@ sph_status sph_sort_pairs(sph_ctx* c, uint32_t* keys, uint32_t* vals, int64_t n)
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed);
 // the cell grid of the FP32 runs: its tables, the tiles it splits, and the lists
 sph_status grid_prepare(sph_ctx* c, int64_t n);
-sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles);
+sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles,
+                            uint32_t* bsum);
 sph_status grid_build_lists(sph_ctx* c, int64_t n, unsigned tiles);
 sph_status launch_drift_check(sph_ctx* c, sph_state* st);
 sph_status launch_flag_clear(sph_ctx* c);
@@ -440,7 +443,11 @@ sph_status sph_count_stats(sph_ctx* c, sph_list_stats* out);
 // looks up (once per device, with that device current) the device address of the statistics
 // scratch array and stores it in the context
 sph_status stats_scratch_init(sph_ctx* c);
-sph_status sph_scan_u32(sph_ctx* c, const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total);
+// exclusive prefix sums of `rows` consecutive rows of nb values, in place; total[r] (device) = row r's sum
+void sph_scan_rows(sph_ctx* c, uint32_t* v, int nb, uint32_t* total, int rows = 1);
+// workgroups of a launch with one per tile (they loop over more): the tiles of the last build, or,
+// under graph replay, whose captured launches outlive a build, what the capacity allows
+unsigned tile_launch(const sph_ctx* c);
 struct MlpView;
 bool mlp_view(const sph_ctx* c, MlpView* v);   // false if no trained network is loaded
 void mlp_free(sph_ctx* c);

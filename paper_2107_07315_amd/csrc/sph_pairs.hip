@@ -1305,7 +1305,7 @@ static dim3 pass_grid(const sph_ctx* c) {
     const int64_t b = ((int64_t)c->p.pass_blocks + SPH_XCD - 1) / SPH_XCD * SPH_XCD;
     return dim3((unsigned)(b < 65536 ? b : 65536));
   }
-  return dim3((unsigned)(c->cap_tiles < 65536 ? c->cap_tiles : 65536));
+  return dim3(tile_launch(c));
 }
 
 // Calls f(L) with the pair passes' lanes per target as a compile-time constant.
@@ -1431,7 +1431,9 @@ sph_status launch_eos(sph_ctx* c, sph_state* st) {
 
 sph_status launch_stress(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
-  const dim3 g((unsigned)(c->cap_tiles < 4096 ? c->cap_tiles : 4096));   // loops over the work list
+  // loops over the work list
+  const unsigned most = (unsigned)(c->cap_tiles < 4096 ? c->cap_tiles : 4096);
+  const dim3 g(c->p.graph || c->nstress > most ? most : (c->nstress > 0 ? c->nstress : 1u));
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
     dispatch_lanes(pass_lanes(c->p), [&](auto LL) {
       constexpr int KER = decltype(K)::value;
