@@ -29,9 +29,8 @@ sys.path.insert(0, ROOT)
 # Algorithmic HBM bytes: lists at 2 B per entry plus each particle's own records read and results
 # written once (density: FP64 position 32, candidate count 4, D 8, exact counts 8 = 52 B);
 # neighbour records staged through LDS are re-reads served by the caches and are not counted.
-# FP64: the density pass reads the candidate lists and writes the exact lists, the force pass
-# reads the exact lists.  FP32: both passes read the candidate lists (the force terms vanish
-# beyond the support) and no exact list is written.
+# Both passes read the candidate lists (the force terms vanish beyond the support); no exact list is
+# written.
 # The survey's algorithmic figures per particle-update (its work-per-pass table: density with its
 # EoS epilogue about 32 FLOP per pair at about 100 pairs, forces with the background epilogue
 # about 63 FLOP per pair plus the crust terms, about 6.5 kFLOP; bytes 104 / 114 per particle in
@@ -40,8 +39,8 @@ SURVEY_FLOP = {"density": 3200, "forces": 6500}
 SURVEY_BYTES = {("density", "FP64"): 104, ("density", "FP32"): 80, ("forces", "FP64"): 114, ("forces", "FP32"): 70}
 DENS_FLOP = {"candidate": 10, "pair": 20, "particle": 12}
 FORCE_FLOP = {"pair": 73, "particle": 110}
-DENS_BYTES = {"FP64": 52, "FP32": 52, "candidate": 2, "pair": 2}
-FORCE_BYTES = {"FP64": 176, "FP32": 136, "pair": 2}
+DENS_BYTES = {"FP64": 52, "FP32": 52, "candidate": 2}
+FORCE_BYTES = {"FP64": 176, "FP32": 136, "candidate": 2}
 PEAK = {"FP64": 78.6e12, "FP32": 157.3e12}     # published MI355X vector peaks, FLOP/s
 KERNEL_SOURCES = ("paper_2107_07315_amd/csrc/sph_pairs.hip", "paper_2107_07315_amd/csrc/sph_internal.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pair_passes_2M_traffic.json")
@@ -260,11 +259,10 @@ def roofline(res, n, precision):
     passes = {
         "density": (f"k_density<{'float' if f32 else 'double'}>",
                     cand * DENS_FLOP["candidate"] + pairs * DENS_FLOP["pair"] + n * DENS_FLOP["particle"],
-                    n * DENS_BYTES[precision] + cand * DENS_BYTES["candidate"]
-                    + (0 if f32 else pairs * DENS_BYTES["pair"])),
+                    n * DENS_BYTES[precision] + cand * DENS_BYTES["candidate"]),
         "forces": (f"k_forces<{'float' if f32 else 'double'}>",
                    pairs * FORCE_FLOP["pair"] + n * FORCE_FLOP["particle"],
-                   n * FORCE_BYTES[precision] + (cand if f32 else pairs) * FORCE_BYTES["pair"]),
+                   n * FORCE_BYTES[precision] + cand * FORCE_BYTES["candidate"]),
     }
     # the pass's time per step: one full launch per step (a step that rebuilds the lists also
     # carries a run-ahead launch that found the skin test failed and exited at once)

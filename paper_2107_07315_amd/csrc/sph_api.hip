@@ -833,7 +833,7 @@ sph_status sph_export_neighbours(sph_ctx* c, int64_t* offsets, int32_t* ids, int
   if (!offsets) return note(c, SPH_E_ARG, "offsets is NULL");
   if (c->n > 0 && (c->gen < 2 || !c->lists_valid)) return SPH_E_ORDER;
   const int64_t n = c->n;
-  if (n > 0 && !exact_lists_written(c)) {
+  if (n > 0) {
     sph_status e = launch_exact_lists(c);
     if (e) return e;
   }

@@ -144,6 +144,15 @@ __device__ __forceinline__ double sqrt_fast(double x) {
   r = fma(0.5 * y, fma(-r, r, x), r);
   return x > 0.0 ? r : 0.0;
 }
+// the same for the pair passes: 0 is raised to 1e-300 (one instruction instead of a compare and two
+// selects), where the estimate is finite; r = 1e-150 then stands for 0
+__device__ __forceinline__ double sqrt_pos(double x) {
+  x = fmax(x, 1e-300);
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * fma(-0.5 * x * y, y, 1.5);
+  const double r = x * y;
+  return fma(0.5 * y, fma(-r, r, x), r);
+}
 __device__ __forceinline__ float sqrt_fast(float x) {
   const float r = x * __builtin_amdgcn_rsqf(x);
   return x > 0.0f ? r : 0.0f;
@@ -322,8 +331,8 @@ struct sph_ctx {
   // tile_uoff[t] holds the union of the tile's candidates (particle indices).  Candidate entry k
   // of particle p is the local index into U_t stored at nbr16s[((k/8)*capw + p)*8 + k%8] (groups
   // of 8 entries per lane, so a lane fetches 8 entries with one 16-byte load and a wave's load is
-  // one contiguous 1 KB); the exact lists that the density pass extracts use the same layout in
-  // nbr16 with nbr_count.
+  // one contiguous 1 KB); the exact lists that the neighbour export has the density pass write use the
+  // same layout in nbr16 with nbr_count.
   int32_t* tile_start;
   int32_t* tile_cnt;
   uint32_t* tile_uoff;  // tile t owns tile_u[tile_uoff[t], + min(ucap, cnt * cap_s))
@@ -415,7 +424,6 @@ sph_status launch_drift_check(sph_ctx* c, sph_state* st);
 sph_status launch_flag_clear(sph_ctx* c);
 sph_status launch_density(sph_ctx* c, sph_state* st);   // pair loop
 sph_status launch_exact_lists(sph_ctx* c);               // exact lists of the last evaluation (export)
-bool exact_lists_written(const sph_ctx* c);              // whether the density pass writes them
 sph_status launch_eos(sph_ctx* c, sph_state* st);       // per-particle epilogue
 sph_status launch_stress(sph_ctx* c, sph_state* st);
 sph_status launch_forces(sph_ctx* c, sph_state* st);

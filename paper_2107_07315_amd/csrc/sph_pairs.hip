@@ -1,15 +1,14 @@
 // Pair passes of the particle loop: density (+ EoS epilogue and the exact neighbour decision),
 // velocity gradient / stress rate, and momentum/energy forces (+ fixed-background epilogue).
 //
-// One workgroup = one wavefront = one tile of at most 64 consecutive particles (one lane per
-// target).  The tile's neighbour union U is streamed through LDS in chunks of CH packed records
-// (loaded by the whole wave); each lane walks its ascending 16-bit local list and reads its
-// neighbours' records from LDS.  The walk is software-pipelined: list entries arrive 8 per
-// 16-byte load one group ahead of use, and the next neighbour's LDS record is read before the
-// current pair's arithmetic.  Kernel type and periodicity are compile-time parameters so the
-// inner loops are straight-line code.  The pair arithmetic is templated on the pair precision
-// R: double in the FP64 path, float in the mixed-precision path; epilogues (metric, EoS, GR
-// terms) are FP64.
+// One workgroup = one tile of at most 64 consecutive particles, L lanes per target.  The tile's
+// neighbour union U is streamed through LDS in chunks of CH packed records (loaded by the whole
+// workgroup); each lane walks its ascending 16-bit candidate list and reads its neighbours' records
+// from LDS.  The walk is software-pipelined: list entries arrive 8 per 16-byte load one group ahead
+// of use, and the next neighbour's LDS record is read before the current pair's arithmetic.  Kernel
+// type and periodicity are compile-time parameters so the inner loops are straight-line code.  The
+// pair arithmetic is templated on the pair precision R: double in the FP64 path, float in the
+// mixed-precision path; epilogues (metric, EoS, GR terms) are FP64.
 #include <type_traits>
 
 #include "sph_internal.h"
@@ -83,19 +82,23 @@ __device__ __forceinline__ R kern_F_unit(R r, R ih) {
 __device__ __forceinline__ float sqrt_hw(float x) { return __builtin_amdgcn_sqrtf(x); }
 
 template <typename R> struct Rec;
-// Record scale: the FP64 records hold h, alpha c_s and D; the FP32 ones hold h/2, alpha c_s/2 and
-// D/2 (exact halvings), so the pair means 0.5 (h_a + h_b), 0.5 alpha (c_a + c_b), 0.5 (D_a + D_b)
-// are HS times the sum of the two record values and HS = 1 saves the multiply in FP32 (alpha: the
-// viscosity coefficient, which multiplies the mean sound speed wherever it is used).
+// Record scale: the records hold alpha c_s/2 and D/2 (exact halvings), so the pair means 0.5 alpha
+// (c_a + c_b), 0.5 (D_a + D_b) are plain sums (alpha: the viscosity coefficient, which multiplies the
+// mean sound speed wherever it is used); the FP32 position records hold h/2 too, and 0.5 (h_a + h_b) is
+// HS times the sum of the two record values.
 template <> struct Rec<double> {
-  static constexpr double HS = 0.5;
+  static constexpr double HS = 0.5;   // (positions: pos4 holds h itself)
   using P4 = double4;
   using V4 = double4;
   using A2 = double2;
   static constexpr int CH_D = 256;   // LDS records per chunk and wave: density 8 KB
-  static constexpr int CHMAX_D = 1024;  // per workgroup: 32 KB + 8 KB of list staging, 4 workgroups per CU
+  static constexpr int CHMAX_D = 1024;  // per workgroup: 32 KB, 4 workgroups per CU
   static constexpr int CH_S = 128;   // stress 8 KB
-  static constexpr int CH_F = 128;   // forces 10 KB
+  // forces: 20 KB a wave, 80 KB at 4 lanes, two workgroups per CU.  Wide, so that almost every union is
+  // one chunk (2M star: 712 members on average) and the walk is the unrolled one: the chunk's end costs
+  // the other walk more than the occupancy gives it.  2M / 200k star: 937 / 94 us; with 166 records a
+  // wave (three workgroups) 1045 / 85, with 128 1180 on the 2M star
+  static constexpr int CH_F = 256;
 };
 template <> struct Rec<float> {
   static constexpr float HS = 1.0f;
@@ -103,10 +106,31 @@ template <> struct Rec<float> {
   using V4 = float4;
   using A2 = float2;
   static constexpr int CH_D = 384;   // density records: FP32 tile-relative (x, y, z, h), 6 KB
-  static constexpr int CHMAX_D = 1280;   // per workgroup: 20 KB + 8 KB of list staging, 5 workgroups per CU
+  static constexpr int CHMAX_D = 1280;   // per workgroup: 20 KB, 5 workgroups per CU
   static constexpr int CH_S = 256;
   static constexpr int CH_F = 256;
   static constexpr int CH_FS = 128;   // forces with S/D^2 in LDS too (64 bytes a record): 32 KB
+};
+
+// Four-component records in LDS.  FP64 records of 32 bytes are kept as two arrays of 16: a read of 16
+// bytes a lane at a stride of 32 uses every other group of four banks only (force pass on the 2M star:
+// 1.8e8 conflict cycles per launch, 1.1e8 in two arrays).
+template <typename R, int N> struct Lds4;
+template <int N> struct Lds4<float, N> {
+  float4 q[N];
+  __device__ __forceinline__ float4 get(int j) const { return q[j]; }
+  __device__ __forceinline__ void put(int j, const float4& r) { q[j] = r; }
+};
+template <int N> struct Lds4<double, N> {
+  double2 a[N], b[N];
+  __device__ __forceinline__ double4 get(int j) const {
+    const double2 u = a[j], v = b[j];
+    return make_double4(u.x, u.y, v.x, v.y);
+  }
+  __device__ __forceinline__ void put(int j, const double4& r) {
+    a[j] = make_double2(r.x, r.y);
+    b[j] = make_double2(r.z, r.w);
+  }
 };
 
 struct PassArgs {
@@ -121,15 +145,9 @@ struct PassArgs {
   const int32_t* __restrict__ tile_u;
   const int32_t* __restrict__ tile_usize;
   const int32_t* __restrict__ stress_tiles;
-  const uint16_t* __restrict__ nbr16;    // exact lists (written by the density pass), one per slot
-  const int32_t* __restrict__ cnt_sl;   // entries per slot; slot = particle * lanes + sub-index
   int cap_sl;                           // entries a slot holds
   const uint16_t* __restrict__ nbr16s;   // candidate lists of the last build
   const int32_t* __restrict__ cnt_s;
-  // the stress and force passes walk the candidate lists instead of the exact ones (the pair
-  // terms vanish beyond the support, so the sums are the same; the density pass then writes no
-  // exact lists)
-  int cand_walk;
   const uint32_t* __restrict__ tile_st;   // per tile: a particle or union member of type 1 (or null)
   const int32_t* __restrict__ star;
   const StarInfo* __restrict__ stars;
@@ -296,16 +314,18 @@ __device__ __forceinline__ void stage_union(const int32_t* __restrict__ U, int c
     if (b[k] >= 0) put((int)threadIdx.x + k * NT, r[k]);
 }
 
-// The list a stress or force lane walks (slot = particle * L + sub-index) and its length: the exact
-// list written by the density pass, or the candidate list of the last build (candidate k of a
-// particle is entry k / L of slot k % L).
+// The list every pass walks (slot = particle * L + sub-index) and its length: the candidate list of
+// the last build, candidate k of a particle being entry k / L of slot k % L.  The pair terms carry the
+// kernel or its gradient, which are zero beyond the support, so the candidates of the skin add exact
+// zeros.  (Exact lists written by the density pass for the other two cost more than the third of the
+// pairs that they spare, in FP64 too: a wave waits for its longest list, and the density pass for its
+// stores.  2M star, density + force pass: 555 + 943 us with them, 459 + 937 without.)
 template <int L>
 __device__ __forceinline__ const uint4* pass_list(const PassArgs& A, int64_t slot) {
-  return reinterpret_cast<const uint4*>(A.cand_walk ? A.nbr16s : A.nbr16) + slot;
+  return reinterpret_cast<const uint4*>(A.nbr16s) + slot;
 }
 template <int L>
-__device__ __forceinline__ int pass_count(const PassArgs& A, int64_t p, int sub, int64_t slot) {
-  if (!A.cand_walk) return A.cnt_sl[slot];
+__device__ __forceinline__ int pass_count(const PassArgs& A, int64_t p, int sub) {
   const int total = A.cnt_s[p];
   return total > sub ? (total - sub + L - 1) / L : 0;
 }
@@ -532,8 +552,8 @@ __device__ __forceinline__ void density_epilogue(const PassArgs& A, int64_t a, b
   const bool stressed = solid;
   const int64_t n = A.n;
   if (sizeof(R) == 8) {
-    O.fv[a] = make_double4(va[0], va[1], va[2], p.visc_alpha * cs);   // alpha c_s for the viscosity
-    O.fa[a] = make_double2(pi, stressed ? -D : D);
+    O.fv[a] = make_double4(va[0], va[1], va[2], 0.5 * p.visc_alpha * cs);   // alpha c_s / 2 for the viscosity
+    O.fa[a] = make_double2(pi, stressed ? -0.5 * D : 0.5 * D);
     if (stressed)   // S/D^2 is read only for stressed particles (the sign of D in fa marks them)
       for (int c = 0; c < 6; ++c) O.sig[c * n + a] = S[c * n + a] * iD2;
   } else {
@@ -558,13 +578,13 @@ __device__ __forceinline__ void density_epilogue(const PassArgs& A, int64_t a, b
 // H2_f) and the band as H (kBand H + kBand M_a).
 constexpr float kBand = 3.814697265625e-06f;   // 2^-18
 
-// Density pass.  Walks the candidate lists, takes the exact neighbour decision r^2 < (h_a + h_b)^2
+// Density pass.  In FP64 it is bound by instruction issue and LDS reads: 459 us on the 2M star
+// (245M candidate pairs), 565 when it also wrote exact lists and read 32-byte records whole.  Walks the candidate lists, takes the exact neighbour decision r^2 < (h_a + h_b)^2
 // of the FP64 positions on every candidate, sums the kernel over the neighbours in R and counts
-// them; with XL it also writes the exact lists (for the stress and force passes when they walk
-// exact lists, and for the neighbour export).  A workgroup of L waves takes one tile: lane g
-// serves target g / L as sub-lane g % L, walks the candidate slot list (particle * L + sub-lane)
-// and writes the exact hits to the exact slot list of the same index; the L partial sums are
-// added across the lanes.  The per-particle epilogue runs in k_density_epilogue, one lane per
+// them; with XL it also writes the exact lists (for the neighbour export).  A workgroup of L waves
+// takes one tile: lane g serves target g / L as sub-lane g % L, walks the candidate slot list
+// (particle * L + sub-lane) and with XL writes the exact hits to the exact slot list of the same
+// index; the L partial sums are added across the lanes.  The per-particle epilogue runs in k_density_epilogue, one lane per
 // particle.
 //   FP64 (R = double): union records staged in LDS as FP64 (x, y, z, h), FP64 test.
 //   FP32 (R = float): union records staged as FP32 coordinates relative to the tile's first
@@ -580,15 +600,15 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
   using SR = typename std::conditional<F32, float4, double4>::type;
   constexpr int CH = Rec<R>::CH_D * L < Rec<R>::CHMAX_D ? Rec<R>::CH_D * L : Rec<R>::CHMAX_D;
   constexpr int CHU = CH - 1;   // union records per chunk; slot CHU holds the walk's sentinel
-  __shared__ SR sp[CH];
+  __shared__ Lds4<R, CH> sp;
   constexpr int RB = 2;
   __shared__ __align__(16) uint16_t lring[XL ? 64 * L : 1][8 * RB];   // per-lane staging of the exact lists
   const double box = A.p.box, half = 0.5 * box;
   const float boxf = (float)box, halff = (float)half;
   const int tl = threadIdx.x / L, sub = threadIdx.x % L;
   if (threadIdx.x == 0) {   // the sentinel: far from every target, h = 0 (no neighbour, W = 0)
-    if constexpr (F32) sp[CHU] = make_float4(1e10f, 1e10f, 1e10f, 0.0f);
-    else sp[CHU] = make_double4(1e10, 1e10, 1e10, 0.0);
+    if constexpr (F32) sp.put(CHU, make_float4(1e10f, 1e10f, 1e10f, 0.0f));
+    else sp.put(CHU, make_double4(1e10, 1e10, 1e10, 0.0));
   }
   const int64_t ntl = num_tiles(A);
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntl); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
@@ -640,7 +660,7 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
       const double r2 = pair_r2(dx, dy, dz);
       const double H = pa.w + pb.w;
       hit = r2 < H * H;
-      W = kern_W_unit<R, KER>(sqrt_fast((R)r2), rcp_fast((R)(0.5 * H)));
+      W = kern_W_unit<R, KER>(sqrt_pos((R)r2), rcp_fast((R)(0.5 * H)));
       W = hit ? W : (R)0;   // the exact decision also at the support edge
     }
     sum += W;
@@ -649,10 +669,10 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
   auto stage = [&](int c0) {
     stage_union<64 * L, CHU>(tw.U, c0, tw.usize, [&](int32_t b) { return pos64[b]; }, [&](int j, const double4& q) {
       if constexpr (F32)
-        sp[j] = make_float4((float)wrap_sel<PER>(q.x - ref.x, box, half), (float)wrap_sel<PER>(q.y - ref.y, box, half),
-                            (float)wrap_sel<PER>(q.z - ref.z, box, half), (float)q.w);
+        sp.put(j, make_float4((float)wrap_sel<PER>(q.x - ref.x, box, half), (float)wrap_sel<PER>(q.y - ref.y, box, half),
+                              (float)wrap_sel<PER>(q.z - ref.z, box, half), (float)q.w));
       else
-        sp[j] = q;
+        sp.put(j, q);
     });
   };
   if (tw.usize <= CHU) {   // whole union in one chunk: pipelined group walk
@@ -660,7 +680,7 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
     stage(0);
     __syncthreads();
     walk_groups_pf(
-        lst, A.capw * L, cnt, wave_max_i(cnt), CHU, [&](int j) { return sp[j]; },
+        lst, A.capw * L, cnt, wave_max_i(cnt), CHU, [&](int j) { return sp.get(j); },
         [&](int loc, const SR& pb) {
           cand(loc, pb, [&](int l, bool h) {
             if constexpr (XL) wr.put_unchecked(l, h);
@@ -680,7 +700,7 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
       while (tw.next < cend) {
         const int loc = tw.next;
         tw.advance();
-        cand(loc, sp[loc - c0], [&](int l, bool h) {
+        cand(loc, sp.get(loc - c0), [&](int l, bool h) {
           if constexpr (XL) wr.put(l, h);
           else wr.n += h ? 1 : 0;
         });
@@ -691,7 +711,7 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
   sum = lane_group_sum<L>(sum);
   const int nexact = lane_group_sum<L>(wr.n);
   if (tw.valid) {
-    xcount_sl[slot] = wr.n < A.cap_sl ? wr.n : A.cap_sl;
+    if constexpr (XL) xcount_sl[slot] = wr.n < A.cap_sl ? wr.n : A.cap_sl;
     if (sub == 0) xcount[a] = nexact < A.cap ? nexact : A.cap;
     if (nexact > A.cap || wr.n > A.cap_sl) latch_error(A.status, SPH_E_NGB_CAPACITY, (int)a);
   }
@@ -840,8 +860,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
   using V4 = typename Rec<R>::V4;
   constexpr int CH = Rec<R>::CH_S * L;
   const int tl = threadIdx.x / L, sub = threadIdx.x % L;
-  __shared__ P4 sp[CH];
-  __shared__ V4 sv[CH];
+  __shared__ Lds4<R, CH> sp, sv;
   const R box = (R)A.p.box, half = (R)0.5 * box;
   // only the tiles of the work list (tiles with a type-1 particle); every other particle's rates
   // are zero since the last build
@@ -874,7 +893,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
     const R ih = rcp_fast(Rec<R>::HS * (pa.w + pb.w));
     R F;   // without the kernel's constant, applied in the epilogue
     if constexpr (std::is_same<R, float>::value) F = kern_F_unit<float, KER>(sqrt_hw(r2), ih);
-    else F = kern_F_unit<R, KER>(sqrt_fast(r2), ih);
+    else F = kern_F_unit<R, KER>(sqrt_pos(r2), ih);
     const R g[3] = {F * d[0], F * d[1], F * d[2]};
     const R v[3] = {vb.x - va.x, vb.y - va.y, vb.z - va.z};
 #pragma unroll
@@ -885,7 +904,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
   auto stage = [&](int c0, int ch) {
     stage_union<64 * L, CH>(tw.U, c0, c0 + ch < tw.usize ? c0 + ch : tw.usize,
                             [&](int32_t b) { return Recs{pos[b], fv[b]}; },
-                            [&](int j, const Recs& r) { sp[j] = r.p; sv[j] = r.v; });
+                            [&](int j, const Recs& r) { sp.put(j, r.p); sv.put(j, r.v); });
   };
   if (std::is_same<R, float>::value && tw.usize < CH) {
     // FP32 with the whole union in one chunk: pipelined group walk, LDS slot CH - 1 the sentinel
@@ -893,16 +912,16 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
     __syncthreads();
     stage(0, CH - 1);
     if (threadIdx.x == 0) {
-      sp[CH - 1] = P4{(R)1e10, (R)1e10, (R)1e10, (R)0};
-      sv[CH - 1] = V4{(R)0, (R)0, (R)0, (R)0};
+      sp.put(CH - 1, P4{(R)1e10, (R)1e10, (R)1e10, (R)0});
+      sv.put(CH - 1, V4{(R)0, (R)0, (R)0, (R)0});
     }
     __syncthreads();
-    const int cnt = stressed ? pass_count<L>(A, tw.p, sub, slot) : 0;
+    const int cnt = stressed ? pass_count<L>(A, tw.p, sub) : 0;
     walk_groups_pf(
         pass_list<L>(A, slot), A.capw * L, cnt, wave_max_i(cnt), CH - 1,
-        [&](int j) { return Recs{sp[j], sv[j]}; }, [&](int, const Recs& r) { pair(r); }, [] {});
+        [&](int j) { return Recs{sp.get(j), sv.get(j)}; }, [&](int, const Recs& r) { pair(r); }, [] {});
   } else {
-    tw.start(pass_list<L>(A, slot), A.capw * L, stressed ? pass_count<L>(A, tw.p, sub, slot) : 0);
+    tw.start(pass_list<L>(A, slot), A.capw * L, stressed ? pass_count<L>(A, tw.p, sub) : 0);
     for (int c0 = 0; c0 < tw.usize; c0 += CH) {
       __syncthreads();
       stage(c0, CH);
@@ -911,7 +930,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
       while (tw.next < cend) {
         const int j = tw.next - c0;
         tw.advance();
-        pair(Recs{sp[j], sv[j]});
+        pair(Recs{sp.get(j), sv.get(j)});
       }
     }
   }
@@ -921,7 +940,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
     for (int jj = 0; jj < 3; ++jj) G[i][jj] = lane_group_sum<L>(G[i][jj]);
   if (!stressed || sub != 0) continue;
   const double m = particle_mass(A, a) * kern_F_const<KER>();
-  const double D = -(double)faa.y * (2.0 * (double)Rec<R>::HS);  // stressed particles store -D (FP32: -D/2)
+  const double D = -2.0 * (double)faa.y;  // stressed particles store -D/2
   const double iD2 = m / (2.0 * D);
   double ed[3][3], Rd[3][3];
 #pragma unroll
@@ -1006,7 +1025,7 @@ __device__ __forceinline__ void ext_accel(const PassArgs& A, const ForceOut& O, 
   }
 }
 
-// Lane g of the L-wave workgroup walks the exact slot list (g / L, g % L); the partial sums of a
+// Lane g of the L-wave workgroup walks the candidate slot list (g / L, g % L); the partial sums of a
 // target's L lanes are added before the fixed-background epilogue.
 // XS selects the optional sums (compile-time, so that the default mode keeps its registers):
 //   kXDD: sum m v_ab . grad_a W (continuity density and first-law energy);
@@ -1029,14 +1048,13 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   constexpr int CH = (SL ? Rec<float>::CH_FS : Rec<R>::CH_F) * L;
   constexpr int CHU = CH - 1;   // union records per chunk; slot CHU holds the walk's sentinel
   const int tl = threadIdx.x / L, sub = threadIdx.x % L;
-  __shared__ P4 sp[CH];
-  __shared__ V4 sv[CH];
+  __shared__ Lds4<R, CH> sp, sv;
   __shared__ A2 sa2[CH];
   __shared__ R ssg[SL ? 6 : 1][SL ? CH : 1];   // kXSL: S/D^2 of the staged members (0 if unstressed)
   const R box = (R)A.p.box, half = (R)0.5 * box;
   if (threadIdx.x == 0) {   // the sentinel: far from every target, at rest, h = 0, unstressed (F = 0)
-    sp[CHU] = P4{(R)1e10, (R)1e10, (R)1e10, (R)0};
-    sv[CHU] = V4{(R)0, (R)0, (R)0, (R)0};
+    sp.put(CHU, P4{(R)1e10, (R)1e10, (R)1e10, (R)0});
+    sv.put(CHU, V4{(R)0, (R)0, (R)0, (R)0});
     sa2[CHU] = A2{(R)0, (R)1};
   }
   const int64_t ntl = num_tiles(A);
@@ -1048,7 +1066,7 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   const int64_t a = tw.a;
   const int64_t slot = a * L + sub;
   const uint4* lst = pass_list<L>(A, slot);
-  const int cnt = tw.valid ? pass_count<L>(A, tw.p, sub, slot) : 0;
+  const int cnt = tw.valid ? pass_count<L>(A, tw.p, sub) : 0;
   const int64_t n = A.n;
   const sph_params& p = A.p;
   const P4 pa = tw.valid ? pos[a] : P4{0, 0, 0, 1};
@@ -1075,20 +1093,28 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
                     wrap_sel<PER>(pa.z - pb.z, box, half)};
     const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
     const R hab = Rec<R>::HS * (pa.w + pb.w);
-    R F;   // grad_a W = kF F d (the constant kF is applied to the sums)
-    if constexpr (std::is_same<R, float>::value) F = kern_F_unit<float, KER>(sqrt_hw(r2), rcp_fast(hab));
-    else F = kern_F_unit<R, KER>(sqrt_fast(r2), rcp_fast(hab));
+    const R X = r2 + eps_v * hab * hab;
     const R v[3] = {va.x - vb.x, va.y - vb.y, va.z - vb.z};
     const R vr = v[0] * d[0] + v[1] * d[1] + v[2] * d[2];
     const bool b_st = fab.y < 0;
     const R Db = fabs(fab.y);
+    const R Dbar = Da + Db;   // the records hold halves
+    const R acbar = va.w + vb.w;   // alpha c_bar
     // Monaghan viscosity on approaching pairs, Pi = mu (beta mu - alpha c_bar) / Dbar with
     // mu = hab vr / X: with tv = mu / Dbar (one reciprocal), Pi = tv (beta tv Dbar - alpha c_bar)
-    const R X = r2 + eps_v * hab * hab;
-    const R Dbar = Rec<R>::HS * (Da + Db);
-    const R tv = hab * vr * rcp_fast(X * Dbar);
-    const R acbar = Rec<R>::HS * (va.w + vb.w);   // alpha c_bar (the records hold alpha c_s)
-    const R Pi = vr < (R)0 ? tv * fma(beta_v * tv, Dbar, -acbar) : (R)0;
+    R F, Pi;   // grad_a W = kF F d (the constant kF is applied to the sums)
+    if constexpr (std::is_same<R, float>::value) {
+      F = kern_F_unit<float, KER>(sqrt_hw(r2), rcp_fast(hab));
+      const R tv = hab * vr * rcp_fast(X * Dbar);
+      Pi = vr < (R)0 ? tv * fma(beta_v * tv, Dbar, -acbar) : (R)0;
+    } else {
+      // 1/hab and 1/(X Dbar) from one reciprocal of their product (its refinement is five FP64
+      // instructions); a receding pair has tv = 0
+      const R XD = X * Dbar, R1 = rcp_fast(hab * XD);
+      F = kern_F_unit<R, KER>(sqrt_pos(r2), R1 * XD);
+      const R tv = hab * fmin(vr, (R)0) * (R1 * hab);
+      Pi = tv * fma(beta_v * tv, Dbar, -acbar);
+    }
     const R cPF = (pia + fab.x + Pi) * F;
     AP[0] += cPF * d[0];
     AP[1] += cPF * d[1];
@@ -1128,29 +1154,28 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
             return r;
           },
           [&](int j, const RecsS& r) {
-            sp[j] = r.p;
-            sv[j] = r.v;
+            sp.put(j, r.p);
+            sv.put(j, r.v);
             sa2[j] = r.f;
 #pragma unroll
             for (int c = 0; c < 6; ++c) ssg[c][j] = r.s[c];
           });
     } else {
       stage_union<64 * L, CHU>(tw.U, c0, tw.usize, [&](int32_t b) { return Recs{pos[b], fv[b], fa[b]}; },
-                              [&](int j, const Recs& r) { sp[j] = r.p; sv[j] = r.v; sa2[j] = r.f; });
+                              [&](int j, const Recs& r) { sp.put(j, r.p); sv.put(j, r.v); sa2[j] = r.f; });
     }
   };
   auto pair = [&](int loc, const Recs& r) { pair_st(loc, r, std::true_type{}); };
   // a tile whose particles and union members are all of type 0 (the list build's flag) walks
   // without the stress term
   auto stress_tile = [&] { return SL || !A.tile_st || A.tile_st[tile] != 0u; };
-  // FP32 with the whole union in one chunk (the usual case): pipelined group walk.  (In FP64 the 8
-  // inlined copies of the longer pair body run slower than the shifting walk, measured.)
-  if (std::is_same<R, float>::value && tw.usize <= CHU) {
+  // the whole union in one chunk (the usual case): pipelined group walk
+  if (tw.usize <= CHU) {
     __syncthreads();
     stage(0);
     __syncthreads();
     const bool any_st = stress_tile();
-    auto ld = [&](int j) { return Recs{sp[j], sv[j], sa2[j]}; };
+    auto ld = [&](int j) { return Recs{sp.get(j), sv.get(j), sa2[j]}; };
     if (any_st)
       walk_groups_pf(lst, A.capw * L, cnt, wave_max_i(cnt), CHU, ld, pair, [] {});
     else
@@ -1171,7 +1196,7 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
           const int loc = tw.next;
           tw.advance();
           const int j = loc - c0;
-          pair_st(loc, Recs{sp[j], sv[j], sa2[j]}, ST);
+          pair_st(loc, Recs{sp.get(j), sv.get(j), sa2[j]}, ST);
         }
       };
       // (FP64 only: in FP32 this walk serves the rare large unions, and a second copy slowed the
@@ -1268,12 +1293,9 @@ PassArgs make_args(sph_ctx* c, sph_state* st) {
   A.tile_u = c->tile_u;
   A.tile_usize = c->tile_usize;
   A.stress_tiles = c->stress_tiles;
-  A.nbr16 = c->nbr16;
-  A.cnt_sl = c->nbr_count_sl;
   A.cap_sl = slot_capacity(c->cap, pass_lanes(c->p));
   A.nbr16s = c->nbr16s;
   A.cnt_s = c->nbr_count_s;
-  A.cand_walk = exact_lists_written(c) ? 0 : 1;
   A.tile_st = c->tile_st;
   A.star = c->stars ? st->star : nullptr;
   A.stars = c->stars;
@@ -1333,40 +1355,31 @@ static DensOut dens_out(sph_ctx* c, sph_state* st) {
   return O;
 }
 
-// The density pass; it writes the exact lists when the stress and force passes walk them.
 sph_status launch_density(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
   DensOut O = dens_out(c, st);
   const dim3 g = pass_grid(c);
   const bool f32 = c->p.precision == SPH_FP32;
-  const bool xl = !A.cand_walk;
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
     dispatch_lanes(pass_lanes(c->p), [&](auto LL) {
       constexpr int KER = decltype(K)::value;
       constexpr bool PER = decltype(P)::value;
       constexpr int L = decltype(LL)::value;
       const dim3 b(64 * L);
-      auto launch = [&](auto XX) {
-        constexpr bool XL = decltype(XX)::value;
-        if (f32)
-          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, XL>), g, b, 0, c->stream, A, c->pos4, O,
-                             c->nbr16, c->nbr_count, c->nbr_count_sl);
-        else
-          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, XL>), g, b, 0, c->stream, A, c->pos4, O,
-                             c->nbr16, c->nbr_count, c->nbr_count_sl);
-      };
-      if (xl) launch(std::true_type{});
-      else launch(std::false_type{});
+      if (f32)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, false>), g, b, 0, c->stream, A, c->pos4, O,
+                           nullptr, c->nbr_count, nullptr);
+      else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, false>), g, b, 0, c->stream, A, c->pos4, O,
+                           nullptr, c->nbr_count, nullptr);
     });
   });
   HIP_TRY(hipGetLastError());
   return SPH_OK;
 }
 
-bool exact_lists_written(const sph_ctx* c) { return c->p.precision != SPH_FP32; }
-
-// Exact lists of the last evaluation (positions and h of its packed records) when the density
-// pass did not write them: the density pass once more with XL, its sums dropped into scratch.
+// Exact lists of the last evaluation (positions and h of its packed records): the density pass once
+// more with XL, its sums dropped into scratch.
 sph_status launch_exact_lists(sph_ctx* c) {
   sph_state st{};
   st.n = c->n;
