@@ -71,237 +71,256 @@ struct GradArgs {
   MlpView M;
   const float* x;    // normalised inputs, 2 per sample
   const float* t;    // normalised targets
-  int64_t off;       // first sample of the batch; samples wrap modulo n
+  int64_t off;       // first sample of the batch, below n; samples wrap modulo n
   int64_t n;
-  int batch;         // samples in the batch (multiple of 64); block b takes samples [NS b, NS b + NS)
+  int batch;         // samples in the batch (multiple of 64, at most n); block b takes [NS b, NS b + NS)
   float* gpart;
   float* lpart;
 };
 
-// Gradient of L = 1/(2 batch) sum_s sum_o (y_so - t_so)^2 over the block's NS samples (lane l <
-// NS = sample l), written as this block's partial.  Layers 2 and 3 and their weight gradients and
-// back-propagated activations are products on the matrix cores (64 x 64 x NS and 64 x NS x 64);
-// activations are kept in LDS sample-major (row = sample, column = feature).  The forward
-// products take the activations as two BF16 parts, as the inference does (the loss is that of the
-// network the kernels evaluate); the weight gradients use their high parts.  NS = 16 spreads a
-// 4096-sample batch over 256 workgroups, one per CU.
-template <int NS>
-__global__ __launch_bounds__(64) void k_mlp_grad(GradArgs G) {
-  static_assert(NS % 16 == 0 && NS <= 64, "whole 16-sample tiles");
-  constexpr int NT = NS / 16;   // 16-sample tiles
+// Gradient of L = 1/(2 batch) sum_s sum_o (y_so - t_so)^2 over the block's 16 samples, written as
+// this block's partial.  Layers 2 and 3 and their weight gradients and back-propagated activations
+// are products on the matrix cores (64 x 64 x 16 and 64 x 16 x 64).  The forward products take the
+// activations as two BF16 parts, as the inference does (the loss is that of the network the kernels
+// evaluate); the weight gradients use their high parts.
+// Bound by the latency of the chain of layers: a 4096-sample batch is 256 workgroups, one per CU, and
+// nothing of it is large.  So a workgroup is four waves, wave w with features [16 w, 16 w + 16) of
+// every layer: in the layout of the matrix products a lane holds features f0 .. f0 + 3 of sample r
+// throughout, so pre-activations stay in registers from the forward to the backward pass and only what
+// the next product reads goes through LDS (sample-major: row = sample, column = feature); the
+// weights' operands are loaded before the first layer.  One wave with a sample per lane in the vector
+// layers used 16 of its lanes there: 19.2 us a batch of 4096, 10.9 now.  Each value's terms and their
+// order are the same.
+__global__ __launch_bounds__(256) void k_mlp_grad(GradArgs G) {
+  constexpr int NS = kGradSamples;
+  static_assert(NS == 16, "one matrix tile of samples");
   __shared__ __align__(16) uint16_t Ht1[NS * LP];
   __shared__ __align__(16) uint16_t Ht2[NS * LP];
   __shared__ __align__(16) uint16_t Lt1[NS * LP];   // low BF16 parts of the activations
   __shared__ __align__(16) uint16_t Lt2[NS * LP];
-  __shared__ __align__(16) uint16_t Gt[NS * LP];
-  __shared__ __align__(16) float Zt2[NS * LP];
-  __shared__ __align__(16) float Zt3[NS * LP];
-  __shared__ __align__(16) float G32[NS * LP];
-  __shared__ float xs[NS][2], dys[NS][2];
-  const int l = threadIdx.x, q = l >> 4, r = l & 15;
-  const bool own = l < NS;   // the lane holds a sample
+  __shared__ __align__(16) uint16_t Gt3[NS * LP], Gt2[NS * LP];   // gradients at z3, z2
+  __shared__ __align__(16) float H3[NS * LP];
+  __shared__ __align__(16) float Ga[NS * LP], Gb[NS * LP];   // in FP32: at z3 and z1, at z2
+  __shared__ float xs[NS][2], dys[NS][2], w4[2 * MLP_H];
+  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4, r = l & 15;
+  const int f0 = 16 * wv + 4 * q;   // the lane's features of sample r
   const MlpView& M = G.M;
   const float* w = M.wr;
-  const int64_t sg = (G.off + (int64_t)blockIdx.x * NS + (own ? l : 0)) % G.n;
-  const float x0 = own ? G.x[2 * sg] : 0.f, x1 = own ? G.x[2 * sg + 1] : 0.f;
-  const float t0 = own ? G.t[2 * sg] : 0.f, t1 = own ? G.t[2 * sg + 1] : 0.f;
+  int64_t sg = G.off + (int64_t)blockIdx.x * NS + r;   // off < n and batch <= n: at most one wrap
+  if (sg >= G.n) sg -= G.n;
+  const float x0 = G.x[2 * sg], x1 = G.x[2 * sg + 1];
+  const int o = q & 1;   // output layer: lanes 16 o + r of wave 0 hold output o of sample r
+  const float to = G.t[2 * sg + o];
+  uint2 wa2[4], wa3[4], wt3[4], wt2[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int at = (wv * 4 + kk) * 64 + l;
+    wa2[kk] = M.wa2[at];
+    wa3[kk] = M.wa3[at];
+    wt3[kk] = M.wt3[at];
+    wt2[kk] = M.wt2[at];
+  }
+  float b2[4], b3[4], z1[4], z2[4], z3[4], h[4], g[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    b2[j] = w[MLP_OB2 + f0 + j];
+    b3[j] = w[MLP_OB3 + f0 + j];
+    z1[j] = w[MLP_OW1 + 2 * (f0 + j)] * x0 + w[MLP_OW1 + 2 * (f0 + j) + 1] * x1 + w[MLP_OB1 + f0 + j];
+  }
+  if (threadIdx.x < 2 * MLP_H) w4[threadIdx.x] = w[MLP_OW4 + threadIdx.x];
+  if (threadIdx.x < NS) {
+    xs[r][0] = x0;
+    xs[r][1] = x1;
+  }
+  const float b4 = w[MLP_OB4 + o];
   float* gp = G.gpart + (int64_t)blockIdx.x * MLP_NPARAM;
-  if (own) {
-    xs[l][0] = x0;
-    xs[l][1] = x1;
-    // ---- forward ------------------------------------------------------------------------------
-    for (int f = 0; f < 64; f += 4) {
-      float h[4];
+  // ---- forward --------------------------------------------------------------------------------
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        h[j] = silu_f(w[MLP_OW1 + 2 * (f + j)] * x0 + w[MLP_OW1 + 2 * (f + j) + 1] * x1 + w[MLP_OB1 + f + j]);
-      lds_store_split(&Ht1[l * LP + f], &Lt1[l * LP + f], h[0], h[1], h[2], h[3]);
-    }
-  }
+  for (int j = 0; j < 4; ++j) h[j] = silu_f(z1[j]);
+  lds_store_split(&Ht1[r * LP + f0], &Lt1[r * LP + f0], h[0], h[1], h[2], h[3]);
   __syncthreads();
-  // hidden layers: C tile (features 16 mt + 4q + j, samples 16 nt + r)
-  for (int layer = 0; layer < 2; ++layer) {
-    const uint2* wa = layer == 0 ? M.wa2 : M.wa3;
-    const int ob = layer == 0 ? MLP_OB2 : MLP_OB3;
-    const uint16_t* Hin = layer == 0 ? Ht1 : Ht2;
-    const uint16_t* Lin = layer == 0 ? Lt1 : Lt2;
-    float* Z = layer == 0 ? Zt2 : Zt3;
-    for (int nt = 0; nt < NT; ++nt) {
-      bf16x4 b[4], bl[4];
+  // hidden layer: C tile (features 16 wv + 4q + j, samples r)
+  auto layer = [&](const uint2 (&wa)[4], const uint16_t* Hin, const uint16_t* Lin, const float (&bias)[4], float (&z)[4]) {
+    bf16x4 b[4], bl[4];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        b[kk] = lds_b4(&Hin[(16 * nt + r) * LP + 16 * kk + 4 * q]);
-        bl[kk] = lds_b4(&Lin[(16 * nt + r) * LP + 16 * kk + 4 * q]);
-      }
-      for (int mt = 0; mt < 4; ++mt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const bf16x4 wv = as_bf16x4(wa[(mt * 4 + kk) * 64 + l]);
-          acc = mfma_bf16(wv, b[kk], acc);
-          acc = mfma_bf16(wv, bl[kk], acc);
-        }
-        float z[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) z[j] = acc[j] + w[ob + 16 * mt + 4 * q + j];
-        *reinterpret_cast<float4*>(&Z[(16 * nt + r) * LP + 16 * mt + 4 * q]) = make_float4(z[0], z[1], z[2], z[3]);
-        if (layer == 0)
-          lds_store_split(&Ht2[(16 * nt + r) * LP + 16 * mt + 4 * q], &Lt2[(16 * nt + r) * LP + 16 * mt + 4 * q],
-                          silu_f(z[0]), silu_f(z[1]), silu_f(z[2]), silu_f(z[3]));
-      }
+    for (int kk = 0; kk < 4; ++kk) {
+      b[kk] = lds_b4(&Hin[r * LP + 16 * kk + 4 * q]);
+      bl[kk] = lds_b4(&Lin[r * LP + 16 * kk + 4 * q]);
     }
-    __syncthreads();
-  }
-  // output layer and loss (lane = sample)
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      acc = mfma_bf16(as_bf16x4(wa[kk]), b[kk], acc);
+      acc = mfma_bf16(as_bf16x4(wa[kk]), bl[kk], acc);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z[j] = acc[j] + bias[j];
+  };
+  layer(wa2, Ht1, Lt1, b2, z2);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) h[j] = silu_f(z2[j]);
+  lds_store_split(&Ht2[r * LP + f0], &Lt2[r * LP + f0], h[0], h[1], h[2], h[3]);
+  __syncthreads();
+  layer(wa3, Ht2, Lt2, b3, z3);
+  *reinterpret_cast<float4*>(&H3[r * LP + f0]) = make_float4(silu_f(z3[0]), silu_f(z3[1]), silu_f(z3[2]), silu_f(z3[3]));
+  __syncthreads();
+  // output layer and loss
   const float inv = 1.0f / (float)G.batch;
-  float loss = 0.f, d0 = 0.f, d1 = 0.f;
-  if (own) {
-    float y0 = w[MLP_OB4], y1 = w[MLP_OB4 + 1];
-    for (int f = 0; f < 64; ++f) {
-      const float h3 = silu_f(Zt3[l * LP + f]);
-      y0 += w[MLP_OW4 + f] * h3;
-      y1 += w[MLP_OW4 + MLP_H + f] * h3;
-    }
-    const float e0 = y0 - t0, e1 = y1 - t1;
-    loss = 0.5f * (e0 * e0 + e1 * e1) * inv;
-    d0 = e0 * inv;
-    d1 = e1 * inv;
-    dys[l][0] = d0;
-    dys[l][1] = d1;
-    // ---- backward -----------------------------------------------------------------------------
-    // g3 = (W4^T dy) * silu'(z3)  (lane = sample)
+  if (wv == 0) {
+    float y = b4;
+#pragma unroll 4
     for (int f = 0; f < 64; f += 4) {
-      float g[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        g[j] = (w[MLP_OW4 + f + j] * d0 + w[MLP_OW4 + MLP_H + f + j] * d1) * dsilu_f(Zt3[l * LP + f + j]);
-      *reinterpret_cast<float4*>(&G32[l * LP + f]) = make_float4(g[0], g[1], g[2], g[3]);
-      lds_store_b4(&Gt[l * LP + f], g[0], g[1], g[2], g[3]);
+      const float4 hh = *reinterpret_cast<const float4*>(&H3[r * LP + f]);
+      y += w4[o * MLP_H + f] * hh.x;
+      y += w4[o * MLP_H + f + 1] * hh.y;
+      y += w4[o * MLP_H + f + 2] * hh.z;
+      y += w4[o * MLP_H + f + 3] * hh.w;
     }
+    const float e = y - to;
+    const float e0 = __shfl(e, r, 64), e1 = __shfl(e, 16 + r, 64);
+    if (l < 32) dys[r][o] = e * inv;
+    const float ls = wave_sum_f(l < NS ? 0.5f * (e0 * e0 + e1 * e1) * inv : 0.f);
+    if (l == 0) G.lpart[blockIdx.x] = ls;
   }
   __syncthreads();
-  {  // dW4, db3 (lane = feature), db4
-    const int f = l;
-    float a0 = 0.f, a1 = 0.f, bsum = 0.f;
-    for (int s = 0; s < NS; ++s) {
-      const float h3 = silu_f(Zt3[s * LP + f]);
-      a0 += dys[s][0] * h3;
-      a1 += dys[s][1] * h3;
-      bsum += G32[s * LP + f];
+  // ---- backward -------------------------------------------------------------------------------
+  {  // g3 = (W4^T dy) * silu'(z3)
+    const float d0 = dys[r][0], d1 = dys[r][1];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[j] = (w4[f0 + j] * d0 + w4[MLP_H + f0 + j] * d1) * dsilu_f(z3[j]);
+    *reinterpret_cast<float4*>(&Ga[r * LP + f0]) = make_float4(g[0], g[1], g[2], g[3]);
+    lds_store_b4(&Gt3[r * LP + f0], g[0], g[1], g[2], g[3]);
+  }
+  __syncthreads();
+  // gradient at the layer's input: dH_in = W^T G (K = out features), times silu'(z_in)
+  auto back = [&](const uint2 (&wt)[4], const uint16_t* Gt, const float (&z)[4]) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) acc = mfma_bf16(as_bf16x4(wt[kk]), lds_b4(&Gt[r * LP + 16 * kk + 4 * q]), acc);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[j] = acc[j] * dsilu_f(z[j]);
+  };
+  // weight gradient dW = G H_in^T (K = samples), rows [16 wv, 16 wv + 16)
+  auto weight_grad = [&](int ow, const uint16_t* Gt, const uint16_t* Hin) {
+    // A[out 16 wv + r][sample 4q + j], B[sample 4q + j][in 16 nt + r]
+    const bf16x4 a = lds_b4_strided(&Gt[4 * q * LP + 16 * wv + r], LP);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      const f32x4 acc = mfma_bf16(a, lds_b4_strided(&Hin[4 * q * LP + 16 * nt + r], LP), zero);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) gp[ow + MLP_H * (f0 + j) + 16 * nt + r] = acc[j];
     }
-    gp[MLP_OW4 + f] = a0;
-    gp[MLP_OW4 + MLP_H + f] = a1;
-    gp[MLP_OB3 + f] = bsum;
-    const float s0 = wave_sum_f(d0), s1 = wave_sum_f(d1);
+  };
+  back(wt3, Gt3, z2);
+  *reinterpret_cast<float4*>(&Gb[r * LP + f0]) = make_float4(g[0], g[1], g[2], g[3]);
+  lds_store_b4(&Gt2[r * LP + f0], g[0], g[1], g[2], g[3]);
+  if (wv < 2) {          // dW4 (lane = feature)
+    float a = 0.f;
+    for (int s = 0; s < NS; ++s) a += dys[s][wv] * H3[s * LP + l];
+    gp[MLP_OW4 + MLP_H * wv + l] = a;
+  } else if (wv == 2) {  // db3
+    float bsum = 0.f;
+    for (int s = 0; s < NS; ++s) bsum += Ga[s * LP + l];
+    gp[MLP_OB3 + l] = bsum;
+  } else {               // db4
+    const float s0 = wave_sum_f(l < NS ? dys[r][0] : 0.f), s1 = wave_sum_f(l < NS ? dys[r][1] : 0.f);
     if (l == 0) {
       gp[MLP_OB4] = s0;
       gp[MLP_OB4 + 1] = s1;
     }
   }
-  // layers 3 and 2: dW = G * H_in^T (K = samples), dH_in = W^T * G (K = out features)
-  for (int layer = 1; layer >= 0; --layer) {
-    const uint16_t* Hin = layer == 1 ? Ht2 : Ht1;
-    const uint2* wt = layer == 1 ? M.wt3 : M.wt2;
-    const int ow = layer == 1 ? MLP_OW3 : MLP_OW2;
-    for (int mt = 0; mt < 4; ++mt)
-      for (int nt = 0; nt < 4; ++nt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < NT; ++kk) {
-          // A[out 16mt + r][sample 16kk + 4q + j], B[sample 16kk + 4q + j][in 16nt + r]
-          const bf16x4 a = lds_b4_strided(&Gt[(16 * kk + 4 * q) * LP + 16 * mt + r], LP);
-          const bf16x4 b = lds_b4_strided(&Hin[(16 * kk + 4 * q) * LP + 16 * nt + r], LP);
-          acc = mfma_bf16(a, b, acc);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) gp[ow + MLP_H * (16 * mt + 4 * q + j) + 16 * nt + r] = acc[j];
-      }
-    f32x4 dh[4][NT];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          acc = mfma_bf16(as_bf16x4(wt[(mt * 4 + kk) * 64 + l]), lds_b4(&Gt[(16 * nt + r) * LP + 16 * kk + 4 * q]), acc);
-        dh[mt][nt] = acc;
-      }
-    __syncthreads();   // the G of this layer is consumed
-    // g_in = dH_in * silu'(z_in): z2 from LDS, z1 recomputed from the inputs
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int s = 16 * nt + r, f0 = 16 * mt + 4 * q;
-        float g[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int f = f0 + j;
-          const float z = layer == 1 ? Zt2[s * LP + f]
-                                     : w[MLP_OW1 + 2 * f] * xs[s][0] + w[MLP_OW1 + 2 * f + 1] * xs[s][1] + w[MLP_OB1 + f];
-          g[j] = dh[mt][nt][j] * dsilu_f(z);
-        }
-        *reinterpret_cast<float4*>(&G32[s * LP + f0]) = make_float4(g[0], g[1], g[2], g[3]);
-        lds_store_b4(&Gt[s * LP + f0], g[0], g[1], g[2], g[3]);
-      }
-    __syncthreads();
-    const int f = l;
-    if (layer == 1) {   // db2
-      float bsum = 0.f;
-      for (int s = 0; s < NS; ++s) bsum += G32[s * LP + f];
-      gp[MLP_OB2 + f] = bsum;
-    } else {            // dW1, db1
-      float a0 = 0.f, a1 = 0.f, bsum = 0.f;
-      for (int s = 0; s < NS; ++s) {
-        const float g = G32[s * LP + f];
-        a0 += g * xs[s][0];
-        a1 += g * xs[s][1];
-        bsum += g;
-      }
-      gp[MLP_OW1 + 2 * f] = a0;
-      gp[MLP_OW1 + 2 * f + 1] = a1;
-      gp[MLP_OB1 + f] = bsum;
-    }
+  weight_grad(MLP_OW3, Gt3, Ht2);
+  __syncthreads();
+  back(wt2, Gt2, z1);
+  *reinterpret_cast<float4*>(&Ga[r * LP + f0]) = make_float4(g[0], g[1], g[2], g[3]);
+  weight_grad(MLP_OW2, Gt2, Ht1);
+  __syncthreads();
+  float a = 0.f;
+  if (wv < 2) {          // dW1 (lane = feature)
+    for (int s = 0; s < NS; ++s) a += Ga[s * LP + l] * xs[s][wv];
+    gp[MLP_OW1 + 2 * l + wv] = a;
+  } else {               // db1, db2
+    const float* src = wv == 2 ? Ga : Gb;
+    for (int s = 0; s < NS; ++s) a += src[s * LP + l];
+    gp[(wv == 2 ? MLP_OB1 : MLP_OB2) + l] = a;
   }
-  const float ls = wave_sum_f(loss);
-  if (l == 0) G.lpart[blockIdx.x] = ls;
+}
+
+// A weight of W2 or W3 in the two packs that hold it: entry ((mt * 4 + kk) * 64 + 16 q + r), element j
+// is (row 16 mt + r, column 16 kk + 4 q + j) of W, and in the transposed pack of W^T.
+__device__ __forceinline__ void mlp_store_packs(uint16_t* pack, int p, uint32_t bits) {
+  const int which = p >= MLP_OW3 ? 1 : 0, e = p - (which ? MLP_OW3 : MLP_OW2);
+  const int row = e / MLP_H, col = e % MLP_H;
+  auto at = [](int which, int i, int j) {
+    return 4 * (which * 1024 + ((i >> 4) * 4 + (j >> 4)) * 64 + ((j >> 2) & 3) * 16 + (i & 15)) + (j & 3);
+  };
+  pack[at(which, row, col)] = (uint16_t)bits;
+  pack[at(which + 2, col, row)] = (uint16_t)bits;
 }
 
 // Sums the block partials in block order (deterministic), then optionally one Adam step on the
-// FP32 master weights and the copy the kernels use; block 0 also sums the loss.
-__global__ __launch_bounds__(256) void k_mlp_adam(float* w, float* wr, float* m, float* v, const float* gpart,
-                                                  const float* lpart, int nblk, float lr, float bc1, float bc2,
-                                                  float* gsum, float* loss_out) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  // block partials summed in block order; their loads are issued 8 at a time (one wait per 8)
-  auto sum_parts = [&](const float* part, int64_t stride, int64_t off) {
-    float s = 0.f;
-    int b = 0;
-    for (; b + 8 <= nblk; b += 8) {
-      float t[8];
+// FP32 master weights, the copy the kernels use and its matrix operand packs; the last block sums the
+// loss.  The partials (8.8 MB for 4096 samples) are what it reads: kAdamParams parameters a workgroup,
+// so that 271 of them share the read, and 8 groups of lanes stage 32 partials each in LDS at once, where
+// one lane per parameter adds them in order (one thread per parameter reading them 8 at a time, in 34
+// workgroups, waited for memory 32 times: 17.2 us, and 4.7 us for the packs in a launch of their own;
+// 6.5 us now).
+constexpr int kAdamParams = 32, kAdamChunk = 256;   // parameters per workgroup, partials staged at a time
+constexpr int kAdamBlocks = (MLP_NPARAM + kAdamParams - 1) / kAdamParams + 1;
+__global__ __launch_bounds__(256) void k_mlp_adam(float* w, float* wr, float* m, float* v, uint16_t* pack,
+                                                  const float* gpart, const float* lpart, int nblk, float lr, float bc1,
+                                                  float bc2, float* gsum, float* loss_out) {
+  constexpr int kRows = 256 / kAdamParams, kEach = kAdamChunk / kRows;
+  __shared__ float part[kAdamChunk][kAdamParams];
+  const int k = threadIdx.x % kAdamParams, row = threadIdx.x / kAdamParams;
+  const bool loss = (int)blockIdx.x == kAdamBlocks - 1;
+  const int p = blockIdx.x * kAdamParams + k;
+  const bool mine = loss ? k == 0 : p < MLP_NPARAM;
+  const float* src = loss ? lpart : gpart + p;
+  const int64_t stride = loss ? 1 : MLP_NPARAM;
+  const bool step = !loss && mine && row == 0 && lr > 0.f;
+  float m0 = 0.f, v0 = 0.f, w0 = 0.f;
+  if (step) {
+    m0 = m[p];
+    v0 = v[p];
+    w0 = w[p];
+  }
+  float g = 0.f;
+  for (int c0 = 0; c0 < nblk; c0 += kAdamChunk) {
+    float t[kEach];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) t[k] = part[(int64_t)(b + k) * stride + off];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) s += t[k];
+    for (int i = 0; i < kEach; ++i) {
+      const int b = c0 + i * kRows + row;
+      t[i] = mine && b < nblk ? src[(int64_t)b * stride] : 0.f;
     }
-    for (; b < nblk; ++b) s += part[(int64_t)b * stride + off];
-    return s;
-  };
-  if (p < MLP_NPARAM) {
-    const float g = sum_parts(gpart, MLP_NPARAM, p);
-    if (gsum) gsum[p] = g;
-    if (lr > 0.f) {
-      const float mm = 0.9f * m[p] + 0.1f * g;
-      const float vv = 0.999f * v[p] + 0.001f * g * g;
-      m[p] = mm;
-      v[p] = vv;
-      const float wn = w[p] - lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
-      w[p] = wn;
-      wr[p] = mlp_bf16_param(p) ? bf16_round(wn) : wn;
+    if (c0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) part[i * kRows + row][k] = t[i];
+    __syncthreads();
+    const int nb = nblk - c0 < kAdamChunk ? nblk - c0 : kAdamChunk;
+    if (row == 0) {
+#pragma unroll 16
+      for (int b = 0; b < nb; ++b) g += part[b][k];
     }
   }
-  if (p == 0 && loss_out) *loss_out = sum_parts(lpart, 1, 0);
+  if (!mine || row != 0) return;
+  if (loss) {
+    if (loss_out) *loss_out = g;
+    return;
+  }
+  if (gsum) gsum[p] = g;
+  if (step) {
+    const float mm = 0.9f * m0 + 0.1f * g;
+    const float vv = 0.999f * v0 + 0.001f * g * g;
+    m[p] = mm;
+    v[p] = vv;
+    const float wn = w0 - lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
+    w[p] = wn;
+    const bool b16 = mlp_bf16_param(p);
+    wr[p] = b16 ? bf16_round(wn) : wn;
+    if (b16) mlp_store_packs(pack, p, bf16_bits(wn));
+  }
 }
 
 // MFMA A-operand packs of W2, W3 and their transposes from the rounded weights.
@@ -684,7 +703,7 @@ sph_status launch_grad(sph_ctx* c, const float* x, const float* t, int64_t n, in
   G.batch = batch;
   G.gpart = c->mlp->gpart;
   G.lpart = c->mlp->lpart;
-  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_mlp_grad<kGradSamples>), dim3(batch / kGradSamples), dim3(64), 0, c->stream, G);
+  hipLaunchKernelGGL(k_mlp_grad, dim3(batch / kGradSamples), dim3(256), 0, c->stream, G);
   HIP_TRY(hipGetLastError());
   return SPH_OK;
 }
@@ -771,8 +790,8 @@ sph_status sph_mlp_grad(sph_ctx* c, const float* x, const float* t, int64_t n, f
   MlpState* s = c->mlp;
   sph_status e = launch_grad(c, x, t, n, 0, (int)n);
   if (e) return e;
-  hipLaunchKernelGGL(k_mlp_adam, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, c->stream, s->w, s->wr, s->m, s->v,
-                     s->gpart, s->lpart, (int)(n / kGradSamples), 0.f, 1.f, 1.f, s->gsum, s->scal);
+  hipLaunchKernelGGL(k_mlp_adam, dim3(kAdamBlocks), dim3(256), 0, c->stream, s->w, s->wr, s->m, s->v,
+                     reinterpret_cast<uint16_t*>(s->pack), s->gpart, s->lpart, (int)(n / kGradSamples), 0.f, 1.f, 1.f, s->gsum, s->scal);
   HIP_TRY(hipGetLastError());
   float l = 0.f;
   HIP_TRY(hipMemcpyAsync(grad, s->gsum, sizeof(float) * MLP_NPARAM, hipMemcpyDeviceToHost, c->stream));
@@ -812,9 +831,8 @@ sph_status sph_mlp_train(sph_ctx* c, const double* samples, int64_t n, int64_t n
       // samples rotate through the training set; each epoch starts at a different offset
       const int64_t off = (k * batch + (int64_t)ep * 7919) % ntrain;
       if ((e = launch_grad(c, x, t, ntrain, off, batch))) break;
-      hipLaunchKernelGGL(k_mlp_adam, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, c->stream, s->w, s->wr, s->m,
-                         s->v, s->gpart, s->lpart, nblk, (float)lr_t, bc1, bc2, (float*)nullptr, s->scal);
-      hipLaunchKernelGGL(k_mlp_pack, dim3(16), dim3(256), 0, c->stream, s->wr, s->pack);
+      hipLaunchKernelGGL(k_mlp_adam, dim3(kAdamBlocks), dim3(256), 0, c->stream, s->w, s->wr, s->m, s->v,
+                         reinterpret_cast<uint16_t*>(s->pack), s->gpart, s->lpart, nblk, (float)lr_t, bc1, bc2, (float*)nullptr, s->scal);
     }
     if (e) break;
     float hl = 0.f;
