@@ -10,6 +10,7 @@
 // that follow: taken from the other build's order, ten steps of the 2M-particle star differ by
 // 2.5e-5 in the accelerations (both orders are equally far from the FP64 values), a perfect lattice
 // by 2e-3.  With this build FP32 runs reproduce earlier results bit for bit.
+#include "sph_build.h"
 #include "sph_internal.h"
 
 namespace {
@@ -21,15 +22,6 @@ __device__ __forceinline__ int particle_level(double h, const GridInfo& g) {
   int l = 0;
   while (l < g.nlev - 1 && ratio >= (double)(2 << l)) ++l;
   return l;
-}
-
-// The same test against the skin-widened support (1 + s)(h_a + h_b); s1 = 1 + s.  With s = 0 it
-// is bit-identical to neighbour_test.
-__device__ __forceinline__ bool candidate_test(double dx, double dy, double dz, double ha, double hb, double s1) {
-#pragma clang fp contract(off)
-  double r2 = (dx * dx + dy * dy) + dz * dz;
-  double H = (ha + hb) * s1;
-  return r2 < H * H;
 }
 
 // Per level: largest h and the bounding box of the level's particles (a tile's search at a level
@@ -220,138 +212,22 @@ __device__ __forceinline__ double wave_max_d(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
   return v;
 }
-// min / max over aligned groups of 8 lanes
-__device__ __forceinline__ double grp8_min(double v) {
-  for (int off = 1; off < 8; off <<= 1) v = fmin(v, __shfl_xor(v, off, 64));
+// a value that all lanes hold, in scalar registers
+__device__ __forceinline__ double uniform_d(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+// min / max over aligned groups of gs lanes (a power of 2, at most 8)
+__device__ __forceinline__ double grp_min(double v, int gs) {
+  for (int off = 1; off < gs; off <<= 1) v = fmin(v, __shfl_xor(v, off, 64));
   return v;
 }
-__device__ __forceinline__ double grp8_max(double v) {
-  for (int off = 1; off < 8; off <<= 1) v = fmax(v, __shfl_xor(v, off, 64));
+__device__ __forceinline__ double grp_max(double v, int gs) {
+  for (int off = 1; off < gs; off <<= 1) v = fmax(v, __shfl_xor(v, off, 64));
   return v;
 }
-__device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v) {
-  for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off, 64);
-  return v;
-}
-
-struct TileState {
-  int64_t a;
-  int32_t a32;               // a as a 32-bit index (candidate indices are 32-bit), -1 if not valid
-  bool valid;
-  unsigned long long vmask;  // the wave's valid lanes
-  double xa, ya, za, ha;
-  double hs;                 // ha (1 + skin)(1 + 2^-40), the candidate test's scaled h
-  int usize, cnt, ucap;
-  int32_t* U;
-  uint16_t* row;             // the lane's staging row in LDS (8 entries of each of the L slots)
-  uint4* slot0;              // group 0 of the lane's first slot
-  int64_t gstride;           // groups between consecutive groups of one slot (capw * lanes)
-};
-
-// Candidate k of a particle goes to its slot k % L, as entry k / L (L = lanes per target of the
-// pair passes): each lane of the density pass then walks one contiguous slot list.  The lane's
-// LDS row holds 8 L consecutive candidates in arrival order (candidate k at k mod 8 L, so entry p
-// of slot s of the row's group sits at p L + s); when the row is full every slot has a complete
-// group of 8, and the row is stored as L groups (group g of slot s at g * capw * L + s), each
-// gathered from the row by byte permutes.  A row holds group g = k / (8 L) of every slot.
-template <int L>
-__device__ __forceinline__ void store_row_groups(const TileState& T, int g, int nslots) {
-  uint32_t D[4 * L];
-  __builtin_memcpy(D, T.row, sizeof(D));
-#pragma unroll
-  for (int s = 0; s < L; ++s) {
-    if (s >= nslots) break;
-    uint32_t w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if constexpr (L == 1) {
-        w[k] = D[k];
-      } else {
-        const int i0 = 2 * k * L + s, i1 = (2 * k + 1) * L + s;   // entries 2k, 2k+1 of slot s
-        const uint32_t sel = ((i0 & 1) ? 0x0302u : 0x0100u) | ((i1 & 1) ? 0x07060000u : 0x05040000u);
-        w[k] = __builtin_amdgcn_perm(D[i1 >> 1], D[i0 >> 1], sel);
-      }
-    }
-    T.slot0[(int64_t)g * T.gstride + s] = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-}
-template <int L>
-__device__ __forceinline__ void append_candidate(const BuildArgs& B, TileState& T, int loc) {
-  const unsigned k = (unsigned)T.cnt;
-  const uint16_t v = (uint16_t)loc;
-  __builtin_memcpy(T.row + (k & (8 * L - 1)), &v, sizeof(v));
-  ++T.cnt;
-  if ((k & (8 * L - 1)) == 8 * L - 1 && (int)(k / (8 * L)) * 8 < B.cap_sl) store_row_groups<L>(T, (int)(k / (8 * L)), L);
-}
-
-// candidate test (skin-widened, FP64) of every lane's target against batch candidates cb[0..nb),
-// nb <= 64; NB > 0 fixes nb at compile time (full batches).  The test is
-// r^2 < (h_a' + h_b')^2 with h' = h (1 + skin)(1 + 2^-40) (T.hs, cb[j].w) and r^2 by FMA: the
-// factor 1 + 2^-40 exceeds the few ulp by which this rounding can differ from the exact decision
-// of the density pass, so the candidates always contain every pair that test can accept (with a
-// positive skin the rebuild test's own margin of 1e-9 is larger still).
-// Candidates are taken one at a time: the wave's ballot decides at once whether candidate j joins
-// the union (as its next member), and the lanes that hit it append that local index, so the
-// lists come out ascending in local index and U in candidate order.
-template <int L, int NB, bool PER>
-__device__ __forceinline__ void run_batch(const BuildArgs& B, TileState& T, const double4* cb, const int32_t* cbi,
-                                          int nb, double box) {
-  const int lane = threadIdx.x;
-  unsigned long long um = 0ull;   // the batch's union members (wave-uniform)
-  int nm = 0;
-  // the lane's decision (hit) and the wave's mask of it, the mask from the compares themselves
-  // (ballot of the combined flag would first widen it to a vector register)
-  struct Hit { bool hit; unsigned long long m; };
-  auto test = [&](const double4& pb, int32_t bj) -> Hit {
-    const double dx = min_image(T.xa - pb.x, (int)PER, box), dy = min_image(T.ya - pb.y, (int)PER, box),
-                 dz = min_image(T.za - pb.z, (int)PER, box);
-    const double H = T.hs + pb.w;
-    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx)), H2 = H * H;
-    return Hit{T.valid && bj != T.a32 && r2 < H2,
-               __builtin_amdgcn_fcmp(r2, H2, 4 /* ordered less than */) &
-                   __builtin_amdgcn_uicmp(bj, T.a32, 33 /* not equal */) & T.vmask};
-  };
-  auto take = [&](int j, const Hit& t) {
-    const bool hit = t.hit;
-    if (t.m) {
-      um |= 1ull << j;
-      int loc = T.usize + nm;
-      ++nm;
-      loc = loc < T.ucap ? loc : T.ucap - 1;   // union overflow: keep reads in range, error latched
-      if (hit) append_candidate<L>(B, T, loc);
-    }
-  };
-  if constexpr (NB > 0) {
-    // the next candidate's record is read from LDS while this one is tested and appended
-    double4 nx = cb[0];
-    int32_t nbi = cbi[0];
-#pragma unroll 1
-    for (int jb = 0; jb < NB; jb += 8) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const double4 pb = nx;
-        const int32_t bj = nbi;
-        if (jb + k + 1 < NB) {
-          nx = cb[jb + k + 1];
-          nbi = cbi[jb + k + 1];
-        }
-        take(jb + k, test(pb, bj));
-      }
-    }
-  } else {
-    for (int j = 0; j < nb; ++j) take(j, test(cb[j], cbi[j]));
-  }
-  if (!um) return;
-  const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-  if ((um >> lane) & 1ull) {
-    const int loc = T.usize + __popcll(um & lt);
-    if (loc < T.ucap) T.U[loc] = cbi[lane];
-  }
-  T.usize += nm;
-}
-
 // Geometry of one tile, shared by the cost and build kernels: whole-tile box and max h
-// (wave-uniform), and in LDS the sub-boxes of the 8 groups of 8 consecutive particles with their
+// (wave-uniform), and in LDS the sub-boxes of the first 8 groups of gs consecutive particles with their
 // own max h.  Candidates and cells are tested against the sub-boxes, which stays tight where a
 // tile mixes small and large h (a candidate within (h_a + h_b)(1 + skin) of a particle a is that
 // close to a's sub-box).
@@ -359,28 +235,29 @@ struct TileGeom {
   double lo[3], hi[3], hmx;
 };
 
-__device__ __forceinline__ void tile_geometry(const double4 pa, bool valid, TileGeom& G, double (*sub)[8]) {
+__device__ __forceinline__ void tile_geometry(const double4 pa, bool valid, int gs, TileGeom& G, double (*sub)[8]) {
   const int lane = threadIdx.x;
   const double big = 1e300;
   const double q[3] = {pa.x, pa.y, pa.z};
   for (int d = 0; d < 3; ++d) {
-    G.lo[d] = wave_min_d(valid ? q[d] : big);
-    G.hi[d] = wave_max_d(valid ? q[d] : -big);
+    G.lo[d] = uniform_d(wave_min_d(valid ? q[d] : big));
+    G.hi[d] = uniform_d(wave_max_d(valid ? q[d] : -big));
   }
-  G.hmx = wave_max_d(valid ? pa.w : 0.0);
+  G.hmx = uniform_d(wave_max_d(valid ? pa.w : 0.0));
   double gl[3], gh[3];
   for (int d = 0; d < 3; ++d) {
-    gl[d] = grp8_min(valid ? q[d] : big);
-    gh[d] = grp8_max(valid ? q[d] : -big);
+    gl[d] = grp_min(valid ? q[d] : big, gs);
+    gh[d] = grp_max(valid ? q[d] : -big, gs);
   }
-  const double gx = grp8_max(valid ? pa.w : 0.0);
+  const double gx = grp_max(valid ? pa.w : 0.0, gs);
+  const int gi = lane / gs;
   __syncthreads();
-  if ((lane & 7) == 0) {
+  if (gi * gs == lane && gi < 8) {
     for (int d = 0; d < 3; ++d) {
-      sub[lane >> 3][d] = 0.5 * (gl[d] + gh[d]);
-      sub[lane >> 3][3 + d] = 0.5 * (gh[d] - gl[d]);
+      sub[gi][d] = 0.5 * (gl[d] + gh[d]);
+      sub[gi][3 + d] = 0.5 * (gh[d] - gl[d]);
     }
-    sub[lane >> 3][6] = gx;
+    sub[gi][6] = gx;
   }
   __syncthreads();
 }
@@ -481,7 +358,7 @@ __global__ __launch_bounds__(64) void k_tile_cost(const double4* __restrict__ po
     const bool valid = lane < tile_cnt[t];
     const double4 pa = valid ? pos4[tile_start[t] + lane] : make_double4(0.0, 0.0, 0.0, 0.0);
     TileGeom G;
-    tile_geometry(pa, valid, G, sub);
+    tile_geometry(pa, valid, 8, G, sub);
     int64_t tot = 0;
     for (int l = 0; l < g.nlev; ++l) {
       LevelBox L;
@@ -534,57 +411,201 @@ __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, 
 //  1. the 64 lanes take 64 cells of the level box at once, cull them against the sub-boxes and
 //     load their particle ranges;
 //  2. the wave gathers the cells' particles 64 at a time (a wave-wide prefix sum maps lanes to
-//     (cell, offset)), pre-tests each against the sub-boxes and appends survivors to an LDS batch;
-//  3. per batch of 64 candidates every lane runs the skin-widened FP64 test against all of them,
-//     building a 64-bit hit mask; the OR of the masks gives the batch's new union members (in
-//     candidate order) and each lane appends the local indices of its hits.
+//     (cell, offset)), tests each against the tile's box and appends survivors to an LDS batch;
+//  3. a batch of 64 candidates is tested against the 64 targets on the matrix cores (sph_build.h):
+//     the sign of r^2 - (h_a' + h_b')^2 is the decision wherever its size exceeds kBand (|x|^2 + h'^2
+//     of both), twice what the test can be off (16 2^-22 of that, see the other build's bound); the few
+//     pairs within it are decided by the FP64 test.
+// The decision is thus the FP64 one for every pair, r^2 < (h_a' + h_b')^2 with h' = h (1 + skin)
+// (1 + 2^-40) and r^2 by FMA: the factor 1 + 2^-40 exceeds the few ulp by which this rounding can differ
+// from the exact decision of the density pass, so the candidates always contain every pair that test can
+// accept (with a positive skin the rebuild test's own margin of 1e-9 is larger still).
 // Tile t is particles [tile_start[t], tile_start[t] + tile_cnt[t]) of the array order (at most 64).
-// Candidates enter batches in a fixed order (level, cell, cell-sorted position), so U and the
-// lists are deterministic and each list is ascending in local index.
+// Candidates enter batches in a fixed order (level, cell, cell-sorted position); one that any target
+// hits joins the union, as its next member, and each target appends the local indices of its hits, so U
+// and the lists are deterministic and each list is ascending in local index.
+// Bound by instruction issue.  The FP64 test of every candidate by every lane (10 operations a pair, and
+// eight sub-box tests a candidate to keep the batches short) took 3.43 ms on the 2M star (skin 0.14),
+// 1.08 ms on a 300k snapshot and 0.50 ms on the 1M shell; this takes 2.15, 0.58 and
+// 0.32.  (Sub-box or particle tests of the candidates on top of the box test cost more than the batches
+// they save: 2.27 ms, 0.73 in small tiles only.)
+constexpr float kBand = 0x1p-17f;
 template <bool PER, int NL>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_build_tiles(BuildArgs B) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_build_tiles(BuildArgs B) {
   __shared__ int32_t c_s[64], c_o[64];
   __shared__ double sub[8][8];   // per group of 8 tile particles: centre xyz, half-width xyz, max h
-  __shared__ double4 tp[16];     // the particles of a small tile (its exact pre-filter)
-  __shared__ double4 cb[128];
+  __shared__ float4 cb[128];     // candidates waiting: scaled x, y, z, h'
   __shared__ int32_t cbi[128];
-  __shared__ __align__(16) uint16_t crow[64][8 * NL];   // per lane: staging of the candidate lists
+  __shared__ __align__(16) uint16_t ring[64 * kRingRow];
+  // a batch's candidate that is target l itself, in the padding of its ring
+  auto self = [&](int l) -> uint32_t& { return *reinterpret_cast<uint32_t*>(ring + kRingRow * l + kRing); };
   const int lane = threadIdx.x;
   const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   const GridInfo& g = *B.grid;
   const double box = g.box;
   const double s1 = 1.0 + g.skin;
   const double s1w = s1 * (1.0 + 0x1p-40);   // the batch test's widened factor
+  const float s1f = (float)s1 * (1.0f + 1e-5f);
+  // the candidate of a batch that this lane lifts: the products' rows come out in an order in which
+  // lane l holds bit l' of the masks, so it takes candidate l' and the bits are in batch order
+  const int lj = 32 * ((lane >> 2) & 1) + 16 * (lane >> 5) + 4 * ((lane >> 3) & 3) + (lane & 3);
   const int64_t ntiles = g.ntiles;
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
     const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
     if (t >= ntiles) break;
-    const int32_t tcnt = B.tile_cnt[t];
-    const int64_t p = (int64_t)B.tile_start[t] + lane;
-    TileState T;
-    T.valid = lane < tcnt;
-    T.a = T.valid ? p : -1;
-    T.a32 = (int32_t)T.a;
-    T.vmask = __builtin_amdgcn_ballot_w64(T.valid);
-    const double4 pa = T.valid ? B.pos4[T.a] : make_double4(0.0, 0.0, 0.0, 0.0);
-    T.xa = pa.x; T.ya = pa.y; T.za = pa.z; T.ha = pa.w; T.hs = pa.w * s1w;
+    const int32_t tcnt = B.tile_cnt[t], ts = B.tile_start[t];
+    const bool valid = lane < tcnt;
+    const int32_t a = ts + lane;
+    const double4 pa = valid ? B.pos4[a] : make_double4(0.0, 0.0, 0.0, 0.0);
+    const double ha = pa.w * s1w;
     TileGeom G;
-    tile_geometry(pa, T.valid, G, sub);
-    if (lane < 16) tp[lane] = pa;
-    // small tiles (split because they are expensive) pre-filter candidates exactly against
-    // their own particles: far fewer batches, each of which would use only tcnt lanes
-    const bool small = tcnt <= 16;
+    // small tiles (split off because their neighbourhoods are dear) are often a few particles far apart:
+    // cells are culled against groups as small as 8 boxes allow, down to the single particle
+    tile_geometry(pa, valid, tcnt > 32 ? 8 : (tcnt > 16 ? 4 : (tcnt > 8 ? 2 : 1)), G, sub);
+    const double cx = uniform_d(0.5 * (G.lo[0] + G.hi[0])), cy = uniform_d(0.5 * (G.lo[1] + G.hi[1])),
+                 cz = uniform_d(0.5 * (G.lo[2] + G.hi[2]));
+    const double wx = uniform_d(0.5 * (G.hi[0] - G.lo[0])), wy = uniform_d(0.5 * (G.hi[1] - G.lo[1])),
+                 wz = uniform_d(0.5 * (G.hi[2] - G.lo[2]));
     const uint32_t uoff = B.tile_uoff[t];
-    T.ucap = (int)((int64_t)tcnt * B.cap < B.ucap ? (int64_t)tcnt * B.cap : B.ucap);
-    if ((int64_t)uoff + T.ucap > B.upool) {
-      T.ucap = 0;
+    int ucap = (int)((int64_t)tcnt * B.cap < B.ucap ? (int64_t)tcnt * B.cap : B.ucap);
+    if ((int64_t)uoff + ucap > B.upool) {
+      ucap = 0;
       if (lane == 0) latch_error(B.status, SPH_E_NGB_CAPACITY, -1);
     }
-    T.U = B.tile_u + uoff;
-    T.usize = 0; T.cnt = 0;
-    T.row = crow[lane];
-    T.slot0 = reinterpret_cast<uint4*>(B.nbr16) + (T.valid ? p : 0) * NL;
-    T.gstride = B.capw * NL;
+    int32_t* U = B.tile_u + uoff;
+    // lengths are scaled so that the tile's reach is 100
+    const float wr = sqrtf((float)(wx * wx + wy * wy + wz * wz)) * (1.f + 1e-6f), hmx = (float)G.hmx * (1.f + 1e-6f);
+    const float sc = 100.f / (wr + 2.f * hmx * s1f + 1e-30f);
+    const float reach = (wr + hmx * s1f) * sc * (1.f + 1e-5f);
+    // scaled components of a particle at d from the tile's centre
+    auto scaled = [&](double dx, double dy, double dz, double hp) {
+      return make_float4((float)dx * sc, (float)dy * sc, (float)dz * sc, (float)hp * sc);
+    };
+    // the lane's particle of a product; one that is not there or out of every target's reach never hits.
+    // Returns |x|^2 + h'^2
+    auto lift = [&](float4& p, bool in, float& w) -> float {
+      const float r2 = p.x * p.x + p.y * p.y + p.z * p.z, h2 = p.w * p.w, far = reach + p.w;
+      w = r2 - h2;
+      if (!(in && r2 < far * far && h2 < 1e30f)) {   // (NaN fails too)
+        p = make_float4(0.f, 0.f, 0.f, 0.f);
+        w = 60000.f;
+        return 0.f;
+      }
+      return r2 + h2;
+    };
+    constexpr float kListMax = 3e4f;   // |x|^2 + h'^2 that FP16 takes
+    f16x8 T[2];
+    bool by_pair;
+    {
+      float w;
+      float4 p = scaled(min_image(pa.x - cx, (int)PER, box), min_image(pa.y - cy, (int)PER, box),
+                        min_image(pa.z - cz, (int)PER, box), ha);
+      const float m = lift(p, valid, w);
+      lift_operands<true>(p.x, p.y, p.z, p.w, w, T);
+      by_pair = __ballot(m > 0.5f * kListMax) != 0ull;
+    }
+    // a periodic box less than twice the reach across: images of a pair relative to the centre may differ
+    if (PER) by_pair = by_pair || fmax(wx, fmax(wy, wz)) + (G.hmx + g.hmax) * s1 * (1.0 + 1e-5) > 0.499 * box;
+    ListOut<NL> out;
+    out.ring = ring + kRingRow * lane;
+    out.slot0 = reinterpret_cast<uint4*>(B.nbr16) + (valid ? (int64_t)a : 0) * NL;
+    out.gstride = B.capw * NL;
+    out.cap_sl = B.cap_sl;
+    out.cnt = out.stored = 0;
+    int usize = 0;
+    // the FP64 decision of the lane's target on a waiting candidate
+    auto exact = [&](int j) -> bool {
+      const double4 q = B.pos4[cbi[j]];
+      const double dx = min_image(pa.x - q.x, (int)PER, box), dy = min_image(pa.y - q.y, (int)PER, box),
+                   dz = min_image(pa.z - q.z, (int)PER, box);
+      const double H = ha + q.w * s1w;
+      return fma(dz, dz, fma(dy, dy, dx * dx)) < H * H;
+    };
+    auto batch = [&](int nb) {
+      const bool in = lj < nb;
+      float4 p = cb[lj];
+      const int32_t b = in ? cbi[lj] : -1;
+      uint32_t m0, m1;
+      float w;
+      const float mag = lift(p, in, w);
+      if (!by_pair && !__ballot(mag > kListMax)) {
+        f16x8 C[2];
+        lift_operands<false>(p.x, p.y, p.z, p.w, w, C);
+        const float band = kBand * (0.5f * kListMax + (__ballot(mag > 0.5f * kListMax) ? kListMax : 0.5f * kListMax));
+        uint32_t q[2], near[2] = {0u, 0u};
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+          __builtin_amdgcn_sched_barrier(0);   // 32 of the products' registers at a time
+          const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          const f32x16 D0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(C[0], T[tb], zero, 0, 0, 0);
+          const f32x16 D1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(C[1], T[tb], zero, 0, 0, 0);
+          uint32_t q0 = 0u, q1 = 0u;
+          float least = 1e30f;
+#pragma unroll
+          for (int e = 15; e >= 0; --e) {
+            q0 = __builtin_amdgcn_alignbit(q0, __float_as_uint(D0[e]), 31u);
+            q1 = __builtin_amdgcn_alignbit(q1, __float_as_uint(D1[e]), 31u);
+            least = fminf(fminf(least, fabsf(D0[e])), fabsf(D1[e]));
+          }
+          q[tb] = q0 | (q1 << 16);
+          if (__ballot(least < band)) {
+            uint32_t n0 = 0u, n1 = 0u;
+#pragma unroll
+            for (int e = 15; e >= 0; --e) {
+              n0 = __builtin_amdgcn_alignbit(n0, __float_as_uint(fabsf(D0[e]) - band), 31u);
+              n1 = __builtin_amdgcn_alignbit(n1, __float_as_uint(fabsf(D1[e]) - band), 31u);
+            }
+            near[tb] = n0 | (n1 << 16);
+          }
+        }
+        // lane l < 32 holds rows 8 i + j (upper lanes: 8 i + 4 + j) of targets l and 32 + l: each
+        // lane receives both halves of its own target
+        m0 = q[0];
+        m1 = q[1];
+        swap32(m0, m1);
+        if (__ballot((near[0] | near[1]) != 0u)) {
+          swap32(near[0], near[1]);
+          auto decide = [&](uint32_t m, uint32_t left, int base) -> uint32_t {
+            while (left) {
+              const int k = __builtin_ctz(left);
+              left &= left - 1;
+              m = (m & ~(1u << k)) | ((exact(base + k) ? 1u : 0u) << k);
+            }
+            return m;
+          };
+          m0 = decide(m0, near[0], 0);
+          m1 = decide(m1, near[1], 32);
+        }
+      } else {
+        m0 = m1 = 0u;
+        for (int j = 0; j < nb; ++j) {
+          const uint32_t bit = (valid && exact(j) ? 1u : 0u) << (j & 31);
+          if (j < 32) m0 |= bit;
+          else m1 |= bit;
+        }
+      }
+      // a particle is not its own neighbour
+      const int ta = b - ts;   // the target this candidate is, if it is of the tile
+      if (__ballot(in && ta >= 0 && ta < tcnt)) {
+        self(lane) = 64u;
+        __syncthreads();
+        if (in && ta >= 0 && ta < tcnt) self(ta) = (uint32_t)lj;
+        __syncthreads();
+        const uint32_t sb = self(lane);
+        if (sb < 32u) m0 &= ~(1u << sb);
+        else if (sb < 64u) m1 &= ~(1u << (sb - 32u));
+      }
+      const uint32_t u0 = wave_or(m0), u1 = wave_or(m1);   // the batch's union members
+      if (!(u0 | u1)) return;
+      const int n0 = __builtin_popcount(u0);
+      {
+        const uint32_t uw = lj < 32 ? u0 : u1;
+        const int loc = usize + (lj < 32 ? 0 : n0) + __builtin_popcount(uw & ((1u << (lj & 31)) - 1u));
+        if (((uw >> (lj & 31)) & 1u) && loc < ucap) U[loc] = b;
+      }
+      out.append(m0, m1, u0, u1, usize, ucap > 0 ? ucap - 1 : 0);
+      usize += n0 + __builtin_popcount(u1);
+    };
     int pend = 0;   // candidates waiting in cb (wave-uniform)
     for (int l = 0; l < g.nlev; ++l) {
       LevelBox L;
@@ -607,98 +628,68 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         c_s[lane] = s;
         c_o[lane] = inc - cntc;
         __syncthreads();
-        // phase 2: gather candidates, 4 rounds of 64 per pass (loads of all 4 issued together),
-        // pre-test against the sub-boxes (small tiles: against their particles) and append the
-        // survivors to the batch in slot order
-        for (int q0 = 0; q0 < Tc; q0 += 256) {
-          double4 pbu[4];
-          int32_t bu[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int slot = q0 + 64 * u + lane;
-            pbu[u] = make_double4(0.0, 0.0, 0.0, 0.0);
-            bu[u] = -1;
-            if (slot < Tc) {
-              int lo_i = 0, hi_i = 63;   // last cell with c_o <= slot
-              while (lo_i < hi_i) {
-                const int mid = (lo_i + hi_i + 1) >> 1;
-                if (c_o[mid] <= slot) lo_i = mid;
-                else hi_i = mid - 1;
-              }
-              const int32_t sp = c_s[lo_i] + (slot - c_o[lo_i]);
-              bu[u] = (int32_t)B.perm[sp];
-              pbu[u] = B.pos_sorted[sp];
-            }
+        // phase 2: gather candidates 64 at a time, the next 64 in flight, test against the tile's box
+        // and append the survivors to the batch in slot order
+        auto fetch = [&](int slot, double4& pb) -> int32_t {
+          pb = make_double4(0.0, 0.0, 0.0, 0.0);
+          if (slot >= Tc) return -1;
+          int lo_i = 0, hi_i = 63;   // last cell with c_o <= slot
+          while (lo_i < hi_i) {
+            const int mid = (lo_i + hi_i + 1) >> 1;
+            if (c_o[mid] <= slot) lo_i = mid;
+            else hi_i = mid - 1;
           }
-          // pre-test of the 4 rounds: each sub-box (particle) is read from LDS once for all 4
-          bool pass[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) pass[u] = false;
-          if (small) {
-            for (int k = 0; k < tcnt; ++k) {
-              const double4 q = tp[k];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const double4 pb = pbu[u];
-                pass[u] |= candidate_test(min_image(q.x - pb.x, (int)PER, box), min_image(q.y - pb.y, (int)PER, box),
-                                          min_image(q.z - pb.z, (int)PER, box), q.w, pb.w, s1);
-              }
-            }
-          } else {
+          const int32_t sp = c_s[lo_i] + (slot - c_o[lo_i]);
+          pb = B.pos_sorted[sp];
+          return (int32_t)B.perm[sp];
+        };
+        double4 p0;
+        int32_t b0 = fetch(lane, p0);
 #pragma unroll 1
-            for (int gi = 0; gi < 8; ++gi) {
-              const double cx = sub[gi][0], cy = sub[gi][1], cz = sub[gi][2];
-              const double wx = sub[gi][3], wy = sub[gi][4], wz = sub[gi][5], hg = sub[gi][6];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const double4 pb = pbu[u];
-                const double ex = fmax(0.0, fabs(min_image(pb.x - cx, (int)PER, box)) - wx);
-                const double ey = fmax(0.0, fabs(min_image(pb.y - cy, (int)PER, box)) - wy);
-                const double ez = fmax(0.0, fabs(min_image(pb.z - cz, (int)PER, box)) - wz);
-                const double Rb = (hg + pb.w) * s1 * (1.0 + 1e-9);
-                pass[u] |= ex * ex + ey * ey + ez * ez < Rb * Rb && hg > 0.0;
-              }
-            }
+        for (int q0 = 0; q0 < Tc; q0 += 64) {
+          double4 p1;
+          const int32_t b1 = fetch(q0 + 64 + lane, p1);
+          const double dx = min_image(p0.x - cx, (int)PER, box), dy = min_image(p0.y - cy, (int)PER, box),
+                       dz = min_image(p0.z - cz, (int)PER, box);
+          const double ex = fmax(0.0, fabs(dx) - wx), ey = fmax(0.0, fabs(dy) - wy), ez = fmax(0.0, fabs(dz) - wz);
+          const double Rb = (G.hmx + p0.w) * s1 * (1.0 + 1e-9);
+          const bool pass = b0 >= 0 && ex * ex + ey * ey + ez * ez < Rb * Rb;
+          const unsigned long long m = __ballot(pass);
+          if (pass) {
+            const int k = pend + __popcll(m & lt);
+            cb[k] = scaled(dx, dy, dz, p0.w * s1w);
+            cbi[k] = b0;
           }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (q0 + 64 * u >= Tc) break;
-            const double4 pb = pbu[u];
-            pass[u] = pass[u] && bu[u] >= 0;
-            const unsigned long long m = __ballot(pass[u]);
-            if (pass[u]) {
-              const int k = pend + __popcll(m & lt);
-              cb[k] = make_double4(pb.x, pb.y, pb.z, pb.w * s1w);
-              cbi[k] = bu[u];
-            }
-            pend += __popcll(m);
+          pend += __popcll(m);
+          __syncthreads();
+          if (pend >= 64) {   // phase 3 on a full batch
+            batch(64);
+            const int rest = pend - 64;
+            float4 mv = make_float4(0.f, 0.f, 0.f, 0.f);
+            int32_t mi = 0;
+            if (lane < rest) { mv = cb[64 + lane]; mi = cbi[64 + lane]; }
             __syncthreads();
-            if (pend >= 64) {   // phase 3 on a full batch
-              run_batch<NL, 64, PER>(B, T, cb, cbi, 64, box);
-              const int rest = pend - 64;
-              double4 mv = make_double4(0.0, 0.0, 0.0, 0.0);
-              int32_t mi = 0;
-              if (lane < rest) { mv = cb[64 + lane]; mi = cbi[64 + lane]; }
-              __syncthreads();
-              if (lane < rest) { cb[lane] = mv; cbi[lane] = mi; }
-              pend = rest;
-              __syncthreads();
-            }
+            if (lane < rest) { cb[lane] = mv; cbi[lane] = mi; }
+            pend = rest;
+            __syncthreads();
           }
+          p0 = p1;
+          b0 = b1;
         }
       }
     }
-    if (pend > 0) run_batch<NL, 0, PER>(B, T, cb, cbi, pend, box);
+    if (pend > 0) batch(pend);
     __syncthreads();
-    if (T.valid && T.cnt <= B.cap && (T.cnt & (8 * NL - 1))) {
-      // the partly filled last row: slots s < r hold a partial last group g (a slot's count is at
-      // most that of slot 0, so the capacity test of slot 0 covers them all)
-      const int r = T.cnt & (8 * NL - 1), g = T.cnt / (8 * NL);
-      if ((T.cnt + NL - 1) / NL <= B.cap_sl) store_row_groups<NL>(T, g, r < NL ? r : NL);
+    // what is left in the rings: whole groups, then a partly filled last one (slots s < r of it
+    // hold entries; a slot's count is at most that of slot 0, whose capacity covers them all)
+    if (valid && out.cnt <= B.cap) {
+      while (out.cnt - 8 * NL * out.stored >= 8 * NL) out.store_group(NL);
+      const int r = out.cnt - 8 * NL * out.stored;
+      if (r > 0) out.store_group(r < NL ? r : NL);
     }
-    if (T.valid) B.count[p] = T.cnt < B.cap ? T.cnt : B.cap;
-    if (lane == 0) B.tile_usize[t] = T.usize < T.ucap ? T.usize : T.ucap;
-    if (T.usize > T.ucap || T.cnt > B.cap) latch_error(B.status, SPH_E_NGB_CAPACITY, (int)(T.valid ? T.a : -1));
+    if (valid) B.count[a] = out.cnt < B.cap ? out.cnt : B.cap;
+    if (lane == 0) B.tile_usize[t] = usize < ucap ? usize : ucap;
+    if (usize > ucap || out.cnt > B.cap) latch_error(B.status, SPH_E_NGB_CAPACITY, valid ? a : -1);
   }
 }
 

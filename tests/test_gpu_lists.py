@@ -41,7 +41,7 @@ def _cloud(name, rng):
     return x, np.full(400, 0.12), 1.0
 
 
-def _brute(x, h, box):
+def _brute(x, h, box, s1=1.0):
     n = h.size
     out = []
     for a in range(n):
@@ -49,16 +49,14 @@ def _brute(x, h, box):
         if box > 0:
             d = np.where(d > 0.5 * box, d - box, np.where(d < -0.5 * box, d + box, d))
         r2 = (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]
-        H = h[a] + h
+        H = (h[a] + h) * s1
         hit = r2 < H * H
         hit[a] = False
         out.append(np.nonzero(hit)[0])
     return out
 
 
-@pytest.mark.parametrize("name", ["one", "ragged", "tiles", "wide_h", "outliers", "pile", "periodic", "periodic_small"])
-@pytest.mark.parametrize("precision,lanes,skin", [("FP64", 4, 0.08), ("FP32", 4, 0.14), ("FP64", 1, 0.0), ("FP32", 2, 0.3)])
-def test_lists_equal_brute_force(name, precision, lanes, skin):
+def _evaluate(name, precision, lanes, skin):
     from paper_2107_07315_amd import sph
     x, h, box = _cloud(name, np.random.Generator(np.random.PCG64(7)))
     n = h.size
@@ -71,6 +69,14 @@ def test_lists_equal_brute_force(name, precision, lanes, skin):
     st = sph.DeviceState(arrays)
     ctx.evaluate(st)
     ctx.sph_sync()
+    return ctx, st, x, h, box
+
+
+@pytest.mark.parametrize("name", ["one", "ragged", "tiles", "wide_h", "outliers", "pile", "periodic", "periodic_small"])
+@pytest.mark.parametrize("precision,lanes,skin", [("FP64", 4, 0.08), ("FP32", 4, 0.14), ("FP64", 1, 0.0), ("FP32", 2, 0.3)])
+def test_lists_equal_brute_force(name, precision, lanes, skin):
+    ctx, st, x, h, box = _evaluate(name, precision, lanes, skin)
+    n = h.size
     off, ids = ctx.sph_export_neighbours(n)
     order = st.numpy(["id"])["id"]
     want = _brute(x, h, box)
@@ -81,4 +87,15 @@ def test_lists_equal_brute_force(name, precision, lanes, skin):
     s = ctx.sph_neighbour_stats()
     assert s["pairs"] == sum(v.size for v in want)
     assert s["candidates"] >= s["pairs"]
+    ctx.close()
+
+
+@pytest.mark.parametrize("name", ["ragged", "tiles", "wide_h", "outliers", "pile", "periodic", "periodic_small"])
+def test_fp32_candidates_are_the_fp64_decision(name):
+    """The FP32 lists decide the order of the FP32 sums, so they hold the candidates of the FP64 test at
+    the skin-widened support and no others (the matrix-core test leaves the close pairs to it)."""
+    skin = 0.14
+    ctx, _, x, h, box = _evaluate(name, "FP32", 4, skin)
+    want = sum(v.size for v in _brute(x, h, box, 1.0 + skin))
+    assert ctx.sph_neighbour_stats()["candidates"] == want
     ctx.close()
