@@ -29,6 +29,7 @@ struct KdkArgs {
   // was cleared; a step finds a smaller non-zero value there when an earlier step (run ahead of
   // the host's test) broke the bound, and then leaves the state alone.  flag == nullptr: no test
   uint32_t check_id; uint32_t* flag;
+  uint32_t* host_flag;   // pinned host copy of *flag, written by the particle that raises it
   // positions and h read from and written to pos4 only (inside a multi-step call the public
   // x, y, z, h are brought up to date once, before a list build and at the end of the call)
   bool deferred;
@@ -116,8 +117,9 @@ __device__ __forceinline__ void kick_drift_from(const KdkArgs& K, int64_t a, con
     const int per = K.p.periodic;
     const double box = K.p.box;
     if (skin_exceeded(min_image(xn - b.x, per, box), min_image(yn - b.y, per, box), min_image(zn - b.z, per, box),
-                      h, b, K.grid->skin))
-      atomicMax(K.flag, K.check_id);
+                      h, b, K.grid->skin) &&
+        atomicMax(K.flag, K.check_id) < K.check_id)
+      __hip_atomic_store(K.host_flag, K.check_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   K.vx[a] = vh[0] + hdt * ax;
   K.vy[a] = vh[1] + hdt * ay;
@@ -246,6 +248,7 @@ KdkArgs make_kdk(sph_ctx* c, sph_state* st, double dt) {
   K.grid = c->grid;
   K.check_id = c->check_id;
   K.flag = nullptr;
+  K.host_flag = c->step_host;
   K.deferred = false;
   K.cont = c->p.density_mode == SPH_DENS_CONTINUITY;
   K.Dst = st->D;
@@ -268,7 +271,10 @@ __global__ __launch_bounds__(kB) void k_unpack_pos(const double4* __restrict__ p
   h[a] = q.w;
 }
 
-__global__ void k_flag_clear(uint32_t* f) { *f = 0u; }   // a kernel, not a memset: graph-safe
+__global__ void k_flag_clear(uint32_t* f, uint32_t* host) {   // a kernel, not a memset: graph-safe
+  *f = 0u;
+  __hip_atomic_store(host, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Courant step of an evaluation: dtw[slot] = cfl * min_a h_a / (c_L,a + |v_a|) from the per-block
 // minima of the density epilogue (one workgroup, a fixed reduction order).
@@ -354,7 +360,7 @@ sph_status launch_dt_init(sph_ctx* c) {
 }
 
 sph_status launch_flag_clear(sph_ctx* c) {
-  hipLaunchKernelGGL(k_flag_clear, dim3(1), dim3(1), 0, c->stream, c->drift_flag);
+  hipLaunchKernelGGL(k_flag_clear, dim3(1), dim3(1), 0, c->stream, c->drift_flag, c->step_host);
   HIP_TRY(hipGetLastError());
   return SPH_OK;
 }

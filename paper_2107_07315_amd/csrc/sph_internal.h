@@ -308,10 +308,11 @@ struct sph_ctx {
   uint32_t g_epoch;
   uint32_t check_id;    // value a failed drift test writes when no step number applies (1)
   uint32_t* drift_flag; // device word: largest check id (step number) that saw a skin violation
-  uint32_t* drift_host; // pinned host copy
+  uint32_t* drift_host; // pinned host copies of words read back
+  uint32_t* step_host;  // pinned host word that follows drift_flag in the kicks (coherent memory)
   uint32_t eval_seq;    // step number of a run-ahead evaluation being queued (0: none)
   bool pos_deferred;    // st->x, y, z, h lag behind pos4 (kicks inside a multi-step call)
-  hipEvent_t step_ev[2];   // run-ahead steps: the skin-test word of a step has reached the host
+  hipEvent_t step_ev[2];   // run-ahead steps: a step's work, and with it its skin test's word, is complete
   int64_t rebuilds;
   double4* pos_build;   // x, y, z, h at the last candidate-list build
   // grid and sort
