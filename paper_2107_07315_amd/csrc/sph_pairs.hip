@@ -162,6 +162,19 @@ struct PassArgs {
 
 constexpr int kNone = 0x7fffffff;
 
+// What a thread of a pair pass does: L M consecutive lanes serve a target, M of them to each of its L
+// slot lists (M > 1: each takes 8 / M consecutive entries of every group of 8).  A workgroup of 64 L
+// threads then serves 64 / M targets, so a tile is the work of M workgroups ("parts").
+template <int L, int M>
+struct TargetLane {
+  int q, slot, part;   // target among the workgroup's, its slot list, and which of the slot's M lanes
+  bool lead;           // the target's first lane
+  __device__ __forceinline__ explicit TargetLane(int t) : q(t / (L * M)), slot(t % L), part(t / L % M), lead(t % (L * M) == 0) {}
+  __device__ __forceinline__ int first(int of) const { return 64 / M * of; }
+  __device__ __forceinline__ int target(int of) const { return first(of) + q; }
+  __device__ __forceinline__ bool takes(int k) const { return M == 1 || (k & 7) / (8 / M) == part; }
+};
+
 // Per-lane walk over a slot list stored as 16-byte groups of 8 16-bit local indices (group g at
 // base + g * gstride).  The group after the current one is always in flight (8 entries ahead);
 // the current group is consumed by funnel shifts.
@@ -231,33 +244,47 @@ __device__ __forceinline__ void walk_groups(const uint4* base, int64_t gstride, 
   }
 }
 
+// The lane's part of a slot list's group where M lanes share a slot (8 / M consecutive entries each).
+template <int M> struct GroupPart;
+template <> struct GroupPart<1> { using T = uint4; };
+template <> struct GroupPart<2> { using T = uint2; };
+template <> struct GroupPart<4> { using T = uint32_t; };
+template <int M>
+__device__ __forceinline__ int part_entry(const typename GroupPart<M>::T& q, int i) {
+  uint32_t w[4 / M];
+  __builtin_memcpy(w, &q, sizeof(w));
+  return (int)((i & 1) ? (w[i / 2] >> 16) : (w[i / 2] & 0xffffu));
+}
+
 // Software-pipelined walk of a whole slot list when the tile's union sits in LDS as one chunk.
 // Every lane of the wave runs the wave's longest list (cmax, wave-uniform), so the body is
 // straight-line code with no per-entry branch: entries past the lane's own count read the records
 // of LDS slot `pad`, a sentinel particle far from every target (its pair terms are exactly zero,
 // with no overflow), and pass no list entry on.  The records of the next entry are read from LDS
 // (load(j)) before the current entry's arithmetic (f(loc, rec)); the next 16-byte group of 8
-// entries is read from memory one group ahead; group_end() runs after every group of 8.
-template <typename Ld, typename F, typename G>
-__device__ __forceinline__ void walk_groups_pf(const uint4* base, int64_t gstride, int cnt, int cmax, int pad,
+// entries is read from memory one group ahead; group_end() runs after every group of 8.  With M > 1
+// the lane takes part `part` of every group.
+template <int M, typename Ld, typename F, typename G>
+__device__ __forceinline__ void walk_groups_pf(const uint4* base, int64_t gstride, int part, int cnt, int cmax, int pad,
                                                Ld&& load, F&& f, G&& group_end) {
-  auto ent = [](const uint4& q, int i) -> int {
-    const uint32_t w = i < 2 ? q.x : (i < 4 ? q.y : (i < 6 ? q.z : q.w));
-    return (int)((i & 1) ? (w >> 16) : (w & 0xffffu));
-  };
-  uint4 g = make_uint4(0u, 0u, 0u, 0u);
-  if (cnt > 0) g = base[0];
+  using Q = typename GroupPart<M>::T;
+  constexpr int E = 8 / M;
+  auto ent = [](const Q& q, int i) -> int { return part_entry<M>(q, i); };
+  auto at = [&](const uint4* q) -> Q { return reinterpret_cast<const Q*>(q)[part]; };
+  const int o = E * part;   // the lane's first entry in a group
+  Q g{};
+  if (o < cnt) g = at(base);
   const uint4* gp = base + gstride;
-  auto rec = load(cnt > 0 ? ent(g, 0) : pad);
+  auto rec = load(o < cnt ? ent(g, 0) : pad);
   for (int k0 = 0; k0 < cmax; k0 += 8) {
-    uint4 nx = g;
-    if (k0 + 8 < cnt) nx = *gp;
+    Q nx = g;
+    if (k0 + 8 + o < cnt) nx = at(gp);
     gp += gstride;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < E; ++i) {
       if (k0 + i >= cmax) break;   // wave-uniform
-      const int k1 = k0 + i + 1;
-      const auto nrec = load(k1 < cnt ? (i < 7 ? ent(g, i + 1) : ent(nx, 0)) : pad);
+      const int k1 = i < E - 1 ? k0 + o + i + 1 : k0 + 8 + o;
+      const auto nrec = load(k1 < cnt ? (i < E - 1 ? ent(g, i + 1) : ent(nx, 0)) : pad);
       f(ent(g, i), rec);
       rec = nrec;
     }
@@ -590,7 +617,7 @@ constexpr float kBand = 3.814697265625e-06f;   // 2^-18
 //   FP32 (R = float): union records staged as FP32 coordinates relative to the tile's first
 //   particle (16 bytes), the decision taken in FP32 and, inside the guard band kBand, again
 //   exactly from the FP64 positions; the lists are the same as in FP64.
-template <typename R, int KER, bool PER, int L, bool XL>
+template <typename R, int KER, bool PER, int L, int M, bool XL>
 __global__ __launch_bounds__(64 * L)
 __attribute__((amdgpu_waves_per_eu(std::is_same<R, float>::value ? 5 : 4)))
 void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
@@ -605,15 +632,20 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
   __shared__ __align__(16) uint16_t lring[XL ? 64 * L : 1][8 * RB];   // per-lane staging of the exact lists
   const double box = A.p.box, half = 0.5 * box;
   const float boxf = (float)box, halff = (float)half;
-  const int tl = threadIdx.x / L, sub = threadIdx.x % L;
+  static_assert(M == 1 || !XL, "the exact lists are written by L lanes per target");
+  const TargetLane<L, M> me(threadIdx.x);
+  const int sub = me.slot;
   if (threadIdx.x == 0) {   // the sentinel: far from every target, h = 0 (no neighbour, W = 0)
     if constexpr (F32) sp.put(CHU, make_float4(1e10f, 1e10f, 1e10f, 0.0f));
     else sp.put(CHU, make_double4(1e10, 1e10, 1e10, 0.0));
   }
-  const int64_t ntl = num_tiles(A);
+  const int64_t ntl = num_tiles(A) * M;
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntl); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
-    const int64_t tile = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
-    if (tile >= ntl) break;
+    const int64_t item = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
+    if (item >= ntl) break;
+    const int64_t tile = item / M;
+    const int tl = me.target((int)(item % M));
+    if (M > 1 && me.first((int)(item % M)) >= A.tile_cnt[tile]) continue;   // no target left for this part
   TileWalk tw;
   tw.begin(A, tile, tl);
   const int total = tw.valid ? A.cnt_s[tw.p] : 0;
@@ -679,8 +711,8 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
     __syncthreads();
     stage(0);
     __syncthreads();
-    walk_groups_pf(
-        lst, A.capw * L, cnt, wave_max_i(cnt), CHU, [&](int j) { return sp.get(j); },
+    walk_groups_pf<M>(
+        lst, A.capw * L, me.part, cnt, wave_max_i(cnt), CHU, [&](int j) { return sp.get(j); },
         [&](int loc, const SR& pb) {
           cand(loc, pb, [&](int l, bool h) {
             if constexpr (XL) wr.put_unchecked(l, h);
@@ -699,8 +731,9 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
       const int cend = c0 + CHU;
       while (tw.next < cend) {
         const int loc = tw.next;
+        const bool mine = me.takes(tw.k);
         tw.advance();
-        cand(loc, sp.get(loc - c0), [&](int l, bool h) {
+        if (mine) cand(loc, sp.get(loc - c0), [&](int l, bool h) {
           if constexpr (XL) wr.put(l, h);
           else wr.n += h ? 1 : 0;
         });
@@ -708,14 +741,14 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
     }
   }
   if constexpr (XL) wr.flush();
-  sum = lane_group_sum<L>(sum);
-  const int nexact = lane_group_sum<L>(wr.n);
+  sum = lane_group_sum<L * M>(sum);
+  const int nexact = lane_group_sum<L * M>(wr.n);
   if (tw.valid) {
     if constexpr (XL) xcount_sl[slot] = wr.n < A.cap_sl ? wr.n : A.cap_sl;
-    if (sub == 0) xcount[a] = nexact < A.cap ? nexact : A.cap;
+    if (me.lead) xcount[a] = nexact < A.cap ? nexact : A.cap;
     if (nexact > A.cap || wr.n > A.cap_sl) latch_error(A.status, SPH_E_NGB_CAPACITY, (int)a);
   }
-  if (tw.valid && sub == 0) {
+  if (tw.valid && me.lead) {
     const double W0 = wendland_self<double>(KER, pa.w);   // the particle's own term
     // the FP32 sum holds kernel values / 8 (kern_W_unit_eighth); the factor 8 is exact
     O.D[a] = particle_mass(A, a) * fma((F32 ? 8.0 : 1.0) * kern_W_const<KER>(), (double)sum, W0);
@@ -850,7 +883,7 @@ __global__ void k_word_clear(int32_t* w) { *w = 0; }   // a kernel, not a memset
 // ---- velocity gradient and stress rate ---------------------------------------------------------
 // Lane g of the L-wave workgroup walks the exact slot list (g / L, g % L) written by the density
 // pass; the partial velocity gradients of a target's L lanes are added before the epilogue.
-template <typename R, int KER, bool PER, int L>
+template <typename R, int KER, bool PER, int L, int M>
 __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Rec<R>::P4* __restrict__ pos,
                                                    const typename Rec<R>::V4* __restrict__ fv,
                                                    const typename Rec<R>::A2* __restrict__ fa,
@@ -859,14 +892,16 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
   using P4 = typename Rec<R>::P4;
   using V4 = typename Rec<R>::V4;
   constexpr int CH = Rec<R>::CH_S * L;
-  const int tl = threadIdx.x / L, sub = threadIdx.x % L;
+  const TargetLane<L, M> me(threadIdx.x);
+  const int sub = me.slot;
   __shared__ Lds4<R, CH> sp, sv;
   const R box = (R)A.p.box, half = (R)0.5 * box;
   // only the tiles of the work list (tiles with a type-1 particle); every other particle's rates
   // are zero since the last build
   const int64_t nst = cancelled(A) ? 0 : (int64_t)A.grid->nstress;
-  for (int64_t w = blockIdx.x; w < nst; w += gridDim.x) {
-    const int64_t tile = A.stress_tiles[w];
+  for (int64_t w = blockIdx.x; w < nst * M; w += gridDim.x) {
+    const int64_t tile = A.stress_tiles[w / M];
+    const int tl = me.target((int)(w % M));
   TileWalk tw;
   tw.begin(A, tile, tl);
   const int64_t a = tw.a;
@@ -874,7 +909,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
   const int64_t n = A.n;
   const typename Rec<R>::A2 faa = tw.valid ? fa[a] : typename Rec<R>::A2{0, 1};
   const bool stressed = tw.valid && faa.y < 0;
-  if (tw.valid && !stressed && sub == 0) {  // fluid particle (or fluidized): no deviatoric stress evolution
+  if (tw.valid && !stressed && me.lead) {  // fluid particle (or fluidized): no deviatoric stress evolution
     for (int c = 0; c < 6; ++c) dSdt[c * n + a] = 0.0;
     sdot[a] = 0.0;
   }
@@ -906,9 +941,9 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
                             [&](int32_t b) { return Recs{pos[b], fv[b]}; },
                             [&](int j, const Recs& r) { sp.put(j, r.p); sv.put(j, r.v); });
   };
-  if (std::is_same<R, float>::value && tw.usize < CH) {
-    // FP32 with the whole union in one chunk: pipelined group walk, LDS slot CH - 1 the sentinel
-    // (far away, h = 0: F = 0)
+  if (tw.usize < CH) {
+    // the whole union in one chunk: pipelined group walk, LDS slot CH - 1 the sentinel (far away,
+    // h = 0: F = 0)
     __syncthreads();
     stage(0, CH - 1);
     if (threadIdx.x == 0) {
@@ -917,8 +952,8 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
     }
     __syncthreads();
     const int cnt = stressed ? pass_count<L>(A, tw.p, sub) : 0;
-    walk_groups_pf(
-        pass_list<L>(A, slot), A.capw * L, cnt, wave_max_i(cnt), CH - 1,
+    walk_groups_pf<M>(
+        pass_list<L>(A, slot), A.capw * L, me.part, cnt, wave_max_i(cnt), CH - 1,
         [&](int j) { return Recs{sp.get(j), sv.get(j)}; }, [&](int, const Recs& r) { pair(r); }, [] {});
   } else {
     tw.start(pass_list<L>(A, slot), A.capw * L, stressed ? pass_count<L>(A, tw.p, sub) : 0);
@@ -929,16 +964,17 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
       const int cend = c0 + CH;
       while (tw.next < cend) {
         const int j = tw.next - c0;
+        const bool mine = me.takes(tw.k);
         tw.advance();
-        pair(Recs{sp.get(j), sv.get(j)});
+        if (mine) pair(Recs{sp.get(j), sv.get(j)});
       }
     }
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int jj = 0; jj < 3; ++jj) G[i][jj] = lane_group_sum<L>(G[i][jj]);
-  if (!stressed || sub != 0) continue;
+    for (int jj = 0; jj < 3; ++jj) G[i][jj] = lane_group_sum<L * M>(G[i][jj]);
+  if (!stressed || !me.lead) continue;
   const double m = particle_mass(A, a) * kern_F_const<KER>();
   const double D = -2.0 * (double)faa.y;  // stressed particles store -D/2
   const double iD2 = m / (2.0 * D);
@@ -1034,7 +1070,7 @@ __device__ __forceinline__ void ext_accel(const PassArgs& A, const ForceOut& O, 
 // for workloads where most tiles hold stressed particles (otherwise each stressed pair reads the
 // neighbour's union index and six S/D^2 values from memory).
 constexpr int kXDD = 1, kXGP = 2, kXSL = 4;
-template <typename R, int KER, bool PER, int L, int XS>
+template <typename R, int KER, bool PER, int L, int M, int XS>
 __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) void k_forces(PassArgs A, const typename Rec<R>::P4* __restrict__ pos,
                                                    const typename Rec<R>::V4* __restrict__ fv,
                                                    const typename Rec<R>::A2* __restrict__ fa,
@@ -1047,7 +1083,8 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   static_assert(!SL || std::is_same<R, float>::value, "S/D^2 in LDS: FP32 records only");
   constexpr int CH = (SL ? Rec<float>::CH_FS : Rec<R>::CH_F) * L;
   constexpr int CHU = CH - 1;   // union records per chunk; slot CHU holds the walk's sentinel
-  const int tl = threadIdx.x / L, sub = threadIdx.x % L;
+  const TargetLane<L, M> me(threadIdx.x);
+  const int sub = me.slot;
   __shared__ Lds4<R, CH> sp, sv;
   __shared__ A2 sa2[CH];
   __shared__ R ssg[SL ? 6 : 1][SL ? CH : 1];   // kXSL: S/D^2 of the staged members (0 if unstressed)
@@ -1057,10 +1094,13 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
     sv.put(CHU, V4{(R)0, (R)0, (R)0, (R)0});
     sa2[CHU] = A2{(R)0, (R)1};
   }
-  const int64_t ntl = num_tiles(A);
+  const int64_t ntl = num_tiles(A) * M;
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntl); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
-    const int64_t tile = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
-    if (tile >= ntl) break;
+    const int64_t item = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
+    if (item >= ntl) break;
+    const int64_t tile = item / M;
+    const int tl = me.target((int)(item % M));
+    if (M > 1 && me.first((int)(item % M)) >= A.tile_cnt[tile]) continue;   // no target left for this part
   TileWalk tw;
   tw.begin(A, tile, tl);
   const int64_t a = tw.a;
@@ -1177,10 +1217,10 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
     const bool any_st = stress_tile();
     auto ld = [&](int j) { return Recs{sp.get(j), sv.get(j), sa2[j]}; };
     if (any_st)
-      walk_groups_pf(lst, A.capw * L, cnt, wave_max_i(cnt), CHU, ld, pair, [] {});
+      walk_groups_pf<M>(lst, A.capw * L, me.part, cnt, wave_max_i(cnt), CHU, ld, pair, [] {});
     else
-      walk_groups_pf(
-          lst, A.capw * L, cnt, wave_max_i(cnt), CHU, ld,
+      walk_groups_pf<M>(
+          lst, A.capw * L, me.part, cnt, wave_max_i(cnt), CHU, ld,
           [&](int loc, const Recs& r) { pair_st(loc, r, std::false_type{}); }, [] {});
   } else {
     const bool any_st = sizeof(R) == 4 || XS != 0 || stress_tile();
@@ -1194,9 +1234,10 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
       auto walk = [&](auto ST) {
         while (tw.next < cend) {
           const int loc = tw.next;
+          const bool mine = me.takes(tw.k);
           tw.advance();
           const int j = loc - c0;
-          pair_st(loc, Recs{sp.get(j), sv.get(j), sa2[j]}, ST);
+          if (mine) pair_st(loc, Recs{sp.get(j), sv.get(j), sa2[j]}, ST);
         }
       };
       // (FP64 only: in FP32 this walk serves the rare large unions, and a second copy slowed the
@@ -1209,13 +1250,13 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    AP[i] = lane_group_sum<L>(AP[i]);
-    AS[i] = lane_group_sum<L>(AS[i]);
+    AP[i] = lane_group_sum<L * M>(AP[i]);
+    AS[i] = lane_group_sum<L * M>(AS[i]);
   }
-  ud = lane_group_sum<L>(ud);
-  if constexpr (DD) dd = lane_group_sum<L>(dd);
-  if constexpr (GP) gp = lane_group_sum<L>(gp);
-  if (!tw.valid || sub != 0) continue;
+  ud = lane_group_sum<L * M>(ud);
+  if constexpr (DD) dd = lane_group_sum<L * M>(dd);
+  if constexpr (GP) gp = lane_group_sum<L * M>(gp);
+  if (!tw.valid || !me.lead) continue;
   const double m = particle_mass(A, a) * kern_F_const<KER>();
   double APd[3] = {m * (double)AP[0], m * (double)AP[1], m * (double)AP[2]};
   double ASd[3] = {m * (double)AS[0], m * (double)AS[1], m * (double)AS[2]};
@@ -1322,20 +1363,36 @@ static void dispatch_cfg(int kernel, int periodic, Fn&& f) {
 
 // one workgroup per tile (up to 65536), or a persistent grid of pass_blocks (a multiple of the
 // XCD count) that loops over the tiles
-static dim3 pass_grid(const sph_ctx* c) {
+static dim3 pass_grid(const sph_ctx* c, int split) {
   if (c->p.pass_blocks > 0) {
     const int64_t b = ((int64_t)c->p.pass_blocks + SPH_XCD - 1) / SPH_XCD * SPH_XCD;
     return dim3((unsigned)(b < 65536 ? b : 65536));
   }
-  return dim3(tile_launch(c));
+  return dim3(tile_launch(c) * (unsigned)split);
 }
 
-// Calls f(L) with the pair passes' lanes per target as a compile-time constant.
+// Lanes per slot list of the pair passes (FP64, 4 slots): with few tiles each tile is shared by 2 or 4
+// workgroups while that still gives about one workgroup per CU (256).  A pass over few tiles waits for one
+// workgroup's walk, which the lanes divide; beyond one workgroup per CU the unions staged M times cost
+// more than that.  Ten steps, us, at M = 1 / 2 / 4: lattice of 64 tiles 644 / 537 / 483, of 132
+// 732 / 710 / 765, of 240 743 / 749 / 885; relaxation of 65 tiles 501 / 460 / 461, of 156 479 / 483 / 500.
+// FP32 sums keep their order.
+static int pass_split(const sph_ctx* c) {
+  constexpr unsigned kFill = 256 + 16;
+  if (c->p.precision == SPH_FP32 || pass_lanes(c->p) != 4) return 1;
+  return 4 * c->ntiles <= kFill ? 4 : (2 * c->ntiles <= kFill ? 2 : 1);
+}
+
+// Calls f(L, M) with the pair passes' slots per target and the lanes per slot (pass_split) as
+// compile-time constants.
 template <typename Fn>
-static void dispatch_lanes(int lanes, Fn&& f) {
-  if (lanes == 4) f(std::integral_constant<int, 4>{});
-  else if (lanes == 2) f(std::integral_constant<int, 2>{});
-  else f(std::integral_constant<int, 1>{});
+static void dispatch_lanes(int lanes, int split, Fn&& f) {
+  using std::integral_constant;
+  if (lanes == 4 && split == 4) f(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+  else if (lanes == 4 && split == 2) f(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+  else if (lanes == 4) f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+  else if (lanes == 2) f(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+  else f(integral_constant<int, 1>{}, integral_constant<int, 1>{});
 }
 
 static DensOut dens_out(sph_ctx* c, sph_state* st) {
@@ -1358,19 +1415,20 @@ static DensOut dens_out(sph_ctx* c, sph_state* st) {
 sph_status launch_density(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
   DensOut O = dens_out(c, st);
-  const dim3 g = pass_grid(c);
+  const int split = pass_split(c);
+  const dim3 g = pass_grid(c, split);
   const bool f32 = c->p.precision == SPH_FP32;
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
-    dispatch_lanes(pass_lanes(c->p), [&](auto LL) {
+    dispatch_lanes(pass_lanes(c->p), split, [&](auto LL, auto MM) {
       constexpr int KER = decltype(K)::value;
       constexpr bool PER = decltype(P)::value;
-      constexpr int L = decltype(LL)::value;
+      constexpr int L = decltype(LL)::value, M = decltype(MM)::value;
       const dim3 b(64 * L);
       if (f32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, false>), g, b, 0, c->stream, A, c->pos4, O,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, 1, false>), g, b, 0, c->stream, A, c->pos4, O,
                            nullptr, c->nbr_count, nullptr);
       else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, false>), g, b, 0, c->stream, A, c->pos4, O,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, M, false>), g, b, 0, c->stream, A, c->pos4, O,
                            nullptr, c->nbr_count, nullptr);
     });
   });
@@ -1387,19 +1445,20 @@ sph_status launch_exact_lists(sph_ctx* c) {
   A.stop = nullptr;
   DensOut O{};
   O.D = c->tmp;
-  const dim3 g = pass_grid(c);
+  const int split = 1;
+  const dim3 g = pass_grid(c, split);
   const bool f32 = c->p.precision == SPH_FP32;
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
-    dispatch_lanes(pass_lanes(c->p), [&](auto LL) {
+    dispatch_lanes(pass_lanes(c->p), split, [&](auto LL, auto MM) {
       constexpr int KER = decltype(K)::value;
       constexpr bool PER = decltype(P)::value;
       constexpr int L = decltype(LL)::value;
       const dim3 b(64 * L);
       if (f32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, true>), g, b, 0, c->stream, A, c->pos4, O,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, 1, true>), g, b, 0, c->stream, A, c->pos4, O,
                            c->nbr16, c->nbr_count, c->nbr_count_sl);
       else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, true>), g, b, 0, c->stream, A, c->pos4,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, 1, true>), g, b, 0, c->stream, A, c->pos4,
                            O, c->nbr16, c->nbr_count, c->nbr_count_sl);
     });
   });
@@ -1445,19 +1504,20 @@ sph_status launch_eos(sph_ctx* c, sph_state* st) {
 sph_status launch_stress(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
   // loops over the work list
-  const unsigned most = (unsigned)(c->cap_tiles < 4096 ? c->cap_tiles : 4096);
-  const dim3 g(c->p.graph || c->nstress > most ? most : (c->nstress > 0 ? c->nstress : 1u));
+  const int split = pass_split(c);
+  const unsigned most = (unsigned)(c->cap_tiles < 4096 ? c->cap_tiles : 4096), want = c->nstress * (unsigned)split;
+  const dim3 g(c->p.graph || want > most ? most : (want > 0 ? want : 1u));
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
-    dispatch_lanes(pass_lanes(c->p), [&](auto LL) {
+    dispatch_lanes(pass_lanes(c->p), split, [&](auto LL, auto MM) {
       constexpr int KER = decltype(K)::value;
       constexpr bool PER = decltype(P)::value;
-      constexpr int L = decltype(LL)::value;
+      constexpr int L = decltype(LL)::value, M = decltype(MM)::value;
       const dim3 b(64 * L);
       if (c->p.precision == SPH_FP32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<float, KER, PER, L>), g, b, 0, c->stream, A, c->pos4f, c->fvf,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<float, KER, PER, L, 1>), g, b, 0, c->stream, A, c->pos4f, c->fvf,
                            c->faf, st->S, c->mu, st->dSdt, c->sdot);
       else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<double, KER, PER, L>), g, b, 0, c->stream, A, c->pos4, c->fv,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<double, KER, PER, L, M>), g, b, 0, c->stream, A, c->pos4, c->fv,
                            c->fa, st->S, c->mu, st->dSdt, c->sdot);
     });
   });
@@ -1471,26 +1531,27 @@ sph_status launch_forces(sph_ctx* c, sph_state* st) {
   const int xs = (c->p.dtP_mode == SPH_DTP_LAGGED && c->p.background == SPH_TOV) ? kXGP
                  : (c->p.density_mode == SPH_DENS_CONTINUITY || c->p.energy_mode == SPH_ENERGY_FIRST_LAW) ? kXDD
                                                                                                         : 0;
-  const dim3 g = pass_grid(c);
+  const int split = pass_split(c);
+  const dim3 g = pass_grid(c, split);
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
-    dispatch_lanes(pass_lanes(c->p), [&](auto LL) {
+    dispatch_lanes(pass_lanes(c->p), split, [&](auto LL, auto MM) {
       constexpr int KER = decltype(K)::value;
       constexpr bool PER = decltype(P)::value;
-      constexpr int L = decltype(LL)::value;
+      constexpr int L = decltype(LL)::value, M = decltype(MM)::value;
       const dim3 b(64 * L);
       auto launch = [&](auto XX) {
         constexpr int X = decltype(XX)::value;
         if (c->p.precision == SPH_FP32)
-          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<float, KER, PER, L, X>), g, b, 0, c->stream, A, c->pos4f,
+          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<float, KER, PER, L, 1, X>), g, b, 0, c->stream, A, c->pos4f,
                              c->fvf, c->faf, c->sigf, c->tovf, c->sdot, O);
         else
-          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<double, KER, PER, L, X>), g, b, 0, c->stream, A, c->pos4,
+          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<double, KER, PER, L, M, X>), g, b, 0, c->stream, A, c->pos4,
                              c->fv, c->fa, c->sig, c->tovf, c->sdot, O);
       };
       if (xs == kXGP) launch(std::integral_constant<int, kXGP>{});
       else if (xs == kXDD) launch(std::integral_constant<int, kXDD>{});
       else if (c->stress_heavy && c->p.precision == SPH_FP32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<float, KER, PER, L, kXSL>), g, b, 0, c->stream, A, c->pos4f,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<float, KER, PER, L, 1, kXSL>), g, b, 0, c->stream, A, c->pos4f,
                            c->fvf, c->faf, c->sigf, c->tovf, c->sdot, O);
       else launch(std::integral_constant<int, 0>{});
     });
