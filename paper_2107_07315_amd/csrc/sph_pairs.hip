@@ -162,6 +162,30 @@ struct PassArgs {
 
 constexpr int kNone = 0x7fffffff;
 
+// Largest value of v over the wave, as a wave-uniform (scalar) value, by lane shifts within the vector
+// registers (through LDS each of the six steps is a round trip).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto step = [&](auto ctrl, auto rows) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+    v = o > v ? o : v;
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr 1, 2, 4, 8
+  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast 15, 31
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// the smallest and the largest slot list of the wave
+struct CountRange {
+  int lo, hi;
+};
+__device__ __forceinline__ CountRange count_range(int cnt) {
+  return CountRange{(int)(0x7fffffffu - wave_max_u32(0x7fffffffu - (uint32_t)cnt)), (int)wave_max_u32((uint32_t)cnt)};
+}
+
 // What a thread of a pair pass does: L M consecutive lanes serve a target, M of them to each of its L
 // slot lists (M > 1: each takes 8 / M consecutive entries of every group of 8).  A workgroup of 64 L
 // threads then serves 64 / M targets, so a tile is the work of M workgroups ("parts").
@@ -223,27 +247,6 @@ struct TileWalk {
   }
 };
 
-// Walk of a whole slot list when the tile's union fits one LDS chunk: f(local index) for every
-// entry, a 16-byte group (8 entries) per round with the entries taken at fixed positions (no
-// shifts or per-entry boundary tests), the next group in flight during the current one's 8 pairs.
-template <typename F>
-__device__ __forceinline__ void walk_groups(const uint4* base, int64_t gstride, int cnt, F&& f) {
-  uint4 g = make_uint4(0u, 0u, 0u, 0u);
-  if (cnt > 0) g = base[0];
-  const uint4* gp = base + gstride;
-  for (int k0 = 0; k0 < cnt; k0 += 8) {
-    uint4 nx = g;
-    if (k0 + 8 < cnt) nx = *gp;
-    gp += gstride;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t w = i < 2 ? g.x : (i < 4 ? g.y : (i < 6 ? g.z : g.w));
-      if (k0 + i < cnt) f((int)((i & 1) ? (w >> 16) : (w & 0xffffu)));
-    }
-    g = nx;
-  }
-}
-
 // The lane's part of a slot list's group where M lanes share a slot (8 / M consecutive entries each).
 template <int M> struct GroupPart;
 template <> struct GroupPart<1> { using T = uint4; };
@@ -257,15 +260,18 @@ __device__ __forceinline__ int part_entry(const typename GroupPart<M>::T& q, int
 }
 
 // Software-pipelined walk of a whole slot list when the tile's union sits in LDS as one chunk.
-// Every lane of the wave runs the wave's longest list (cmax, wave-uniform), so the body is
-// straight-line code with no per-entry branch: entries past the lane's own count read the records
-// of LDS slot `pad`, a sentinel particle far from every target (its pair terms are exactly zero,
-// with no overflow), and pass no list entry on.  The records of the next entry are read from LDS
+// Every lane of the wave runs the wave's longest list (w.hi), so the body is straight-line code with no
+// per-entry branch: entries past the lane's own count read the records of LDS slot `pad`, a sentinel
+// particle far from every target (its pair terms are exactly zero, with no overflow), and pass no list
+// entry on.  With FAST the groups that are whole in every list of the wave (w.lo) go
+// through a loop that does not test the entry: three vector instructions of a pair's 34 in the FP32
+// density pass (328 -> 323 us on the 2M star); the longer bodies of the other passes lose more by the
+// second copy (FP32 forces 538 -> 595, FP64 923 -> 1527).  The records of the next entry are read from LDS
 // (load(j)) before the current entry's arithmetic (f(loc, rec)); the next 16-byte group of 8
 // entries is read from memory one group ahead; group_end() runs after every group of 8.  With M > 1
 // the lane takes part `part` of every group.
-template <int M, typename Ld, typename F, typename G>
-__device__ __forceinline__ void walk_groups_pf(const uint4* base, int64_t gstride, int part, int cnt, int cmax, int pad,
+template <int M, bool FAST, typename Ld, typename F, typename G>
+__device__ __forceinline__ void walk_groups_pf(const uint4* base, int64_t gstride, int part, int cnt, CountRange w, int pad,
                                                Ld&& load, F&& f, G&& group_end) {
   using Q = typename GroupPart<M>::T;
   constexpr int E = 8 / M;
@@ -276,13 +282,28 @@ __device__ __forceinline__ void walk_groups_pf(const uint4* base, int64_t gstrid
   if (o < cnt) g = at(base);
   const uint4* gp = base + gstride;
   auto rec = load(o < cnt ? ent(g, 0) : pad);
-  for (int k0 = 0; k0 < cmax; k0 += 8) {
+  int k0 = 0;
+  if constexpr (FAST) {
+    for (; k0 + (M > 1 ? 15 : 8) < w.lo; k0 += 8) {
+      const Q nx = at(gp);
+      gp += gstride;
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const auto nrec = load(i < E - 1 ? ent(g, i + 1) : ent(nx, 0));
+        f(ent(g, i), rec);
+        rec = nrec;
+      }
+      group_end();
+      g = nx;
+    }
+  }
+  for (; k0 < w.hi; k0 += 8) {
     Q nx = g;
     if (k0 + 8 + o < cnt) nx = at(gp);
     gp += gstride;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      if (k0 + i >= cmax) break;   // wave-uniform
+      if (k0 + i >= w.hi) break;   // wave-uniform
       const int k1 = i < E - 1 ? k0 + o + i + 1 : k0 + 8 + o;
       const auto nrec = load(k1 < cnt ? (i < E - 1 ? ent(g, i + 1) : ent(nx, 0)) : pad);
       f(ent(g, i), rec);
@@ -293,21 +314,24 @@ __device__ __forceinline__ void walk_groups_pf(const uint4* base, int64_t gstrid
   }
 }
 
-// Largest value of v over the wave, as a wave-uniform (scalar) value.
-__device__ __forceinline__ int wave_max_i(int v) {
+// v of the lane at distance 1 or 2 by exclusive or (a permutation within four lanes, no LDS round trip)
+template <int X, typename T>
+__device__ __forceinline__ T quad_xor(T v) {
+  static_assert(X == 1 || X == 2, "within four lanes");
+  int w[sizeof(T) / 4];
+  __builtin_memcpy(w, &v, sizeof(T));
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const int o = __shfl_xor(v, off, 64);
-    v = o > v ? o : v;
-  }
-  return __builtin_amdgcn_readfirstlane(v);
+  for (int& k : w) k = __builtin_amdgcn_mov_dpp(k, X == 1 ? 0xb1 : 0x4e, 0xf, 0xf, true);
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
 }
-
 // Sum over the L adjacent lanes that share a target (every one of them receives the sum).
 template <int L, typename T>
 __device__ __forceinline__ T lane_group_sum(T v) {
+  if constexpr (L > 1) v += quad_xor<1>(v);
+  if constexpr (L > 2) v += quad_xor<2>(v);
 #pragma unroll
-  for (int off = 1; off < L; off <<= 1) v += __shfl_xor(v, off, 64);
+  for (int off = 4; off < L; off <<= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 
@@ -711,8 +735,8 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
     __syncthreads();
     stage(0);
     __syncthreads();
-    walk_groups_pf<M>(
-        lst, A.capw * L, me.part, cnt, wave_max_i(cnt), CHU, [&](int j) { return sp.get(j); },
+    walk_groups_pf<M, F32>(
+        lst, A.capw * L, me.part, cnt, count_range(cnt), CHU, [&](int j) { return sp.get(j); },
         [&](int loc, const SR& pb) {
           cand(loc, pb, [&](int l, bool h) {
             if constexpr (XL) wr.put_unchecked(l, h);
@@ -952,8 +976,8 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
     }
     __syncthreads();
     const int cnt = stressed ? pass_count<L>(A, tw.p, sub) : 0;
-    walk_groups_pf<M>(
-        pass_list<L>(A, slot), A.capw * L, me.part, cnt, wave_max_i(cnt), CH - 1,
+    walk_groups_pf<M, false>(
+        pass_list<L>(A, slot), A.capw * L, me.part, cnt, count_range(cnt), CH - 1,
         [&](int j) { return Recs{sp.get(j), sv.get(j)}; }, [&](int, const Recs& r) { pair(r); }, [] {});
   } else {
     tw.start(pass_list<L>(A, slot), A.capw * L, stressed ? pass_count<L>(A, tw.p, sub) : 0);
@@ -1217,10 +1241,10 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
     const bool any_st = stress_tile();
     auto ld = [&](int j) { return Recs{sp.get(j), sv.get(j), sa2[j]}; };
     if (any_st)
-      walk_groups_pf<M>(lst, A.capw * L, me.part, cnt, wave_max_i(cnt), CHU, ld, pair, [] {});
+      walk_groups_pf<M, false>(lst, A.capw * L, me.part, cnt, count_range(cnt), CHU, ld, pair, [] {});
     else
-      walk_groups_pf<M>(
-          lst, A.capw * L, me.part, cnt, wave_max_i(cnt), CHU, ld,
+      walk_groups_pf<M, false>(
+          lst, A.capw * L, me.part, cnt, count_range(cnt), CHU, ld,
           [&](int loc, const Recs& r) { pair_st(loc, r, std::false_type{}); }, [] {});
   } else {
     const bool any_st = sizeof(R) == 4 || XS != 0 || stress_tile();
