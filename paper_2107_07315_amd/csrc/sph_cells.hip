@@ -259,16 +259,23 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t& total)
   return before + inc - v;
 }
 
+// Tiles of small FP64 sets (with 4 list slots per particle) start at every 32nd particle: the pair passes
+// then give a target 8 lanes (4 slots of 2 lanes), so a workgroup is as full and its walk half as long, and
+// the build's waves have half the targets.  Ten steps, us, with tiles of 64 and 32: 8000-particle lattice
+// 701 and 638, 13.8k 733 and 676, 22k 879 and 865, 33k 847 and 915 (there 64 fills every CU twice, once);
+// 15k star with diagnostics 1135 and 993, 20k relaxation 604 and 570, 20k snapshot 380 and 368.
+constexpr int64_t kTiles32 = 24576;
+
 // Start flags of the first cut, and their count per block.
 __global__ __launch_bounds__(kB) void k_tile_flags(const uint32_t* __restrict__ gkeys, const double* __restrict__ h,
-                                                   int64_t n, const GridInfo* __restrict__ gp, double cut,
+                                                   int64_t n, const GridInfo* __restrict__ gp, double cut, int len,
                                                    uint32_t* __restrict__ flag, uint32_t* __restrict__ bsum) {
   const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
   uint32_t v = 0u;
   for (int k = 0; k < 4; ++k) {
     const int64_t p = p0 + k;
     if (p >= n) break;
-    const uint32_t f = ((p & 63) == 0 || morton_jump(*gp, gkeys, p) > cut * h[p]) ? 1u : 0u;
+    const uint32_t f = ((p & (len - 1)) == 0 || morton_jump(*gp, gkeys, p) > cut * h[p]) ? 1u : 0u;
     flag[p] = f;
     v += f;
   }
@@ -536,8 +543,8 @@ __global__ __launch_bounds__(64) void k_tile_cost(const GridInfo* __restrict__ g
 // and the dearest tests 107 batches of 64 candidates (2700 without the split; 36 on average);
 // cutting every tile above 8000 at 4 h costs 15% more tiles, which the pair passes pay for at
 // every evaluation.  Sets of at most kSplitSmall particles (1100 tiles, about one a SIMD) take half
-// the thresholds: there more tiles run side by side, and the dearest tile is the build's time.  Reads
-// the tile of p from the scan of the old flags.
+// the thresholds, sets of kTiles32 a third (their tiles are smaller): there more tiles run side by side, and
+// the dearest tile is the build's time.  Reads the tile of p from the scan of the old flags.
 constexpr int32_t kSplit4 = 12000, kSplit2 = 18000, kSplitSmall = 65536;
 __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
                                                    int64_t n, const int32_t* __restrict__ tile_start,
@@ -545,7 +552,7 @@ __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, 
                                                    const double4* __restrict__ pos4, const GridInfo* __restrict__ gp,
                                                    uint32_t* __restrict__ bsum) {
   const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
-  const int32_t half = n <= kSplitSmall ? 2 : 1;
+  const int32_t part = n <= kTiles32 ? 3 : (n <= kSplitSmall ? 2 : 1);
   uint32_t v = 0u, tot;
   for (int k = 0; k < 4; ++k) {
     const int64_t p = p0 + k;
@@ -554,8 +561,8 @@ __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, 
     if (!f) {   // p > 0: particle 0 starts a tile
       const int64_t t = (int64_t)idx[p] - 1;
       const int32_t c = cost[t];
-      if (c > kSplit4 / half) {
-        const bool dear = c > kSplit2 / half;
+      if (c > kSplit4 / part) {
+        const bool dear = c > kSplit2 / part;
         f = (dear && ((p - tile_start[t]) & 31) == 0) ||
             morton_jump(*gp, gkeys, p) > (dear ? 2.0 : 4.0) * fmin(pos4[p].w, pos4[p - 1].w);
         if (f) flag[p] = 1u;
@@ -1045,7 +1052,8 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   uint32_t* flag = reinterpret_cast<uint32_t*>(c->tmp);
   uint32_t* idx = flag + c->capw;
   uint32_t* bsum = c->sort.scan_bsum;
-  hipLaunchKernelGGL(k_tile_flags, dim3(nb4), dim3(kB), 0, s, c->keys, st->h, n, c->grid, tile_cut_of(c->p), flag, bsum);
+  c->tile_len = c->p.precision != SPH_FP32 && pass_lanes(c->p) == 4 && n <= kTiles32 ? 32 : 64;
+  hipLaunchKernelGGL(k_tile_flags, dim3(nb4), dim3(kB), 0, s, c->keys, st->h, n, c->grid, tile_cut_of(c->p), c->tile_len, flag, bsum);
   const bool per = c->p.periodic != 0;
   // FP32 pair sums keep the order of the cell grid's lists (see sph_cellgrid.hip)
   const bool cells = c->p.precision == SPH_FP32;

@@ -340,6 +340,7 @@ struct sph_ctx {
   int32_t* tile_u;
   int64_t upool;        // entries of tile_u
   int64_t cap_tiles;
+  int tile_len;         // targets of a full tile of the last build
   int32_t* tile_usize;
   int32_t* stress_tiles;  // tiles with a type-1 particle, in tile order (nstress of them)
   uint32_t* tile_st;      // per tile: 1 if a particle or a union member is of type 1

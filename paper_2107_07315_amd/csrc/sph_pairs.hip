@@ -158,6 +158,7 @@ struct PassArgs {
   // step number in [1, seq] (that step's drift broke the skin bound); stop == nullptr: never
   const uint32_t* stop;
   uint32_t seq;
+  int parts;   // workgroups to a tile (a tile of at most 64 targets: 64 / M each)
 };
 
 constexpr int kNone = 0x7fffffff;
@@ -188,7 +189,7 @@ __device__ __forceinline__ CountRange count_range(int cnt) {
 
 // What a thread of a pair pass does: L M consecutive lanes serve a target, M of them to each of its L
 // slot lists (M > 1: each takes 8 / M consecutive entries of every group of 8).  A workgroup of 64 L
-// threads then serves 64 / M targets, so a tile is the work of M workgroups ("parts").
+// threads then serves 64 / M targets: a tile of more is the work of several workgroups ("parts").
 template <int L, int M>
 struct TargetLane {
   int q, slot, part;   // target among the workgroup's, its slot list, and which of the slot's M lanes
@@ -663,13 +664,14 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
     if constexpr (F32) sp.put(CHU, make_float4(1e10f, 1e10f, 1e10f, 0.0f));
     else sp.put(CHU, make_double4(1e10, 1e10, 1e10, 0.0));
   }
-  const int64_t ntl = num_tiles(A) * M;
+  const int64_t ntl = num_tiles(A) * (M > 1 ? A.parts : 1);
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntl); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
     const int64_t item = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
     if (item >= ntl) break;
-    const int64_t tile = item / M;
-    const int tl = me.target((int)(item % M));
-    if (M > 1 && me.first((int)(item % M)) >= A.tile_cnt[tile]) continue;   // no target left for this part
+    const int64_t tile = M > 1 ? item / A.parts : item;
+    const int of = M > 1 ? (int)(item % A.parts) : 0;
+    const int tl = me.target(of);
+    if (M > 1 && me.first(of) >= A.tile_cnt[tile]) continue;   // no target left for this part
   TileWalk tw;
   tw.begin(A, tile, tl);
   const int total = tw.valid ? A.cnt_s[tw.p] : 0;
@@ -923,9 +925,9 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
   // only the tiles of the work list (tiles with a type-1 particle); every other particle's rates
   // are zero since the last build
   const int64_t nst = cancelled(A) ? 0 : (int64_t)A.grid->nstress;
-  for (int64_t w = blockIdx.x; w < nst * M; w += gridDim.x) {
-    const int64_t tile = A.stress_tiles[w / M];
-    const int tl = me.target((int)(w % M));
+  for (int64_t w = blockIdx.x; w < nst * A.parts; w += gridDim.x) {
+    const int64_t tile = A.stress_tiles[w / A.parts];
+    const int tl = me.target((int)(w % A.parts));
   TileWalk tw;
   tw.begin(A, tile, tl);
   const int64_t a = tw.a;
@@ -1118,13 +1120,14 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
     sv.put(CHU, V4{(R)0, (R)0, (R)0, (R)0});
     sa2[CHU] = A2{(R)0, (R)1};
   }
-  const int64_t ntl = num_tiles(A) * M;
+  const int64_t ntl = num_tiles(A) * (M > 1 ? A.parts : 1);
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntl); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
     const int64_t item = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
     if (item >= ntl) break;
-    const int64_t tile = item / M;
-    const int tl = me.target((int)(item % M));
-    if (M > 1 && me.first((int)(item % M)) >= A.tile_cnt[tile]) continue;   // no target left for this part
+    const int64_t tile = M > 1 ? item / A.parts : item;
+    const int of = M > 1 ? (int)(item % A.parts) : 0;
+    const int tl = me.target(of);
+    if (M > 1 && me.first(of) >= A.tile_cnt[tile]) continue;   // no target left for this part
   TileWalk tw;
   tw.begin(A, tile, tl);
   const int64_t a = tw.a;
@@ -1368,6 +1371,7 @@ PassArgs make_args(sph_ctx* c, sph_state* st) {
   A.has_mlp = mlp_view(c, &A.mlp) ? 1 : 0;
   A.stop = c->eval_seq ? c->drift_flag : nullptr;
   A.seq = c->eval_seq;
+  A.parts = 1;
   return A;
 }
 
@@ -1385,6 +1389,7 @@ static void dispatch_cfg(int kernel, int periodic, Fn&& f) {
   }
 }
 
+static int pass_parts(const sph_ctx* c, int split) { return split > 1 ? c->tile_len * split / 64 : 1; }
 // one workgroup per tile (up to 65536), or a persistent grid of pass_blocks (a multiple of the
 // XCD count) that loops over the tiles
 static dim3 pass_grid(const sph_ctx* c, int split) {
@@ -1392,19 +1397,19 @@ static dim3 pass_grid(const sph_ctx* c, int split) {
     const int64_t b = ((int64_t)c->p.pass_blocks + SPH_XCD - 1) / SPH_XCD * SPH_XCD;
     return dim3((unsigned)(b < 65536 ? b : 65536));
   }
-  return dim3(tile_launch(c) * (unsigned)split);
+  return dim3(tile_launch(c) * (unsigned)pass_parts(c, split));
 }
 
-// Lanes per slot list of the pair passes (FP64, 4 slots): with few tiles each tile is shared by 2 or 4
-// workgroups while that still gives about one workgroup per CU (256).  A pass over few tiles waits for one
-// workgroup's walk, which the lanes divide; beyond one workgroup per CU the unions staged M times cost
-// more than that.  Ten steps, us, at M = 1 / 2 / 4: lattice of 64 tiles 644 / 537 / 483, of 132
-// 732 / 710 / 765, of 240 743 / 749 / 885; relaxation of 65 tiles 501 / 460 / 461, of 156 479 / 483 / 500.
-// FP32 sums keep their order.
+// Lanes per slot list of the pair passes: 2 with the 32-target tiles of small FP64 sets, and 4, two
+// workgroups to a tile, while that still gives about one workgroup per CU (256).  A pass over few tiles
+// waits for one workgroup's walk, which the lanes divide; beyond one workgroup per CU the unions staged
+// twice cost more than that.  Ten steps, us, with 2 and 4: lattice of 128 tiles 519 and 475 (644 with one
+// lane and tiles of 64), of 256 638 and 654; star of 130 tiles 957 and 959, of 322 663 and 685.  FP32 sums
+// keep their order.
 static int pass_split(const sph_ctx* c) {
   constexpr unsigned kFill = 256 + 16;
-  if (c->p.precision == SPH_FP32 || pass_lanes(c->p) != 4) return 1;
-  return 4 * c->ntiles <= kFill ? 4 : (2 * c->ntiles <= kFill ? 2 : 1);
+  if (c->p.precision == SPH_FP32 || pass_lanes(c->p) != 4 || c->tile_len != 32) return 1;
+  return 2 * c->ntiles <= kFill ? 4 : 2;
 }
 
 // Calls f(L, M) with the pair passes' slots per target and the lanes per slot (pass_split) as
@@ -1440,6 +1445,7 @@ sph_status launch_density(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
   DensOut O = dens_out(c, st);
   const int split = pass_split(c);
+  A.parts = pass_parts(c, split);
   const dim3 g = pass_grid(c, split);
   const bool f32 = c->p.precision == SPH_FP32;
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
@@ -1529,7 +1535,8 @@ sph_status launch_stress(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
   // loops over the work list
   const int split = pass_split(c);
-  const unsigned most = (unsigned)(c->cap_tiles < 4096 ? c->cap_tiles : 4096), want = c->nstress * (unsigned)split;
+  A.parts = pass_parts(c, split);
+  const unsigned most = (unsigned)(c->cap_tiles < 4096 ? c->cap_tiles : 4096), want = c->nstress * (unsigned)pass_parts(c, split);
   const dim3 g(c->p.graph || want > most ? most : (want > 0 ? want : 1u));
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
     dispatch_lanes(pass_lanes(c->p), split, [&](auto LL, auto MM) {
@@ -1556,6 +1563,7 @@ sph_status launch_forces(sph_ctx* c, sph_state* st) {
                  : (c->p.density_mode == SPH_DENS_CONTINUITY || c->p.energy_mode == SPH_ENERGY_FIRST_LAW) ? kXDD
                                                                                                         : 0;
   const int split = pass_split(c);
+  A.parts = pass_parts(c, split);
   const dim3 g = pass_grid(c, split);
   dispatch_cfg(c->p.kernel, c->p.periodic, [&](auto K, auto P) {
     dispatch_lanes(pass_lanes(c->p), split, [&](auto LL, auto MM) {

@@ -1,6 +1,6 @@
-"""FP64 pair passes with several workgroups to a tile (few tiles): tile counts on both sides of the limits
-where a tile is the work of 4, 2 and 1 workgroups, and unions wider than one LDS chunk, against the same
-evaluation with 2 lanes per target (one workgroup to a tile)."""
+"""FP64 pair passes of small sets, with 2 and 4 lanes to a slot list and tiles of 32: particle and tile counts
+on both sides of the limits, and unions wider than one LDS chunk, against the same evaluation with 2 lanes
+per target (tiles of 64, one lane to a slot list)."""
 import numpy as np
 import pytest
 
@@ -16,7 +16,7 @@ TOL = 1000 * 2.0 ** -53 * 100
 
 
 @pytest.mark.parametrize("n_side,widen", [(3, 1.0), (12, 1.0), (12, 2.2), (16, 1.0), (17, 1.0), (20, 1.0), (20, 2.2),
-                                          (21, 1.0), (24, 1.0)])
+                                          (24, 1.0), (29, 1.0), (30, 1.0)])
 def test_split_tiles_give_the_same_sums(n_side, widen):
     w = W.lattice(n_side=n_side)
     rng = np.random.default_rng(n_side)
