@@ -1029,21 +1029,23 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
     } else {   // state that the next evaluation reads although it is an output
       if (c->p.density_mode == SPH_DENS_CONTINUITY) A[m++] = {st->D, 8, false, nullptr};
       if (c->p.dtP_mode == SPH_DTP_LAGGED) A[m++] = {st->P, 8, false, nullptr};
-      // the step's half-step copies, into their second buffer (outside a step nothing reads them)
+      // the step's half-step copies, into their second buffer (outside a step nothing reads them); in
+      // place where captured kicks hold the first one (a new capture costs more than the copy)
       for (int k = 0; k < SPH_HALF_FIELDS; ++k)
         if (k < 10 || c->p.density_mode == SPH_DENS_CONTINUITY)
-          A[m++] = {c->half + (int64_t)k * c->capacity, 8, k >= 4 && k < 10, c->half_alt + (int64_t)k * c->capacity};
+          A[m++] = {c->half + (int64_t)k * c->capacity, 8, k >= 4 && k < 10,
+                    c->p.graph ? nullptr : c->half_alt + (int64_t)k * c->capacity};
     }
     A[m++] = {st->id, 4, false, nullptr};
     if (st->star) A[m++] = {st->star, 4, false, nullptr};
     A[m++] = {st->broken, 1, false, nullptr};
     A[m++] = {st->type, 1, false, nullptr};
     if ((e = permute_arrays(c, A, m, st->type, n))) return e;
-    if (outputs_recomputed) {
+    if (outputs_recomputed && !c->p.graph) {
       double* t = c->half;
       c->half = c->half_alt;
       c->half_alt = t;
-      ++c->graph_epoch;   // captured kicks hold the old buffer
+      ++c->graph_epoch;   // a graph captured before would hold the old buffer
     }
     hipLaunchKernelGGL(k_pack_pos, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, st->h, st->star, c->stars, n, c->pos4,
                        c->p.precision == SPH_FP32 ? c->pos4f : nullptr, c->pos_build, st->type, st->dSdt, c->sdot);
