@@ -136,26 +136,15 @@ __device__ __forceinline__ double rcp_fast(double x) {
 }
 __device__ __forceinline__ float rcp_fast(float x) { return __builtin_amdgcn_rcpf(x); }
 // sqrt: the rsq estimate (relative error near 2^-23) after one Newton step has an error near
-// 1.5 e^2; the closing step on r = x y squares it again, to rounding level.
-__device__ __forceinline__ double sqrt_fast(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = y * fma(-0.5 * x * y, y, 1.5);
-  double r = x * y;
-  r = fma(0.5 * y, fma(-r, r, x), r);
-  return x > 0.0 ? r : 0.0;
-}
-// the same for the pair passes: 0 is raised to 1e-300 (one instruction instead of a compare and two
-// selects), where the estimate is finite; r = 1e-150 then stands for 0
+// 1.5 e^2; the closing step on r = x y squares it again, to rounding level.  0 is raised to 1e-300
+// (one instruction instead of a compare and two selects), where the estimate is finite; r = 1e-150
+// then stands for 0.
 __device__ __forceinline__ double sqrt_pos(double x) {
   x = fmax(x, 1e-300);
   double y = __builtin_amdgcn_rsq(x);
   y = y * fma(-0.5 * x * y, y, 1.5);
   const double r = x * y;
   return fma(0.5 * y, fma(-r, r, x), r);
-}
-__device__ __forceinline__ float sqrt_fast(float x) {
-  const float r = x * __builtin_amdgcn_rsqf(x);
-  return x > 0.0f ? r : 0.0f;
 }
 
 // ---- Wendland kernels with support 2 h_ab: W and F such that grad_a W = F (x_a - x_b) -------
