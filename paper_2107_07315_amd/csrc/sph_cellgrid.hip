@@ -426,9 +426,9 @@ __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, 
 // and the lists are deterministic and each list is ascending in local index.
 // Bound by instruction issue.  The FP64 test of every candidate by every lane (10 operations a pair, and
 // eight sub-box tests a candidate to keep the batches short) took 3.43 ms on the 2M star (skin 0.14),
-// 1.08 ms on a 300k snapshot and 0.50 ms on the 1M shell; this takes 2.15, 0.58 and
+// 1.08 ms on a 300k snapshot and 0.50 ms on the 1M shell; this takes 1.88, 0.51 and
 // 0.32.  (Sub-box or particle tests of the candidates on top of the box test cost more than the batches
-// they save: 2.27 ms, 0.73 in small tiles only.)
+// they save: 3.11 ms with the sub-boxes, 2.27 against 2.15 with the particles of small tiles.)
 constexpr float kBand = 0x1p-17f;
 template <bool PER, int NL>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_build_tiles(BuildArgs B) {
@@ -625,21 +625,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
         }
         const int Tc = __shfl(inc, 63, 64);
         __syncthreads();
-        c_s[lane] = s;
-        c_o[lane] = inc - cntc;
+        // the cells with particles, in order: the end of each in the block's candidates, and what leads from
+        // a candidate to its cell-sorted position
+        const unsigned long long filled = __ballot(cntc > 0);
+        if (cntc > 0) {
+          const int k = __popcll(filled & lt);
+          c_s[k] = s - (inc - cntc);
+          c_o[k] = inc;
+        }
         __syncthreads();
         // phase 2: gather candidates 64 at a time, the next 64 in flight, test against the tile's box
         // and append the survivors to the batch in slot order
+        // (a lane's candidates ascend, so it goes on from its last cell: a binary search of the block in
+        // every round is six dependent LDS reads, 2.15 instead of 1.88 ms on the 2M star)
+        int cell = -1, cend = 0, cbase = 0;
         auto fetch = [&](int slot, double4& pb) -> int32_t {
           pb = make_double4(0.0, 0.0, 0.0, 0.0);
           if (slot >= Tc) return -1;
-          int lo_i = 0, hi_i = 63;   // last cell with c_o <= slot
-          while (lo_i < hi_i) {
-            const int mid = (lo_i + hi_i + 1) >> 1;
-            if (c_o[mid] <= slot) lo_i = mid;
-            else hi_i = mid - 1;
+          while (slot >= cend) {   // ends: the last filled cell ends at Tc
+            ++cell;
+            cbase = c_s[cell];
+            cend = c_o[cell];
           }
-          const int32_t sp = c_s[lo_i] + (slot - c_o[lo_i]);
+          const int32_t sp = cbase + slot;
           pb = B.pos_sorted[sp];
           return (int32_t)B.perm[sp];
         };
