@@ -153,16 +153,15 @@ const char* sph_status_string(sph_status s) {
 void sph_destroy(sph_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
-  void* bufs[] = {c->grid, c->keys, c->vals, c->cell_se, c->pos_sorted, c->sub_box, c->tile_box, c->super_box, c->sort.keys_alt, c->sort.vals_alt,
+  void* bufs[] = {c->grid, c->keys, c->vals, c->cell_se, c->pos_sorted, c->sub_box, c->sort.keys_alt, c->sort.vals_alt,
                   c->sort.hist, c->sort.rowtot, c->sort.partial, c->sort.scan_bsum, c->tile_u, c->tile_start, c->tile_cnt, c->tile_uoff,
                   c->tile_usize, c->stress_tiles, c->tile_st, c->nbr16, c->nbr_count, c->nbr_count_sl, c->nbr16s, c->nbr_count_s, c->pos_build, c->drift_flag,
                   c->pos4, c->fv, c->fa, c->sig, c->pos4f, c->fvf,
-                  c->faf, c->sigf, c->mu, c->Y0, c->B, c->sdot, c->tovf, c->half, c->half_alt, c->tmp, c->stars, c->status,
+                  c->faf, c->sigf, c->mu, c->Y0, c->B, c->sdot, c->tovf, c->half_mem, c->tmp, c->stars, c->status,
                   c->dsum, c->dDdt, c->xcoef, c->dtw, c->dtpart, c->eos_list, c->eos_list_n};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (c->drift_host) (void)hipHostFree(c->drift_host);
-  if (c->step_host) (void)hipHostFree(c->step_host);
   if (c->tab_own) (void)hipFree(c->tab_own);
   if (c->diag_part) (void)hipFree(c->diag_part);
   mlp_free(c);
@@ -206,10 +205,10 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
   c->sort.scan_cap = (capw + 1023) / 1024;
   c->max_cells = kMaxCells;
   c->sort.max_blocks = (int)((cap + 4095) / 4096);
+  const int64_t nsub = capw / 8 + capw + 8;   // boxes of runs; the tiles' and the tile runs' follow them
   if ((e = dalloc(&c->grid, 1)) || (e = dalloc(&c->keys, cap)) || (e = dalloc(&c->vals, cap)) ||
       (e = dalloc(&c->cell_se, c->max_cells)) || (e = dalloc(&c->pos_sorted, cap)) ||
-      (e = dalloc(&c->sub_box, capw / 8 + capw + 8)) || (e = dalloc(&c->tile_box, capw)) ||
-      (e = dalloc(&c->super_box, capw / 64 + 1)) ||
+      (e = dalloc(&c->sub_box, nsub + capw + capw / 64 + 1)) ||
       (e = dalloc(&c->sort.keys_alt, cap)) || (e = dalloc(&c->sort.vals_alt, cap)) ||
       (e = dalloc(&c->sort.hist, (size_t)256 * (c->sort.max_blocks > 128 ? c->sort.max_blocks : 128))) || (e = dalloc(&c->sort.rowtot, 256)) ||
       (e = dalloc(&c->sort.partial, (size_t)8 * 1024)) ||
@@ -227,21 +226,23 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
       (e = dalloc(&c->faf, cap)) || (e = dalloc(&c->sigf, 6 * cap)) || (e = dalloc(&c->mu, cap)) ||
       (e = dalloc(&c->Y0, cap)) || (e = dalloc(&c->B, cap)) || (e = dalloc(&c->sdot, cap)) ||
       (e = dalloc(&c->tovf, cap)) ||
-      (e = dalloc(&c->half, SPH_HALF_FIELDS * cap)) ||
-      (e = dalloc(&c->half_alt, SPH_HALF_FIELDS * cap)) || (e = dalloc(&c->tmp, capw)) || (e = dalloc(&c->status, 1)) ||
+      (e = dalloc(&c->half_mem, 2 * SPH_HALF_FIELDS * cap)) || (e = dalloc(&c->tmp, capw)) || (e = dalloc(&c->status, 1)) ||
       (e = dalloc(&c->dsum, cap)) || (e = dalloc(&c->dDdt, cap)) || (e = dalloc(&c->xcoef, 5 * cap)) ||
       (e = dalloc(&c->dtw, 8)) || (e = dalloc(&c->dtpart, 65536 + 4096)) || (e = dalloc(&c->eos_list, cap)) ||
       (e = dalloc(&c->eos_list_n, 1))) {
     sph_destroy(c);
     return note(nullptr, e, "device scratch for capacity %lld does not fit", (long long)capacity);
   }
-  if (hipHostMalloc((void**)&c->drift_host, 4 * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess)
+  c->tile_box = c->sub_box + nsub;
+  c->super_box = c->tile_box + capw;
+  c->half = c->half_mem;
+  c->half_alt = c->half_mem + SPH_HALF_FIELDS * cap;
+  if (hipHostMalloc((void**)&c->drift_host, 5 * sizeof(uint32_t), hipHostMallocCoherent) != hipSuccess) {
     c->drift_host = nullptr;
-  if (hipHostMalloc((void**)&c->step_host, sizeof(uint32_t), hipHostMallocCoherent) != hipSuccess) c->step_host = nullptr;
-  if (!c->drift_host || !c->step_host) {
     sph_destroy(c);
     return note(nullptr, SPH_E_OOM, "pinned host word");
   }
+  c->step_host = c->drift_host + 4;
   if ((e = stats_scratch_init(c))) {
     sph_destroy(c);
     return note(nullptr, e, "address of the statistics scratch array on device %d", c->device);

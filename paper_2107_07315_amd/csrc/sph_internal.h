@@ -356,6 +356,7 @@ struct sph_ctx {
   double4* tovf;        // per particle: fixed-background force coefficients (k_P, B_x, B_y, B_z)
   // half-step copies for kick-drift-kick
   double* half;         // SPH_HALF_FIELDS * cap: vx, vy, vz, u, S[6], D
+  double* half_mem;     // both buffers of the half-step copies
   double* half_alt;     // where a list build inside a step gathers them (the two change places)
   double* tmp;          // permutation staging, 8 bytes * cap
   // ensemble
