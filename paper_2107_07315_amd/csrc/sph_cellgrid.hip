@@ -1,4 +1,4 @@
-// Candidate-list build on a multi-level cell grid, for the FP32 pair sums.
+// Candidate-list build on a multi-level cell grid, for FP32 pair sums and for shells in both precisions.
 //
 // Particles are binned into up to four levels by h (factor 2 per level), each with its own uniform
 // grid (cell size 2 hmax_l / cell_div) addressed by Morton codes.  A tile searches every level l
@@ -10,6 +10,13 @@
 // that follow: taken from the other build's order, ten steps of the 2M-particle star differ by
 // 2.5e-5 in the accelerations (both orders are equally far from the FP64 values), a perfect lattice
 // by 2e-3.  With this build FP32 runs reproduce earlier results bit for bit.
+// A shell between an inner and an outer wall keeps it in FP64 too, with tiles of 64 particles and one
+// lane to a slot list at every size, so that its sums keep their order: where all particles lie in one
+// layer, the radii in a slab differ by 4e-5 of themselves, and the linear fit of sph_diagnostics solves
+// normal equations of a condition up to 1e11.  Sums in the other build's order change the state after
+// ten steps by 1e-12 at most, and the fit with it by 4e-10 to 1.5e-7 (20k to 290k particles).  Ten steps
+// with the record, us, with the other build and with this one: 21k particles 1240 and 1510, 81k 2185 and
+// 2580, 290k 4340 and 4790.
 #include "sph_build.h"
 #include "sph_internal.h"
 

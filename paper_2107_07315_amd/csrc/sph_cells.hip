@@ -8,7 +8,7 @@
 // 8 consecutive particles of a tile, one per tile, one per 64 tiles, each with its largest h, so a
 // search adapts to the tenfold range of smoothing lengths by itself (no grid, no second sort).
 // k_build_tiles descends the boxes for every tile and tests what is left on the matrix cores.  FP32
-// runs take the lists of a cell grid instead (sph_cellgrid.hip, which says why).
+// runs and shells take the lists of a cell grid instead (sph_cellgrid.hip, which says why).
 #include <stddef.h>
 #include <string.h>
 
@@ -1054,11 +1054,10 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   uint32_t* flag = reinterpret_cast<uint32_t*>(c->tmp);
   uint32_t* idx = flag + c->capw;
   uint32_t* bsum = c->sort.scan_bsum;
-  c->tile_len = c->p.precision != SPH_FP32 && pass_lanes(c->p) == 4 && n <= kTiles32 ? 32 : 64;
+  const bool cells = keeps_sum_order(c->p);
+  c->tile_len = !cells && pass_lanes(c->p) == 4 && n <= kTiles32 ? 32 : 64;
   hipLaunchKernelGGL(k_tile_flags, dim3(nb4), dim3(kB), 0, s, c->keys, st->h, n, c->grid, tile_cut_of(c->p), c->tile_len, flag, bsum);
   const bool per = c->p.periodic != 0;
-  // FP32 pair sums keep the order of the cell grid's lists (see sph_cellgrid.hip)
-  const bool cells = c->p.precision == SPH_FP32;
   const dim3 tgrid(tile_grid(c->cap_tiles));
   auto starts = [&] {
     sph_scan_rows(c, bsum, (int)nb4, &c->grid->ntiles);

@@ -11,7 +11,8 @@
 #define SPH_PI 3.14159265358979323846
 
 // Global state of a list build: bounding box and h range of the particles, the skin in force, the
-// sizes of the tile table, and the multi-level cell grid of the FP32 runs: particles are binned into levels by smoothing length
+// sizes of the tile table, and the multi-level cell grid of the runs that keep the sums' order
+// (keeps_sum_order): particles are binned into levels by smoothing length
 // (level l holds h in [hmin 2^l, hmin 2^(l+1)), the top level takes the rest); each level has
 // its own uniform grid whose cells are addressed by a Morton code inside a per-level block of
 // 2^(3 bits) entries starting at base[l].  All fields are computed on the device.
@@ -307,11 +308,11 @@ struct sph_ctx {
   // grid and sort
   GridInfo* grid;       // device
   uint32_t *keys, *vals;  // Morton keys and the permutation that sorts them
-  // cell grid (FP32 runs)
+  // cell grid (keeps_sum_order)
   int2* cell_se;        // per cell [start, end) in the cell-sorted order; cleared at every build
   int64_t max_cells;
   double4* pos_sorted;  // x, y, z, h in the cell-sorted order
-  // boxes (FP64 runs)
+  // boxes (the other runs)
   Box* sub_box;         // per 8 consecutive particles of a tile, at (tile_start >> 3) + tile + k
   Box* tile_box;
   Box* super_box;       // per 64 consecutive tiles
@@ -407,7 +408,7 @@ sph_status sph_sort_pairs(sph_ctx* c, uint32_t* keys, uint32_t* vals, int64_t n)
 // outputs_recomputed: the outputs (D, rho, P, c_s, accelerations, du/dt, dS/dt) are recomputed
 // before they are next read, so they are not reordered
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed);
-// the cell grid of the FP32 runs: its tables, the tiles it splits, and the lists
+// the cell grid (keeps_sum_order): its tables, the tiles it splits, and the lists
 sph_status grid_prepare(sph_ctx* c, int64_t n);
 sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles,
                             uint32_t* bsum);
@@ -466,6 +467,11 @@ __host__ __device__ __forceinline__ int64_t nbr_index(int64_t k, int64_t p, int6
 // hits (and the particle's list at most cap).  Slot s of the exact lists is entry k at
 // nbr_index(k, s, capw * L).
 __host__ __device__ __forceinline__ int pass_lanes(const sph_params& p) { return p.lanes > 0 ? p.lanes : 4; }
+// Runs whose pair sums keep the order that the cell grid's lists, tiles of 64 and one lane to a slot list
+// give them (sph_cellgrid.hip says why): all FP32 runs, and shells, which an inner wall holds open.
+__host__ __device__ __forceinline__ bool keeps_sum_order(const sph_params& p) {
+  return p.precision == SPH_FP32 || p.wall_in > 0.0;
+}
 // Tile cut in smoothing lengths (the measured best with 4 lanes per target on the 2M star)
 __host__ __device__ __forceinline__ double tile_cut_of(const sph_params& p) { return p.tile_cut > 0.0 ? p.tile_cut : 10.0; }
 __host__ __device__ __forceinline__ int slot_capacity(int cap, int L) {

@@ -1400,11 +1400,10 @@ static dim3 pass_grid(const sph_ctx* c, int split) {
 // workgroups to a tile, while that still gives about one workgroup per CU (256).  A pass over few tiles
 // waits for one workgroup's walk, which the lanes divide; beyond one workgroup per CU the unions staged
 // twice cost more than that.  Ten steps, us, with 2 and 4: lattice of 128 tiles 519 and 475 (644 with one
-// lane and tiles of 64), of 256 638 and 654; star of 130 tiles 957 and 959, of 322 663 and 685.  FP32 sums
-// keep their order.
+// lane and tiles of 64), of 256 638 and 654; star of 130 tiles 957 and 959, of 322 663 and 685.
 static int pass_split(const sph_ctx* c) {
   constexpr unsigned kFill = 256 + 16;
-  if (c->p.precision == SPH_FP32 || pass_lanes(c->p) != 4 || c->tile_len != 32) return 1;
+  if (c->tile_len != 32) return 1;   // (never in the runs that keep the sums' order)
   return 2 * c->ntiles <= kFill ? 4 : 2;
 }
 
