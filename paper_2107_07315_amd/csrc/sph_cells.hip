@@ -877,13 +877,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       }
       sm = __ballot(near);
     }
-    // what is left in the rings: whole groups, then a partly filled last one (slots s < r of it
-    // hold entries; a slot's count is at most that of slot 0, whose capacity covers them all)
-    if (valid && out.cnt <= B.cap) {
-      while (out.cnt - 8 * NL * out.stored >= 8 * NL) out.store_group(NL);
-      const int r = out.cnt - 8 * NL * out.stored;
-      if (r > 0) out.store_group(r < NL ? r : NL);
-    }
+    if (valid) out.finish();
     if (valid) B.count[a] = out.cnt < B.cap ? out.cnt : B.cap;
     if (lane == 0) B.tile_usize[t] = usize < ucap ? usize : ucap;
     if (usize > ucap || out.cnt > B.cap) latch_error(B.status, SPH_E_NGB_CAPACITY, valid ? a : -1);
