@@ -591,10 +591,13 @@ __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, 
 // |x_b|^2 + h_a'^2 + h_b'^2 the parts leave out at most 2^-22 of a value, the product lo.lo 2^-22 of
 // hi.hi, and the FP32 inputs and the accumulation 40 2^-24 M, in all below 16 2^-22 M against the
 // band's 32 2^-22 M (a widening of H by 3e-5).  Lengths are scaled so that the tile's reach is 100.
+// A low part below 2^-14 is subnormal in FP16 and may be off by 2^-25 instead: in the ten products and
+// w of a pair that adds at most 2^-22 + 2^-25 M, which the other half of the band covers where M >= 1/4.
+// A tile with a target of h' < 1/2 (its reach 200 times h' or more) is tested pair by pair.
 // In a tile so wide that the band would lengthen its lists (centre-to-corner above 8 of its smallest
-// h) every hit is tested again from the FP32 coordinates' differences; a batch with a candidate
-// beyond FP16's range, and a periodic box less than twice the tile's reach across, take the test
-// pair by pair in FP64.
+// h) every hit is tested again from the FP32 coordinates' differences.  Pair by pair, in FP64, are tested
+// a batch with a candidate beyond FP16's range, such tiles, and those of a periodic box less than twice
+// their reach across.
 // A candidate hit by any target joins the union, as its next member, and each target appends the
 // local indices of its hits to its list, ascending.
 // Bound by instruction issue (about 490 vector instructions a batch, half of them the appends, and
@@ -695,7 +698,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       float w;
       const float m = lift(pa, valid, tx, ty, tz, th, w);
       lift_operands<true>(tx, ty, tz, th, w, T);
-      by_pair = __ballot(m > kListMax) != 0ull;
+      by_pair = __ballot(m > kListMax || (valid && !(th >= 0.5f))) != 0ull;
     }
     if (PER) by_pair = by_pair || fmaxf(own.w.x, fmaxf(own.w.y, own.w.z)) + (own.c.w + (float)g.hmax) * s1f > 0.499f * boxf;
     ListOut<NL> out;
@@ -748,7 +751,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
           cand[32 * cword + cbit] = make_float4(x, y, z, h);
           __syncthreads();
           // coordinates rounded to FP32 (their differences to 2^-22 |x|, |x| < 2 sqrt(kListMax)): the
-          // support widened by 1e-5 and 1e-4 of the scaled unit holds every pair of the exact test
+          // support widened by 1e-5 and 2e-4 of the scaled unit holds every pair of the exact test
           auto again = [&](uint32_t m, int word) -> uint32_t {
             uint32_t keep = 0u;
             while (m) {
