@@ -88,6 +88,7 @@ template <typename R> struct Rec;
 // HS times the sum of the two record values.
 template <> struct Rec<double> {
   static constexpr double HS = 0.5;   // (positions: pos4 holds h itself)
+  static constexpr double FAR = 1e100;   // sentinel coordinate: beyond any particle, its square still finite
   using P4 = double4;
   using V4 = double4;
   using A2 = double2;
@@ -102,6 +103,7 @@ template <> struct Rec<double> {
 };
 template <> struct Rec<float> {
   static constexpr float HS = 1.0f;
+  static constexpr float FAR = 1e10f;
   using P4 = float4;
   using V4 = float4;
   using A2 = float2;
@@ -661,8 +663,7 @@ void k_density(PassArgs A, const double4* __restrict__ pos64, DensOut O,
   const TargetLane<L, M> me(threadIdx.x);
   const int sub = me.slot;
   if (threadIdx.x == 0) {   // the sentinel: far from every target, h = 0 (no neighbour, W = 0)
-    if constexpr (F32) sp.put(CHU, make_float4(1e10f, 1e10f, 1e10f, 0.0f));
-    else sp.put(CHU, make_double4(1e10, 1e10, 1e10, 0.0));
+    sp.put(CHU, SR{Rec<R>::FAR, Rec<R>::FAR, Rec<R>::FAR, 0});
   }
   const int64_t ntl = num_tiles(A) * (M > 1 ? A.parts : 1);
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntl); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
@@ -973,7 +974,7 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
     __syncthreads();
     stage(0, CH - 1);
     if (threadIdx.x == 0) {
-      sp.put(CH - 1, P4{(R)1e10, (R)1e10, (R)1e10, (R)0});
+      sp.put(CH - 1, P4{Rec<R>::FAR, Rec<R>::FAR, Rec<R>::FAR, (R)0});
       sv.put(CH - 1, V4{(R)0, (R)0, (R)0, (R)0});
     }
     __syncthreads();
@@ -1116,7 +1117,7 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   __shared__ R ssg[SL ? 6 : 1][SL ? CH : 1];   // kXSL: S/D^2 of the staged members (0 if unstressed)
   const R box = (R)A.p.box, half = (R)0.5 * box;
   if (threadIdx.x == 0) {   // the sentinel: far from every target, at rest, h = 0, unstressed (F = 0)
-    sp.put(CHU, P4{(R)1e10, (R)1e10, (R)1e10, (R)0});
+    sp.put(CHU, P4{Rec<R>::FAR, Rec<R>::FAR, Rec<R>::FAR, (R)0});
     sv.put(CHU, V4{(R)0, (R)0, (R)0, (R)0});
     sa2[CHU] = A2{(R)0, (R)1};
   }
