@@ -452,7 +452,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   const double box = g.box;
   const double s1 = 1.0 + g.skin;
   const double s1w = s1 * (1.0 + 0x1p-40);   // the batch test's widened factor
-  const float s1f = (float)s1 * (1.0f + 1e-5f);
   // the candidate of a batch that this lane lifts: the products' rows come out in an order in which
   // lane l holds bit l' of the masks, so it takes candidate l' and the bits are in batch order
   const int lj = 32 * ((lane >> 2) & 1) + 16 * (lane >> 5) + 4 * ((lane >> 3) & 3) + (lane & 3);
@@ -480,13 +479,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
       if (lane == 0) latch_error(B.status, SPH_E_NGB_CAPACITY, -1);
     }
     int32_t* U = B.tile_u + uoff;
-    // lengths are scaled so that the tile's reach is 100
-    const float wr = sqrtf((float)(wx * wx + wy * wy + wz * wz)) * (1.f + 1e-6f), hmx = (float)G.hmx * (1.f + 1e-6f);
-    const float sc = 100.f / (wr + 2.f * hmx * s1f + 1e-30f);
-    const float reach = (wr + hmx * s1f) * sc * (1.f + 1e-5f);
+    // lengths are scaled so that the tile's reach is 100 (in FP64, whatever the caller's unit of length)
+    const double wr = uniform_d(sqrt(wx * wx + wy * wy + wz * wz)), hr = uniform_d(G.hmx * s1);
+    const double sc = uniform_d(100.0 / (wr + 2.0 * hr + 1e-290));
+    const float reach = (float)((wr + hr) * sc) * (1.f + 1e-4f);
     // scaled components of a particle at d from the tile's centre
     auto scaled = [&](double dx, double dy, double dz, double hp) {
-      return make_float4((float)dx * sc, (float)dy * sc, (float)dz * sc, (float)hp * sc);
+      return make_float4((float)(dx * sc), (float)(dy * sc), (float)(dz * sc), (float)(hp * sc));
     };
     // the lane's particle of a product; one that is not there or out of every target's reach never hits.
     // Returns |x|^2 + h'^2

@@ -115,6 +115,8 @@ __global__ __launch_bounds__(64) void k_grid_setup1(GridInfo* g, const unsigned 
   g->nlev = L;
   // origin of the FP32 bounding boxes; a set wider than 2^32 smallest smoothing lengths is refused
   for (int d = 0; d < 3; ++d) g->org[d] = isfinite(g->lo[d]) ? g->lo[d] : 0.0;
+  const bool usual = g->hmin > 1e-290 && g->hmin < 1e290;
+  g->bunit = usual ? ldexp(1.0, -31 - ilogb(g->hmin)) : 1.0;
   if (!periodic)
     for (int d = 0; d < 3; ++d) {
       const double ext = dec_double(g->enc_hi[d]) - g->lo[d];
@@ -411,8 +413,8 @@ __device__ __forceinline__ double grp_max(double v) {
 }
 __device__ __forceinline__ float round_up(double v) { return (float)v * (1.0f + 0x1p-21f) + 1e-37f; }
 
-// Box of the NL lanes of a group: q = position relative to the origin, h, in = the lane holds a
-// particle with finite values.  The half-width is taken about the FP32-rounded centre and rounded
+// Box of the NL lanes of a group: q = position relative to the origin, h (both in the boxes' unit), in = the
+// lane holds a particle with finite values.  The half-width is taken about the FP32-rounded centre and rounded
 // up, so the box holds every particle exactly.
 template <int NL>
 __device__ __forceinline__ Box group_box(const double q[3], double h, bool in) {
@@ -466,9 +468,10 @@ __global__ __launch_bounds__(64) void k_tile_boxes(const GridInfo* __restrict__ 
       crust[t] = cm ? 1u : 0u;
     }
     const double4 p = lane < tc ? pos4[ts + lane] : make_double4(0.0, 0.0, 0.0, 0.0);
-    const double q[3] = {p.x - g.org[0], p.y - g.org[1], p.z - g.org[2]};
-    const bool in = lane < tc && isfinite(q[0]) && isfinite(q[1]) && isfinite(q[2]) && isfinite(p.w);
-    const Box sb = group_box<8>(q, p.w, in), tb = group_box<64>(q, p.w, in);
+    const double q[3] = {(p.x - g.org[0]) * g.bunit, (p.y - g.org[1]) * g.bunit, (p.z - g.org[2]) * g.bunit};
+    const double h = p.w * g.bunit;
+    const bool in = lane < tc && isfinite(q[0]) && isfinite(q[1]) && isfinite(q[2]) && isfinite(h);
+    const Box sb = group_box<8>(q, h, in), tb = group_box<64>(q, h, in);
     if ((lane & 7) == 0 && lane < tc) sub_box[(ts >> 3) + t + (lane >> 3)] = sb;
     if (lane == 0) tile_box[t] = tb;
   }
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(64) void k_tile_cost(const GridInfo* __restrict__ g
                                                   int32_t* __restrict__ cost) {
   const int lane = threadIdx.x;
   const GridInfo& g = *gp;
-  const float s1 = (float)(1.0 + g.skin) * (1.0f + 1e-5f), box = (float)g.box;
+  const float s1 = (float)(1.0 + g.skin) * (1.0f + 1e-5f), box = (float)(g.box * g.bunit);
   const int64_t ntiles = g.ntiles, ns = (ntiles + 63) / 64;
   for (int64_t k_ = blockIdx.x / SPH_XCD, chunk_ = xcd_chunk(ntiles); k_ < chunk_; k_ += gridDim.x / SPH_XCD) {
     const int64_t t = (int64_t)(blockIdx.x % SPH_XCD) * chunk_ + k_;
@@ -639,7 +642,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const int lane = threadIdx.x;
   const GridInfo& g = *B.grid;
   const double box = g.box, s1 = 1.0 + g.skin;
-  const float s1f = (float)s1 * (1.0f + 1e-5f), boxf = (float)box;
+  const float s1f = (float)s1 * (1.0f + 1e-5f), boxf = (float)(box * g.bunit);
+  const double ibu = 1.0 / g.bunit;
   const int64_t ntiles = g.ntiles, ns = (ntiles + 63) / 64;
   const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   // candidate lane c of a batch is bit cbit of word cword of the masks (the order in which the
@@ -668,17 +672,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       if (lane == 0) latch_error(B.status, SPH_E_NGB_CAPACITY, -1);
     }
     int32_t* U = B.tile_u + uoff;
-    const double c0 = g.org[0] + own.c.x, c1 = g.org[1] + own.c.y, c2 = g.org[2] + own.c.z;
+    const double c0 = g.org[0] + own.c.x * ibu, c1 = g.org[1] + own.c.y * ibu, c2 = g.org[2] + own.c.z * ibu;
     const float rt2 = own.w.x * own.w.x + own.w.y * own.w.y + own.w.z * own.w.z;
     const float sc = 100.f / (sqrtf(rt2) + 2.f * own.c.w * s1f + 1e-30f);
     const float reach = (sqrtf(rt2) + own.c.w * s1f) * sc * (1.f + 1e-5f);
+    const double scd = sc * g.bunit;   // from the caller's lengths
     // scaled components; a lane without a (finite) particle, or with one out of every target's reach,
     // never hits (w beyond any -h'^2); returns |x|^2 + h'^2, which must stay below kListMax in FP16
     auto lift = [&](const double4& p, bool in, float& x, float& y, float& z, float& h, float& w) -> float {
-      x = (float)min_image(p.x - c0, (int)PER, box) * sc;
-      y = (float)min_image(p.y - c1, (int)PER, box) * sc;
-      z = (float)min_image(p.z - c2, (int)PER, box) * sc;
-      h = (float)(p.w * s1) * sc;
+      x = (float)(min_image(p.x - c0, (int)PER, box) * scd);
+      y = (float)(min_image(p.y - c1, (int)PER, box) * scd);
+      z = (float)(min_image(p.z - c2, (int)PER, box) * scd);
+      h = (float)(p.w * (s1 * scd));
       const float r2 = x * x + y * y + z * z, h2 = h * h, far = reach + h;
       w = (r2 - h2) - kListBand * (r2 + h2);
       if (!(in && r2 < far * far && h2 < 1e30f)) {   // (NaN fails too)
@@ -690,7 +695,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     };
     constexpr float kListMax = 3e4f;
     f16x8 T[2];
-    const float hmn = (float)wave_min_d(valid ? pa.w : 1e300);
+    const float hmn = (float)(wave_min_d(valid ? pa.w : 1e300) * g.bunit);
     const bool wide = rt2 > 64.f * hmn * hmn;
     bool by_pair = false;
     float tx, ty, tz, th;
@@ -700,7 +705,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       lift_operands<true>(tx, ty, tz, th, w, T);
       by_pair = __ballot(m > kListMax || (valid && !(th >= 0.5f))) != 0ull;
     }
-    if (PER) by_pair = by_pair || fmaxf(own.w.x, fmaxf(own.w.y, own.w.z)) + (own.c.w + (float)g.hmax) * s1f > 0.499f * boxf;
+    if (PER) by_pair = by_pair || fmaxf(own.w.x, fmaxf(own.w.y, own.w.z)) + (own.c.w + (float)(g.hmax * g.bunit)) * s1f > 0.499f * boxf;
     ListOut<NL> out;
     out.ring = ring + kRingRow * lane;
     out.slot0 = reinterpret_cast<uint4*>(B.nbr16) + (valid ? (int64_t)a : 0) * NL;

@@ -24,6 +24,7 @@ struct GridInfo {
   unsigned long long lev_lo[SPH_MAX_LEV][3], lev_hi[SPH_MAX_LEV][3];  // per-level bounding boxes (encoded)
   double lo[3];
   double org[3];        // origin of the FP32 bounding boxes (lo where finite)
+  double bunit;         // lengths in the boxes: this times a length, a power of two that brings hmin near 2^-31
   double hmin, hmax;
   double hlev[SPH_MAX_LEV];
   double cell[SPH_MAX_LEV];
@@ -39,7 +40,8 @@ struct GridInfo {
   uint32_t nstress;     // tiles holding a particle of type 1 (the stress pass's work list)
 };
 
-// Bounding box of a run of particles, relative to GridInfo::org, in FP32 rounded outward:
+// Bounding box of a run of particles, relative to GridInfo::org and in units of 1 / GridInfo::bunit (so that
+// squares stay within FP32's range whatever the caller's unit of length), in FP32 rounded outward:
 // c = centre and largest h (negative: no particle), w = half-widths.
 struct Box {
   float4 c, w;
