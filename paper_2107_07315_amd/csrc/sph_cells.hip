@@ -228,15 +228,18 @@ __global__ __launch_bounds__(kB) void k_gkeys(const double* __restrict__ x, cons
 // that spans the boundary could be that large.  Cutting where 2^(k+1) fine cells exceed 4 h keeps
 // every tile inside a region about 4 smoothing lengths across, in dense and sparse parts alike
 // (the factor is the tile_cut parameter).
-__device__ __forceinline__ double morton_jump(const GridInfo& g, const uint32_t* __restrict__ gkeys, int64_t p) {
+__device__ __forceinline__ double curve_cell(const GridInfo& g) {   // the width of the curve's finest cells
   double ext = 0.0;
   for (int d = 0; d < 3; ++d) {
     const double e = g.periodic ? g.box : dec_double(g.enc_hi[d]) - g.lo[d];
     ext = e > ext ? e : ext;
   }
+  return ext / 1024.0;
+}
+__device__ __forceinline__ double morton_jump(const GridInfo& g, const uint32_t* __restrict__ gkeys, int64_t p) {
   const uint32_t x = gkeys[p] ^ gkeys[p - 1];
   const int lvl = x ? (31 - __clz(x)) / 3 : -1;
-  return lvl >= 0 ? (double)(2 << lvl) * (ext / 1024.0) : 0.0;
+  return lvl >= 0 ? (double)(2 << lvl) * curve_cell(g) : 0.0;
 }
 // Block-wide sums and exclusive scans over 1024 elements a block, 4 consecutive ones a thread
 // (256 threads): a count per block, scanned by k_scan_rows, then each element's index.
@@ -547,13 +550,19 @@ __global__ __launch_bounds__(64) void k_tile_cost(const GridInfo* __restrict__ g
 // cutting every tile above 8000 at 4 h costs 15% more tiles, which the pair passes pay for at
 // every evaluation.  Sets of at most kSplitSmall particles (1100 tiles, about one a SIMD) take half
 // the thresholds, sets of kTiles32 a third (their tiles are smaller): there more tiles run side by side, and
-// the dearest tile is the build's time.  Reads the tile of p from the scan of the old flags.
+// the dearest tile is the build's time.  Where the curve is blind (a cell of it wider than 2 smoothing
+// lengths, in a set with particles far outside) the particles of a cell lie in no order, and 32 of them can
+// have more candidates between them than a union takes: a tile of such particles is cut so that 1.5 times
+// the candidates it can expect (its cost, spread evenly over its box) fit.  100k particles in a cube in no
+// order, one more at 1e5 of its sizes, ms an evaluation: cut at every 32nd position 6.0, at every 8th 15.7
+// (9.3 with the cell grid's lists, always cut at every 8th; 0.6 without the far particle).
+// Reads the tile of p from the scan of the old flags.
 constexpr int32_t kSplit4 = 12000, kSplit2 = 18000, kSplitSmall = 65536;
 __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, const uint32_t* __restrict__ idx,
                                                    int64_t n, const int32_t* __restrict__ tile_start,
                                                    const int32_t* __restrict__ cost, const uint32_t* __restrict__ gkeys,
-                                                   const double4* __restrict__ pos4, const GridInfo* __restrict__ gp,
-                                                   uint32_t* __restrict__ bsum) {
+                                                   const double4* __restrict__ pos4, const Box* __restrict__ tile_box,
+                                                   int ucap, const GridInfo* __restrict__ gp, uint32_t* __restrict__ bsum) {
   const int64_t p0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
   const int32_t part = n <= kTiles32 ? 3 : (n <= kSplitSmall ? 2 : 1);
   uint32_t v = 0u, tot;
@@ -566,8 +575,15 @@ __global__ __launch_bounds__(kB) void k_tile_split(uint32_t* __restrict__ flag, 
       const int32_t c = cost[t];
       if (c > kSplit4 / part) {
         const bool dear = c > kSplit2 / part;
-        f = (dear && ((p - tile_start[t]) & 31) == 0) ||
-            morton_jump(*gp, gkeys, p) > (dear ? 2.0 : 4.0) * fmin(pos4[p].w, pos4[p - 1].w);
+        const double h = fmin(pos4[p].w, pos4[p - 1].w);
+        int len = dear ? 32 : 64;
+        if (gkeys[p] == gkeys[p - 1] && curve_cell(*gp) > 2.0 * h) {
+          const float4 w = tile_box[t].w;
+          const float R = (float)(2.0 * pos4[p].w * (1.0 + gp->skin) * gp->bunit), e = 0.25f * R;
+          const float most = 1.5f * (float)c * (4.18879f * R * R * R) / (8.f * (w.x + e) * (w.y + e) * (w.z + e));
+          len = most * 16.f > (float)ucap ? 8 : (most * 32.f > (float)ucap ? 16 : 32);
+        }
+        f = ((p - tile_start[t]) & (len - 1)) == 0 || morton_jump(*gp, gkeys, p) > (dear ? 2.0 : 4.0) * h;
         if (f) flag[p] = 1u;
       }
     }
@@ -1089,7 +1105,7 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tile_cost<false>), tgrid, dim3(64), 0, s, c->grid, c->tile_cnt, c->tile_box,
                          c->super_box, c->tile_usize);
     hipLaunchKernelGGL(k_tile_split, dim3(nb4), dim3(kB), 0, s, flag, idx, n, c->tile_start, c->tile_usize,
-                       c->keys, c->pos4, c->grid, bsum);
+                       c->keys, c->pos4, c->tile_box, c->ucap, c->grid, bsum);
     starts();
     boxes();
   }
