@@ -99,7 +99,7 @@ __global__ void k_grid_setup2(GridInfo* g, int cell_div, int64_t max_cells, DevS
   double hi[3];
   for (int d = 0; d < 3; ++d) hi[d] = g->periodic ? g->box : dec_double(g->enc_hi[d]);
   double grow = 1.0;
-  for (int attempt = 0; attempt < 64; ++attempt) {
+  for (int attempt = 0; attempt < 64 && g->hmin > 0.0; ++attempt) {
     uint64_t total = 0;
     bool ok = true;
     for (int l = 0; l < g->nlev; ++l) {
@@ -109,15 +109,10 @@ __global__ void k_grid_setup2(GridInfo* g, int cell_div, int64_t max_cells, DevS
       double c = 2.0 * hl / (double)cell_div * grow;
       int bmax = 0;
       for (int d = 0; d < 3; ++d) {
-        int dim;
-        if (g->periodic) {
-          dim = (int)floor(g->box / c);
-          if (dim < 1) dim = 1;
-        } else {
-          double ext = hi[d] - g->lo[d];
-          dim = (int)floor(ext / c) + 1;
-        }
-        if (dim > 1024) ok = false;
+        // counted in FP64: a wide set has more cells than an int counts
+        const double cells = g->periodic ? floor(g->box / c) : floor((hi[d] - g->lo[d]) / c) + 1.0;
+        if (cells > 1024.0) ok = false;
+        const int dim = ok && cells > 1.0 ? (int)cells : 1;
         g->dims[l][d] = dim;
         int b = 0;
         while ((1 << b) < dim) ++b;
