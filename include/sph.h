@@ -192,15 +192,18 @@ sph_status sph_set_params(sph_ctx* ctx, const sph_params* params);
  * permute all state arrays along a global Morton curve and build candidate lists, which contain
  * { b != a : |x_a - x_b| < (1 + skin)(h_a + h_b) }, per tile of at most 64 consecutive particles.  The exact sets
  * N(a) = { b != a : |x_a - x_b|^2 < (h_a + h_b)^2 }, evaluated in FP64 without contraction,
- * are extracted from the candidates by sph_density.  With skin > 0 this call waits for the
- * one-word drift test on the device before deciding. */
+ * are decided on the candidates by sph_density.  With skin > 0 this call waits for the
+ * one-word drift test on the device before deciding.  Latches SPH_E_ARG (sph_sync) for a
+ * smoothing length that is not positive, a periodic box with 2h >= box/2, and a set that is not
+ * periodic and more than 2^32 of its smallest smoothing lengths across (with the cell grid, i.e.
+ * in FP32 and for shells: a set that no grid of 256 cells a side fits, from about 6e8 on). */
 sph_status sph_build_cells(sph_ctx* ctx, sph_state* st);
 
 /* Density summation D_a = sum_b m W(r_ab, h_ab) including b = a (section "Fixed metric
  * background": the computational density D = rho sqrt(gamma) W_L recovered by the standard
  * SPH sum), then rho = D / (psi^6 W_L), P and c_s from the EoS (eq. poly_eos family; the
  * relativistic sound speed of the setup section), the crust shear modulus and yield stress.
- * Also extracts the exact neighbour lists the later stages use.  Writes D, rho, P, cs. */
+ * Also counts the exact neighbours (sph_export_neighbours extracts them).  Writes D, rho, P, cs. */
 sph_status sph_density(sph_ctx* ctx, sph_state* st);
 
 /* Velocity gradient and stress rate (eqs. solid4-solid6): strain and rotation rates from

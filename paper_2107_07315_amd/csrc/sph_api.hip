@@ -765,7 +765,8 @@ sph_status sph_sync(sph_ctx* c) {
     DevStatus z = {0, 0};
     if ((he = hipMemcpy(c->status, &z, sizeof(z), hipMemcpyHostToDevice)) != hipSuccess)
       return note(c, SPH_E_HIP, "clearing the status word: %s", hipGetErrorString(he));
-    static const char* why[8] = {"", "a periodic box too small for one image per pair (2h >= box/2)", "",
+    static const char* why[8] = {"", "a periodic box too small for one image per pair (2h >= box/2), a smoothing length that is not "
+                                 "positive, or a set too wide for its smallest smoothing length (2^32 of it)", "",
                                  "", "", "a neighbour list exceeded its capacity (exact: max_neighbours, candidate: twice that)",
                                  "a field became NaN or Inf", "(rho, u) outside the tabulated equation of state"};
     const char* w = (s.code > 0 && s.code < 8) ? why[s.code] : "";

@@ -1,5 +1,6 @@
-"""What a list build refuses: smoothing lengths that are not positive, a box too small for them, a set too
-wide for them (beyond what an int counts in cells, and infinite).  A set within the limit is taken."""
+"""What a list build refuses, with a reason that names it: smoothing lengths that are not positive, a box too
+small for them, a set too wide for them (beyond what an int counts in cells, and infinite).  A set within
+the limit is taken."""
 import numpy as np
 import pytest
 
@@ -32,6 +33,7 @@ def test_refused(box, h, far, precision):
     with pytest.raises(sph.SphError) as e:
         _sync(box, h, far, precision)
     assert e.value.code == 1
+    assert all(w in e.value.detail for w in ("box too small", "not positive", "too wide")), e.value.detail
 
 
 @pytest.mark.parametrize("precision", ["FP64", "FP32"])
