@@ -153,7 +153,7 @@ const char* sph_status_string(sph_status s) {
 void sph_destroy(sph_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
-  void* bufs[] = {c->grid, c->keys, c->vals, c->cell_se, c->pos_sorted, c->sub_box, c->sort.keys_alt, c->sort.vals_alt,
+  void* bufs[] = {c->grid, c->keys, c->vals, c->cell_se, c->pos_sorted, c->sort.keys_alt, c->sort.vals_alt,
                   c->sort.hist, c->sort.rowtot, c->sort.partial, c->sort.scan_bsum, c->tile_u, c->tile_start, c->tile_cnt, c->tile_uoff,
                   c->tile_usize, c->stress_tiles, c->tile_st, c->nbr16, c->nbr_count, c->nbr_count_sl, c->nbr16s, c->nbr_count_s, c->pos_build, c->drift_flag,
                   c->pos4, c->fv, c->fa, c->sig, c->pos4f, c->fvf,
@@ -205,10 +205,14 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
   c->sort.scan_cap = (capw + 1023) / 1024;
   c->max_cells = kMaxCells;
   c->sort.max_blocks = (int)((cap + 4095) / 4096);
-  const int64_t nsub = capw / 8 + capw + 8;   // boxes of runs; the tiles' and the tile runs' follow them
+  // The exact lists' buffer (2 KB a particle by default) is written by sph_export_neighbours alone, which
+  // reads it before it returns.  In between it holds what a list build and a step need for themselves: the
+  // boxes, of runs, tiles and tile runs, and the second buffer of the half-step copies.
+  const int64_t nsub = capw / 8 + capw + 8, nbox = nsub + capw + capw / 64 + 1;
+  const size_t lists = sizeof(uint16_t) * (size_t)capw * slot_entries_max(c->cap);
+  const size_t between = sizeof(Box) * nbox + sizeof(double) * SPH_HALF_FIELDS * cap;
   if ((e = dalloc(&c->grid, 1)) || (e = dalloc(&c->keys, cap)) || (e = dalloc(&c->vals, cap)) ||
       (e = dalloc(&c->cell_se, c->max_cells)) || (e = dalloc(&c->pos_sorted, cap)) ||
-      (e = dalloc(&c->sub_box, nsub + capw + capw / 64 + 1)) ||
       (e = dalloc(&c->sort.keys_alt, cap)) || (e = dalloc(&c->sort.vals_alt, cap)) ||
       (e = dalloc(&c->sort.hist, (size_t)256 * (c->sort.max_blocks > 128 ? c->sort.max_blocks : 128))) || (e = dalloc(&c->sort.rowtot, 256)) ||
       (e = dalloc(&c->sort.partial, (size_t)8 * 1024)) ||
@@ -217,7 +221,7 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
       (e = dalloc(&c->stress_tiles, c->cap_tiles)) || (e = dalloc(&c->tile_st, c->cap_tiles)) ||
       (e = dalloc(&c->tile_uoff, c->cap_tiles)) ||
       (e = dalloc(&c->sort.scan_bsum, 2 * c->sort.scan_cap)) ||
-      (e = dalloc(&c->nbr16, (size_t)capw * slot_entries_max(c->cap))) || (e = dalloc(&c->nbr_count, capw)) ||
+      (e = dalloc(&c->nbr16, (lists > between ? lists : between) / sizeof(uint16_t))) || (e = dalloc(&c->nbr_count, capw)) ||
       (e = dalloc(&c->nbr_count_sl, (size_t)capw * 4)) ||
       (e = dalloc(&c->nbr16s, (size_t)capw * (c->cap_s + 32))) || (e = dalloc(&c->nbr_count_s, capw)) ||
       (e = dalloc(&c->pos_build, cap)) || (e = dalloc(&c->drift_flag, 1)) ||
@@ -226,17 +230,18 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
       (e = dalloc(&c->faf, cap)) || (e = dalloc(&c->sigf, 6 * cap)) || (e = dalloc(&c->mu, cap)) ||
       (e = dalloc(&c->Y0, cap)) || (e = dalloc(&c->B, cap)) || (e = dalloc(&c->sdot, cap)) ||
       (e = dalloc(&c->tovf, cap)) ||
-      (e = dalloc(&c->half_mem, 2 * SPH_HALF_FIELDS * cap)) || (e = dalloc(&c->tmp, capw)) || (e = dalloc(&c->status, 1)) ||
+      (e = dalloc(&c->half_mem, SPH_HALF_FIELDS * cap)) || (e = dalloc(&c->tmp, capw)) || (e = dalloc(&c->status, 1)) ||
       (e = dalloc(&c->dsum, cap)) || (e = dalloc(&c->dDdt, cap)) || (e = dalloc(&c->xcoef, 5 * cap)) ||
       (e = dalloc(&c->dtw, 8)) || (e = dalloc(&c->dtpart, 65536 + 4096)) || (e = dalloc(&c->eos_list, cap)) ||
       (e = dalloc(&c->eos_list_n, 1))) {
     sph_destroy(c);
     return note(nullptr, e, "device scratch for capacity %lld does not fit", (long long)capacity);
   }
+  c->sub_box = reinterpret_cast<Box*>(c->nbr16);
   c->tile_box = c->sub_box + nsub;
   c->super_box = c->tile_box + capw;
   c->half = c->half_mem;
-  c->half_alt = c->half_mem + SPH_HALF_FIELDS * cap;
+  c->half_alt = reinterpret_cast<double*>(c->sub_box + nbox);
   if (hipHostMalloc((void**)&c->drift_host, 5 * sizeof(uint32_t), hipHostMallocCoherent) != hipSuccess) {
     c->drift_host = nullptr;
     sph_destroy(c);

@@ -314,7 +314,7 @@ struct sph_ctx {
   int2* cell_se;        // per cell [start, end) in the cell-sorted order; cleared at every build
   int64_t max_cells;
   double4* pos_sorted;  // x, y, z, h in the cell-sorted order
-  // boxes (the other runs)
+  // boxes (the other runs; in nbr16)
   Box* sub_box;         // per 8 consecutive particles of a tile, at (tile_start >> 3) + tile + k
   Box* tile_box;
   Box* super_box;       // per 64 consecutive tiles
@@ -336,7 +336,8 @@ struct sph_ctx {
   int32_t* tile_usize;
   int32_t* stress_tiles;  // tiles with a type-1 particle, in tile order (nstress of them)
   uint32_t* tile_st;      // per tile: 1 if a particle or a union member is of type 1
-  uint16_t* nbr16;      // exact lists, one per slot (particle * lanes + sub-index)
+  uint16_t* nbr16;      // exact lists, one per slot (particle * lanes + sub-index), during sph_export_neighbours;
+                        // otherwise the boxes and half_alt
   int32_t* nbr_count;   // exact neighbours per particle
   int32_t* nbr_count_sl;  // entries per slot list
   uint16_t* nbr16s;
@@ -359,8 +360,8 @@ struct sph_ctx {
   double4* tovf;        // per particle: fixed-background force coefficients (k_P, B_x, B_y, B_z)
   // half-step copies for kick-drift-kick
   double* half;         // SPH_HALF_FIELDS * cap: vx, vy, vz, u, S[6], D
-  double* half_mem;     // both buffers of the half-step copies
-  double* half_alt;     // where a list build inside a step gathers them (the two change places)
+  double* half_mem;     // the buffer that the context allocates for them
+  double* half_alt;     // where a list build inside a step gathers them (in nbr16; the two change places)
   double* tmp;          // permutation staging, 8 bytes * cap
   // ensemble
   StarInfo* stars;      // device, may be null
