@@ -928,8 +928,8 @@ __global__ __launch_bounds__(kB) void k_count_stats(const int32_t* __restrict__ 
 }
 
 // Permutes the state arrays in place along c->vals, as many at a time as the staging area holds: the
-// candidate-list buffer, whose lists the build that follows rewrites (c->tmp, one array, where that
-// is smaller).  type comes last: the crust arrays are gathered with its old order.
+// candidate-list buffer (at least 80 bytes a particle), whose lists the build that follows rewrites.  type
+// comes last: the crust arrays are gathered with its old order.
 struct PermArray {
   void* p;
   int elem;
@@ -937,10 +937,8 @@ struct PermArray {
   void* to;   // gathered there for good (a second buffer), or nullptr: back into p
 };
 static sph_status permute_arrays(sph_ctx* c, const PermArray* A, int m, const int8_t* type, int64_t n) {
-  const size_t big = (size_t)c->capw * (size_t)(c->cap_s + 32) * sizeof(uint16_t), one = ((size_t)n * 8 + 255) & ~(size_t)255;
-  const bool fits = big >= one;
-  char* stage = fits ? reinterpret_cast<char*>(c->nbr16s) : reinterpret_cast<char*>(c->tmp);
-  const size_t room = fits ? big : (size_t)c->capw * 8;
+  char* stage = reinterpret_cast<char*>(c->nbr16s);
+  const size_t room = (size_t)c->capw * (size_t)(c->cap_s + 32) * sizeof(uint16_t);
   const unsigned nb = grid_for(n, kB);
   for (int k = 0; k < m;) {
     PermBatch B{};
@@ -1021,10 +1019,11 @@ static void launch_build(const BuildArgs& B, bool per, dim3 grid, hipStream_t s)
   else launch_build_per<false>(B, grid, s);
 }
 
-// Candidate-list build: every particle array of the state (and the half-step copies) is reordered
-// along the global Morton curve (the outputs only when outputs_recomputed is false), tiles are cut
-// from that order, particles are binned into the multi-level grid and each tile's candidates are
-// collected; the positions and h at the list build are kept for the drift test.
+// Candidate-list build: every particle array of the state is reordered along the global Morton curve (the
+// outputs only when outputs_recomputed is false, the half-step copies only when it is true), tiles are cut
+// from that order and each tile's candidates are collected, through the boxes of runs of particles or, where
+// the sums keep their order, through the multi-level grid; the positions and h at the list build are kept
+// for the drift test.
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   const int64_t n = st->n;
   hipStream_t s = c->stream;

@@ -362,7 +362,7 @@ struct sph_ctx {
   double* half;         // SPH_HALF_FIELDS * cap: vx, vy, vz, u, S[6], D
   double* half_mem;     // the buffer that the context allocates for them
   double* half_alt;     // where a list build inside a step gathers them (in nbr16; the two change places)
-  double* tmp;          // permutation staging, 8 bytes * cap
+  double* tmp;          // 8 bytes * capacity: tile start flags and their scan (list build), sums not kept (export)
   // ensemble
   StarInfo* stars;      // device, may be null
   int32_t nstars;

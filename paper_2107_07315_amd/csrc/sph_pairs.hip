@@ -633,13 +633,13 @@ __device__ __forceinline__ void density_epilogue(const PassArgs& A, int64_t a, b
 constexpr float kBand = 3.814697265625e-06f;   // 2^-18
 
 // Density pass.  In FP64 it is bound by instruction issue and LDS reads: 459 us on the 2M star
-// (245M candidate pairs), 565 when it also wrote exact lists and read 32-byte records whole.  Walks the candidate lists, takes the exact neighbour decision r^2 < (h_a + h_b)^2
-// of the FP64 positions on every candidate, sums the kernel over the neighbours in R and counts
-// them; with XL it also writes the exact lists (for the neighbour export).  A workgroup of L waves
-// takes one tile: lane g serves target g / L as sub-lane g % L, walks the candidate slot list
-// (particle * L + sub-lane) and with XL writes the exact hits to the exact slot list of the same
-// index; the L partial sums are added across the lanes.  The per-particle epilogue runs in k_density_epilogue, one lane per
-// particle.
+// (245M candidate pairs), 565 when it also wrote exact lists and read 32-byte records whole.  Walks the
+// candidate lists, takes the exact neighbour decision r^2 < (h_a + h_b)^2 of the FP64 positions on every
+// candidate, sums the kernel over the neighbours in R and counts them; with XL it also writes the exact
+// lists (for the neighbour export).  A workgroup of L waves takes one tile (or, with M > 1, a part of it):
+// lane g serves target g / L as sub-lane g % L, walks the candidate slot list (particle * L + sub-lane) and
+// with XL writes the exact hits to the exact slot list of the same index; the L partial sums are added
+// across the lanes.  The per-particle epilogue runs in k_density_epilogue, one lane per particle.
 //   FP64 (R = double): union records staged in LDS as FP64 (x, y, z, h), FP64 test.
 //   FP32 (R = float): union records staged as FP32 coordinates relative to the tile's first
 //   particle (16 bytes), the decision taken in FP32 and, inside the guard band kBand, again
@@ -908,8 +908,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 __global__ void k_word_clear(int32_t* w) { *w = 0; }   // a kernel, not a memset: graph-safe
 
 // ---- velocity gradient and stress rate ---------------------------------------------------------
-// Lane g of the L-wave workgroup walks the exact slot list (g / L, g % L) written by the density
-// pass; the partial velocity gradients of a target's L lanes are added before the epilogue.
+// Lane g of the L-wave workgroup walks the candidate slot list (g / L, g % L), or with M > 1 its part of
+// one (TargetLane); the partial velocity gradients of a target's lanes are added before the epilogue.
 template <typename R, int KER, bool PER, int L, int M>
 __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Rec<R>::P4* __restrict__ pos,
                                                    const typename Rec<R>::V4* __restrict__ fv,

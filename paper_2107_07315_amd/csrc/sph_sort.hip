@@ -1,6 +1,6 @@
-// Stable LSD radix sort of (32-bit key, 32-bit value) pairs, 8-bit digits, for the cell build.
-// Per pass: block histograms -> exclusive scan over (digit, block) in two small kernels ->
-// stable scatter.  The
+// Stable LSD radix sort of (32-bit key, 32-bit value) pairs, 8-bit digits, for the list builds.
+// Per pass: block histograms -> exclusive scan over (digit, block) in two small kernels (for small sets
+// within the scatter) -> stable scatter.  The
 // scatter ranks keys inside a 64-lane wave with ballot-based digit matching and orders waves and
 // rounds through LDS counters, so equal keys keep their input order.
 #include "sph_internal.h"
@@ -184,12 +184,12 @@ sph_status sph_sort_pairs(sph_ctx* c, uint32_t* keys, uint32_t* vals, int64_t n)
       hipLaunchKernelGGL(k_scatter_small, dim3(nsmall), dim3(kBlock), 0, c->stream, ka, va, n, shift, c->sort.hist, nsmall,
                          kb, vb);
     } else {
-    hipLaunchKernelGGL(k_hist, dim3(nblocks), dim3(kBlock), 0, c->stream, ka, n, shift, c->sort.hist,
-                       nblocks);
-    hipLaunchKernelGGL(k_scan_rows, dim3(256), dim3(256), 0, c->stream, c->sort.hist, nblocks, c->sort.rowtot);
-    hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(256), 0, c->stream, c->sort.rowtot);
-    hipLaunchKernelGGL(k_scatter, dim3(nblocks), dim3(kBlock), 0, c->stream, ka, va, n, shift,
-                       c->sort.hist, c->sort.rowtot, nblocks, kb, vb);
+      hipLaunchKernelGGL(k_hist, dim3(nblocks), dim3(kBlock), 0, c->stream, ka, n, shift, c->sort.hist,
+                         nblocks);
+      hipLaunchKernelGGL(k_scan_rows, dim3(256), dim3(256), 0, c->stream, c->sort.hist, nblocks, c->sort.rowtot);
+      hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(256), 0, c->stream, c->sort.rowtot);
+      hipLaunchKernelGGL(k_scatter, dim3(nblocks), dim3(kBlock), 0, c->stream, ka, va, n, shift,
+                         c->sort.hist, c->sort.rowtot, nblocks, kb, vb);
     }
     uint32_t* t = ka; ka = kb; kb = t;
     t = va; va = vb; vb = t;
