@@ -119,9 +119,9 @@ typedef struct {
   int32_t precision;       /* FP64, or FP32 pair sums with FP64 positions/integration/metric  */
   int32_t max_neighbours;  /* exact-list capacity per particle (0: 512); candidate lists hold  */
                            /*   twice as many                                                  */
-  int32_t cell_div;        /* FP32, and FP64 shells (wall_in > 0): cells per smoothing diameter */
-                           /*   of the finest level (0: 1); without effect in other FP64 runs,  */
-                           /*   whose list build has no cells                                   */
+  int32_t cell_div;        /* cells per smoothing diameter of the finest level (0: 1), where the */
+                           /*   list build has cells: in FP32, and in FP64 for shells (wall_in  */
+                           /*   > 0) and above 2^23 particles; without effect in other runs     */
   double tile_cut;         /* a 64-particle tile is cut where the Morton curve jumps farther  */
                            /*   than tile_cut smoothing lengths (0: 10)                        */
   double skin;             /* relative Verlet skin s: candidate lists hold every b with       */
@@ -195,8 +195,8 @@ sph_status sph_set_params(sph_ctx* ctx, const sph_params* params);
  * are decided on the candidates by sph_density.  With skin > 0 this call waits for the
  * one-word drift test on the device before deciding.  Latches SPH_E_ARG (sph_sync) for a
  * smoothing length that is not positive, a periodic box with 2h >= box/2, and a set that is not
- * periodic and more than 2^32 of its smallest smoothing lengths across (with the cell grid, i.e.
- * in FP32 and for shells: a set that no grid of 256 cells a side fits, from about 6e8 on). */
+ * periodic and more than 2^32 of its smallest smoothing lengths across (where the build has
+ * cells, see cell_div: a set that no grid of 256 cells a side fits, from about 6e8 on). */
 sph_status sph_build_cells(sph_ctx* ctx, sph_state* st);
 
 /* Density summation D_a = sum_b m W(r_ab, h_ab) including b = a (section "Fixed metric

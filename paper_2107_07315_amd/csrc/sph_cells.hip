@@ -8,7 +8,8 @@
 // 8 consecutive particles of a tile, one per tile, one per 64 tiles, each with its largest h, so a
 // search adapts to the tenfold range of smoothing lengths by itself (no grid, no second sort).
 // k_build_tiles descends the boxes for every tile and tests what is left on the matrix cores.  FP32
-// runs and shells take the lists of a cell grid instead (sph_cellgrid.hip, which says why).
+// runs and shells take the lists of a cell grid instead (sph_cellgrid.hip, which says why), and so do very
+// large sets (kBoxesMost).
 #include <stddef.h>
 #include <string.h>
 
@@ -270,6 +271,12 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t& total)
 // 701 and 638, 13.8k 733 and 676, 22k 879 and 865, 33k 847 and 915 (there 64 fills every CU twice, once);
 // 15k star with diagnostics 1135 and 993, 20k relaxation 604 and 570, 20k snapshot 380 and 368.
 constexpr int64_t kTiles32 = 24576;
+
+// The box search of a tile looks at every run of 64 tiles, so its time grows with the square of the set;
+// larger FP64 sets take the cell grid's lists.  List build with boxes and with the grid, ms: particles
+// spread evenly, 4M 4.0 and 4.0, 8M 8.3 and 8.1, 12M 14.2 and 11.8, 16M 20.4 and 15.4; star of 4M 4.7 and
+// 5.2, of 8M 9.5 and 10.4.
+constexpr int64_t kBoxesMost = int64_t(1) << 23;
 
 // Start flags of the first cut, and their count per block.
 __global__ __launch_bounds__(kB) void k_tile_flags(const uint32_t* __restrict__ gkeys, const double* __restrict__ h,
@@ -1022,7 +1029,7 @@ static void launch_build(const BuildArgs& B, bool per, dim3 grid, hipStream_t s)
 // Candidate-list build: every particle array of the state is reordered along the global Morton curve (the
 // outputs only when outputs_recomputed is false, the half-step copies only when it is true), tiles are cut
 // from that order and each tile's candidates are collected, through the boxes of runs of particles or, where
-// the sums keep their order, through the multi-level grid; the positions and h at the list build are kept
+// the sums keep their order and in very large sets, through the multi-level grid; the positions and h at the list build are kept
 // for the drift test.
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   const int64_t n = st->n;
@@ -1071,7 +1078,7 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   uint32_t* flag = reinterpret_cast<uint32_t*>(c->tmp);
   uint32_t* idx = flag + c->capw;
   uint32_t* bsum = c->sort.scan_bsum;
-  const bool cells = keeps_sum_order(c->p);
+  const bool cells = keeps_sum_order(c->p) || n > kBoxesMost;
   c->tile_len = !cells && pass_lanes(c->p) == 4 && n <= kTiles32 ? 32 : 64;
   hipLaunchKernelGGL(k_tile_flags, dim3(nb4), dim3(kB), 0, s, c->keys, st->h, n, c->grid, tile_cut_of(c->p), c->tile_len, flag, bsum);
   const bool per = c->p.periodic != 0;

@@ -310,7 +310,7 @@ struct sph_ctx {
   // grid and sort
   GridInfo* grid;       // device
   uint32_t *keys, *vals;  // Morton keys and the permutation that sorts them
-  // cell grid (keeps_sum_order)
+  // cell grid (keeps_sum_order, and very large sets)
   int2* cell_se;        // per cell [start, end) in the cell-sorted order; cleared at every build
   int64_t max_cells;
   double4* pos_sorted;  // x, y, z, h in the cell-sorted order
@@ -411,7 +411,7 @@ sph_status sph_sort_pairs(sph_ctx* c, uint32_t* keys, uint32_t* vals, int64_t n)
 // outputs_recomputed: the outputs (D, rho, P, c_s, accelerations, du/dt, dS/dt) are recomputed
 // before they are next read, so they are not reordered
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed);
-// the cell grid (keeps_sum_order): its tables, the tiles it splits, and the lists
+// the cell grid: its tables, the tiles it splits, and the lists
 sph_status grid_prepare(sph_ctx* c, int64_t n);
 sph_status grid_split_tiles(sph_ctx* c, int64_t n, uint32_t* flag, const uint32_t* idx, unsigned tiles,
                             uint32_t* bsum);
