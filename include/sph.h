@@ -121,7 +121,8 @@ typedef struct {
                            /*   twice as many                                                  */
   int32_t cell_div;        /* cells per smoothing diameter of the finest level (0: 1), where the */
                            /*   list build has cells: in FP32, and in FP64 for shells (wall_in  */
-                           /*   > 0) and above 2^23 particles; without effect in other runs     */
+                           /*   > 0), skins above 0.2 (0.5 up to 24576 particles) and above     */
+                           /*   2^23 particles; without effect in other runs                    */
   double tile_cut;         /* a 64-particle tile is cut where the Morton curve jumps farther  */
                            /*   than tile_cut smoothing lengths (0: 10)                        */
   double skin;             /* relative Verlet skin s: candidate lists hold every b with       */

@@ -205,9 +205,10 @@ sph_status sph_create(const sph_params* params, void* stream, int64_t capacity, 
   c->sort.scan_cap = (capw + 1023) / 1024;
   c->max_cells = kMaxCells;
   c->sort.max_blocks = (int)((cap + 4095) / 4096);
-  // The exact lists' buffer (2 KB a particle by default) is written by sph_export_neighbours alone, which
-  // reads it before it returns.  In between it holds what a list build and a step need for themselves: the
-  // boxes, of runs, tiles and tile runs, and the second buffer of the half-step copies.
+  // The exact lists' buffer (2 KB a particle by default) is written by sph_export_neighbours, which reads it
+  // before it returns, and by evaluations with a wide skin (exact_lists_written), whose forces read it.  In
+  // between it holds what a list build and, without such lists, a step need for themselves: the boxes, of
+  // runs, tiles and tile runs, and the second buffer of the half-step copies.
   const int64_t nsub = capw / 8 + capw + 8, nbox = nsub + capw + capw / 64 + 1;
   const size_t lists = sizeof(uint16_t) * (size_t)capw * slot_entries_max(c->cap);
   const size_t between = sizeof(Box) * nbox + sizeof(double) * SPH_HALF_FIELDS * cap;
@@ -564,6 +565,10 @@ sph_status sph_step(sph_ctx* c, sph_state* st, double dt, int32_t nsteps) {
   if (c->gen < 4 || st->n != c->n) return note(c, SPH_E_ORDER, "sph_step needs a full evaluation (build, density, stress rate, forces) of this state first");
   if (st->n == 0) return SPH_OK;
   if (c->p.graph && !c->stream) return note(c, SPH_E_ARG, "graph replay needs a non-default stream");
+  if (c->half != c->half_mem && exact_lists_written(c)) {   // out of the way of the lists (nothing is in it between calls)
+    std::swap(c->half, c->half_alt);
+    ++c->graph_epoch;
+  }
   if (c->p.graph && c->p.skin > 0.0 && c->lists_valid) {
     e = step_graphs(c, st, dt, nsteps);
     if (!e) {

@@ -1,5 +1,5 @@
-// Candidate-list build on a multi-level cell grid, for FP32 pair sums, for shells in both precisions and for
-// very large FP64 sets (kBoxesMost in sph_cells.hip).
+// Candidate-list build on a multi-level cell grid, for FP32 pair sums, for shells in both precisions, for
+// FP64 runs with a wide skin (wide_skin) and for very large FP64 sets (kBoxesMost in sph_cells.hip).
 //
 // Particles are binned into up to four levels by h (factor 2 per level), each with its own uniform
 // grid (cell size 2 hmax_l / cell_div) addressed by Morton codes.  A tile searches every level l

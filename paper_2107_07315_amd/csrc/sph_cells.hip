@@ -9,7 +9,7 @@
 // search adapts to the tenfold range of smoothing lengths by itself (no grid, no second sort).
 // k_build_tiles descends the boxes for every tile and tests what is left on the matrix cores.  FP32
 // runs and shells take the lists of a cell grid instead (sph_cellgrid.hip, which says why), and so do very
-// large sets (kBoxesMost).
+// large sets (kBoxesMost) and those with a wide skin (wide_skin).
 #include <stddef.h>
 #include <string.h>
 
@@ -264,13 +264,6 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t& total)
   total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
   return before + inc - v;
 }
-
-// Tiles of small FP64 sets (with 4 list slots per particle) start at every 32nd particle: the pair passes
-// then give a target 8 lanes (4 slots of 2 lanes), so a workgroup is as full and its walk half as long, and
-// the build's waves have half the targets.  Ten steps, us, with tiles of 64 and 32: 8000-particle lattice
-// 701 and 638, 13.8k 733 and 676, 22k 879 and 865, 33k 847 and 915 (there 64 fills every CU twice, once);
-// 15k star with diagnostics 1135 and 993, 20k relaxation 604 and 570, 20k snapshot 380 and 368.
-constexpr int64_t kTiles32 = 24576;
 
 // The box search of a tile looks at every run of 64 tiles, so its time grows with the square of the set;
 // larger FP64 sets take the cell grid's lists.  List build with boxes and with the grid, ms: particles
@@ -1029,7 +1022,7 @@ static void launch_build(const BuildArgs& B, bool per, dim3 grid, hipStream_t s)
 // Candidate-list build: every particle array of the state is reordered along the global Morton curve (the
 // outputs only when outputs_recomputed is false, the half-step copies only when it is true), tiles are cut
 // from that order and each tile's candidates are collected, through the boxes of runs of particles or, where
-// the sums keep their order and in very large sets, through the multi-level grid; the positions and h at the list build are kept
+// the sums keep their order, in very large sets and with a wide skin, through the multi-level grid; the positions and h at the list build are kept
 // for the drift test.
 sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   const int64_t n = st->n;
@@ -1037,12 +1030,15 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   const unsigned nb = grid_for(n, kB), nb4 = grid_for(n, 1024);
   unsigned nred = nb < 1024 ? nb : 1024;
   sph_status e;
+  const bool cells = keeps_sum_order(c->p) || wide_skin(c->p, n) || n > kBoxesMost;
+  c->tile_len = !cells && small_tiles(c->p, n) ? 32 : 64;
   hipLaunchKernelGGL(k_bounds, dim3(nred), dim3(kB), 0, s, st->x, st->y, st->z, st->h, n, c->sort.partial);
   hipLaunchKernelGGL(k_grid_setup1, dim3(1), dim3(64), 0, s, c->grid, c->sort.partial, (int)nred, c->p.periodic,
                      c->p.box, c->p.skin, c->status);
   hipLaunchKernelGGL(k_gkeys, dim3(nb), dim3(kB), 0, s, st->x, st->y, st->z, n, c->grid, c->keys, c->vals);
   if ((e = sph_sort_pairs(c, c->keys, c->vals, n))) return e;
   {
+    const bool in_place = c->p.graph || exact_lists_written(c);
     PermArray A[64];
     int m = 0;
     for (double* a : {st->x, st->y, st->z, st->vx, st->vy, st->vz, st->u, st->h}) A[m++] = {a, 8, false, nullptr};
@@ -1054,18 +1050,19 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
       if (c->p.density_mode == SPH_DENS_CONTINUITY) A[m++] = {st->D, 8, false, nullptr};
       if (c->p.dtP_mode == SPH_DTP_LAGGED) A[m++] = {st->P, 8, false, nullptr};
       // the step's half-step copies, into their second buffer (outside a step nothing reads them); in
-      // place where captured kicks hold the first one (a new capture costs more than the copy)
+      // place where captured kicks hold the first one (a new capture costs more than the copy) or exact
+      // lists take the second one's room
       for (int k = 0; k < SPH_HALF_FIELDS; ++k)
         if (k < 10 || c->p.density_mode == SPH_DENS_CONTINUITY)
           A[m++] = {c->half + (int64_t)k * c->capacity, 8, k >= 4 && k < 10,
-                    c->p.graph ? nullptr : c->half_alt + (int64_t)k * c->capacity};
+                    in_place ? nullptr : c->half_alt + (int64_t)k * c->capacity};
     }
     A[m++] = {st->id, 4, false, nullptr};
     if (st->star) A[m++] = {st->star, 4, false, nullptr};
     A[m++] = {st->broken, 1, false, nullptr};
     A[m++] = {st->type, 1, false, nullptr};
     if ((e = permute_arrays(c, A, m, st->type, n))) return e;
-    if (outputs_recomputed && !c->p.graph) {
+    if (outputs_recomputed && !in_place) {
       double* t = c->half;
       c->half = c->half_alt;
       c->half_alt = t;
@@ -1078,8 +1075,6 @@ sph_status sph_rebin(sph_ctx* c, sph_state* st, bool outputs_recomputed) {
   uint32_t* flag = reinterpret_cast<uint32_t*>(c->tmp);
   uint32_t* idx = flag + c->capw;
   uint32_t* bsum = c->sort.scan_bsum;
-  const bool cells = keeps_sum_order(c->p) || n > kBoxesMost;
-  c->tile_len = !cells && pass_lanes(c->p) == 4 && n <= kTiles32 ? 32 : 64;
   hipLaunchKernelGGL(k_tile_flags, dim3(nb4), dim3(kB), 0, s, c->keys, st->h, n, c->grid, tile_cut_of(c->p), c->tile_len, flag, bsum);
   const bool per = c->p.periodic != 0;
   const dim3 tgrid(tile_grid(c->cap_tiles));

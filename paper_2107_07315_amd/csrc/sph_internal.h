@@ -310,7 +310,7 @@ struct sph_ctx {
   // grid and sort
   GridInfo* grid;       // device
   uint32_t *keys, *vals;  // Morton keys and the permutation that sorts them
-  // cell grid (keeps_sum_order, and very large sets)
+  // cell grid (keeps_sum_order, wide_skin, and very large sets)
   int2* cell_se;        // per cell [start, end) in the cell-sorted order; cleared at every build
   int64_t max_cells;
   double4* pos_sorted;  // x, y, z, h in the cell-sorted order
@@ -324,8 +324,8 @@ struct sph_ctx {
   // tile_uoff[t] holds the union of the tile's candidates (particle indices).  Candidate entry k
   // of particle p is the local index into U_t stored at nbr16s[((k/8)*capw + p)*8 + k%8] (groups
   // of 8 entries per lane, so a lane fetches 8 entries with one 16-byte load and a wave's load is
-  // one contiguous 1 KB); the exact lists that the neighbour export has the density pass write use the
-  // same layout in nbr16 with nbr_count.
+  // one contiguous 1 KB); the exact lists that the density pass writes for the neighbour export, and for
+  // the other passes where the skin is wide, use the same layout in nbr16 with nbr_count.
   int32_t* tile_start;
   int32_t* tile_cnt;
   uint32_t* tile_uoff;  // tile t owns tile_u[tile_uoff[t], + min(ucap, cnt * cap_s))
@@ -336,8 +336,8 @@ struct sph_ctx {
   int32_t* tile_usize;
   int32_t* stress_tiles;  // tiles with a type-1 particle, in tile order (nstress of them)
   uint32_t* tile_st;      // per tile: 1 if a particle or a union member is of type 1
-  uint16_t* nbr16;      // exact lists, one per slot (particle * lanes + sub-index), during sph_export_neighbours;
-                        // otherwise the boxes and half_alt
+  uint16_t* nbr16;      // exact lists, one per slot (particle * lanes + sub-index), from a density pass that writes
+                        // them to the export's or the forces' end; otherwise the boxes and half_alt
   int32_t* nbr_count;   // exact neighbours per particle
   int32_t* nbr_count_sl;  // entries per slot list
   uint16_t* nbr16s;
@@ -420,6 +420,7 @@ sph_status launch_drift_check(sph_ctx* c, sph_state* st);
 sph_status launch_flag_clear(sph_ctx* c);
 sph_status launch_density(sph_ctx* c, sph_state* st);   // pair loop
 sph_status launch_exact_lists(sph_ctx* c);               // exact lists of the last evaluation (export)
+bool exact_lists_written(const sph_ctx* c);              // whether the density pass writes them by itself
 sph_status launch_eos(sph_ctx* c, sph_state* st);       // per-particle epilogue
 sph_status launch_stress(sph_ctx* c, sph_state* st);
 sph_status launch_forces(sph_ctx* c, sph_state* st);
@@ -474,6 +475,24 @@ __host__ __device__ __forceinline__ int pass_lanes(const sph_params& p) { return
 // give them (sph_cellgrid.hip says why): all FP32 runs, and shells, which an inner wall holds open.
 __host__ __device__ __forceinline__ bool keeps_sum_order(const sph_params& p) {
   return p.precision == SPH_FP32 || p.wall_in > 0.0;
+}
+// FP64 sets of at most kTiles32 particles have tiles of 32 (with 4 list slots per particle): the pair passes
+// then give a target 8 lanes (4 slots of 2 lanes), so a workgroup is as full and its walk half as long, and
+// the build's waves have half the targets.  Ten steps, us, with tiles of 64 and 32: 8000-particle lattice
+// 701 and 638, 13.8k 733 and 676, 22k 879 and 865, 33k 847 and 915 (there 64 fills every CU twice, once);
+// 15k star with diagnostics 1135 and 993, 20k relaxation 604 and 570, 20k snapshot 380 and 368.
+constexpr int64_t kTiles32 = 24576;
+__host__ __device__ __forceinline__ bool small_tiles(const sph_params& p, int64_t n) {
+  return !keeps_sum_order(p) && pass_lanes(p) == 4 && n <= kTiles32;
+}
+// With a wide skin most candidates of the FP64 stress and force passes would be beyond the support: the
+// density pass then writes exact lists for them, and the lists are the cell grid's, whose unions spread
+// every target's neighbours over all LDS chunks.  Ten steps, us, without and with: star of 2M particles,
+// skin 0.14 20200 and 20500, 0.22 26700 and 24700, 0.3 35100 and 28500; 200k 0.14 2490 and 2510, 0.22 3140
+// and 2870, 0.5 7720 and 4880; 60k 0.18 1240 and 1110.  Small sets gain by their tiles more: 4096-particle
+// lattice 0.3 640 and 730, 0.5 770 and 790, 1.0 3330 and 1690; 15k star 0.3 830 and 780, 0.5 1070 and 980.
+__host__ __device__ __forceinline__ bool wide_skin(const sph_params& p, int64_t n) {
+  return p.precision != SPH_FP32 && p.skin > (small_tiles(p, n) ? 0.5 : 0.2);
 }
 // Tile cut in smoothing lengths (the measured best with 4 lanes per target on the 2M star)
 __host__ __device__ __forceinline__ double tile_cut_of(const sph_params& p) { return p.tile_cut > 0.0 ? p.tile_cut : 10.0; }

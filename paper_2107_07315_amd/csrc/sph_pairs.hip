@@ -147,9 +147,11 @@ struct PassArgs {
   const int32_t* __restrict__ tile_u;
   const int32_t* __restrict__ tile_usize;
   const int32_t* __restrict__ stress_tiles;
-  int cap_sl;                           // entries a slot holds
+  int cap_sl;                           // entries a slot of the exact lists holds
   const uint16_t* __restrict__ nbr16s;   // candidate lists of the last build
   const int32_t* __restrict__ cnt_s;
+  const uint16_t* __restrict__ nbr16;    // exact lists of the evaluation (exact_lists_written), one per slot,
+  const int32_t* __restrict__ cnt_sl;    //   and their lengths
   const uint32_t* __restrict__ tile_st;   // per tile: a particle or union member of type 1 (or null)
   const int32_t* __restrict__ star;
   const StarInfo* __restrict__ stars;
@@ -368,18 +370,20 @@ __device__ __forceinline__ void stage_union(const int32_t* __restrict__ U, int c
     if (b[k] >= 0) put((int)threadIdx.x + k * NT, r[k]);
 }
 
-// The list every pass walks (slot = particle * L + sub-index) and its length: the candidate list of
-// the last build, candidate k of a particle being entry k / L of slot k % L.  The pair terms carry the
-// kernel or its gradient, which are zero beyond the support, so the candidates of the skin add exact
-// zeros.  (Exact lists written by the density pass for the other two cost more than the third of the
-// pairs that they spare, in FP64 too: a wave waits for its longest list, and the density pass for its
-// stores.  2M star, density + force pass: 555 + 943 us with them, 459 + 937 without.)
-template <int L>
+// The list that the stress and force passes walk (slot = particle * L + sub-index) and its length: the
+// candidate list of the last build, candidate k of a particle being entry k / L of slot k % L.  The pair
+// terms carry the kernel or its gradient, which are zero beyond the support, so the candidates of the skin
+// add exact zeros, and the sums are those of the exact lists.  Exact lists written by the density pass for
+// the other two spare those candidates, but a wave waits for its longest list and the density pass for its
+// stores: they pay only where the skin is wide (exact_lists_written).  Which it is (EL: exact) is known at
+// compile time: a branch on it cost the small sets 1% of a step.
+template <bool EL>
 __device__ __forceinline__ const uint4* pass_list(const PassArgs& A, int64_t slot) {
-  return reinterpret_cast<const uint4*>(A.nbr16s) + slot;
+  return reinterpret_cast<const uint4*>(EL ? A.nbr16 : A.nbr16s) + slot;
 }
-template <int L>
-__device__ __forceinline__ int pass_count(const PassArgs& A, int64_t p, int sub) {
+template <int L, bool EL>
+__device__ __forceinline__ int pass_count(const PassArgs& A, int64_t p, int sub, int64_t slot) {
+  if constexpr (EL) return A.cnt_sl[slot];
   const int total = A.cnt_s[p];
   return total > sub ? (total - sub + L - 1) / L : 0;
 }
@@ -636,7 +640,7 @@ constexpr float kBand = 3.814697265625e-06f;   // 2^-18
 // (245M candidate pairs), 565 when it also wrote exact lists and read 32-byte records whole.  Walks the
 // candidate lists, takes the exact neighbour decision r^2 < (h_a + h_b)^2 of the FP64 positions on every
 // candidate, sums the kernel over the neighbours in R and counts them; with XL it also writes the exact
-// lists (for the neighbour export).  A workgroup of L waves takes one tile (or, with M > 1, a part of it):
+// lists (for the neighbour export, and where exact_lists_written).  A workgroup of L waves takes one tile (or, with M > 1, a part of it):
 // lane g serves target g / L as sub-lane g % L, walks the candidate slot list (particle * L + sub-lane) and
 // with XL writes the exact hits to the exact slot list of the same index; the L partial sums are added
 // across the lanes.  The per-particle epilogue runs in k_density_epilogue, one lane per particle.
@@ -910,7 +914,7 @@ __global__ void k_word_clear(int32_t* w) { *w = 0; }   // a kernel, not a memset
 // ---- velocity gradient and stress rate ---------------------------------------------------------
 // Lane g of the L-wave workgroup walks the candidate slot list (g / L, g % L), or with M > 1 its part of
 // one (TargetLane); the partial velocity gradients of a target's lanes are added before the epilogue.
-template <typename R, int KER, bool PER, int L, int M>
+template <typename R, int KER, bool PER, int L, int M, bool EL>
 __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Rec<R>::P4* __restrict__ pos,
                                                    const typename Rec<R>::V4* __restrict__ fv,
                                                    const typename Rec<R>::A2* __restrict__ fa,
@@ -978,12 +982,12 @@ __global__ __launch_bounds__(64 * L) void k_stress(PassArgs A, const typename Re
       sv.put(CH - 1, V4{(R)0, (R)0, (R)0, (R)0});
     }
     __syncthreads();
-    const int cnt = stressed ? pass_count<L>(A, tw.p, sub) : 0;
+    const int cnt = stressed ? pass_count<L, EL>(A, tw.p, sub, slot) : 0;
     walk_groups_pf<M, false>(
-        pass_list<L>(A, slot), A.capw * L, me.part, cnt, count_range(cnt), CH - 1,
+        pass_list<EL>(A, slot), A.capw * L, me.part, cnt, count_range(cnt), CH - 1,
         [&](int j) { return Recs{sp.get(j), sv.get(j)}; }, [&](int, const Recs& r) { pair(r); }, [] {});
   } else {
-    tw.start(pass_list<L>(A, slot), A.capw * L, stressed ? pass_count<L>(A, tw.p, sub) : 0);
+    tw.start(pass_list<EL>(A, slot), A.capw * L, stressed ? pass_count<L, EL>(A, tw.p, sub, slot) : 0);
     for (int c0 = 0; c0 < tw.usize; c0 += CH) {
       __syncthreads();
       stage(c0, CH);
@@ -1096,7 +1100,13 @@ __device__ __forceinline__ void ext_accel(const PassArgs& A, const ForceOut& O, 
 // and kXSL (FP32, with neither sum): the neighbours' S/D^2 staged in LDS with the other records,
 // for workloads where most tiles hold stressed particles (otherwise each stressed pair reads the
 // neighbour's union index and six S/D^2 values from memory).
-constexpr int kXDD = 1, kXGP = 2, kXSL = 4;
+// kXEL (FP64): the walk of the exact lists that the density pass wrote (exact_lists_written).
+// kXSC (FP64, with kXEL and neither sum): LDS chunks of half the records, four workgroups per CU instead of two, for
+// skins so wide that most unions are more than one chunk anyway.  2M star, ten steps, ms, with chunks of
+// 1024 and 512: skin 0.26 26.2 and 26.4, 0.3 29.2 and 28.5, 0.4 34.8 and 33.0; 200k star 0.3 3.37 and 3.41,
+// 0.4 4.04 and 3.96.
+constexpr int kXDD = 1, kXGP = 2, kXSL = 4, kXSC = 8, kXEL = 16;
+constexpr double kSkinSC = 0.3;
 template <typename R, int KER, bool PER, int L, int M, int XS>
 __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) void k_forces(PassArgs A, const typename Rec<R>::P4* __restrict__ pos,
                                                    const typename Rec<R>::V4* __restrict__ fv,
@@ -1106,9 +1116,9 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   using P4 = typename Rec<R>::P4;
   using V4 = typename Rec<R>::V4;
   using A2 = typename Rec<R>::A2;
-  constexpr bool DD = (XS & 3) != 0, GP = (XS & 3) == kXGP, SL = (XS & kXSL) != 0;
+  constexpr bool DD = (XS & 3) != 0, GP = (XS & 3) == kXGP, SL = (XS & kXSL) != 0, EL = (XS & kXEL) != 0;
   static_assert(!SL || std::is_same<R, float>::value, "S/D^2 in LDS: FP32 records only");
-  constexpr int CH = (SL ? Rec<float>::CH_FS : Rec<R>::CH_F) * L;
+  constexpr int CH = (SL ? Rec<float>::CH_FS : Rec<R>::CH_F / ((XS & kXSC) ? 2 : 1)) * L;
   constexpr int CHU = CH - 1;   // union records per chunk; slot CHU holds the walk's sentinel
   const TargetLane<L, M> me(threadIdx.x);
   const int sub = me.slot;
@@ -1133,8 +1143,8 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
   tw.begin(A, tile, tl);
   const int64_t a = tw.a;
   const int64_t slot = a * L + sub;
-  const uint4* lst = pass_list<L>(A, slot);
-  const int cnt = tw.valid ? pass_count<L>(A, tw.p, sub) : 0;
+  const uint4* lst = pass_list<EL>(A, slot);
+  const int cnt = tw.valid ? pass_count<L, EL>(A, tw.p, sub, slot) : 0;
   const int64_t n = A.n;
   const sph_params& p = A.p;
   const P4 pa = tw.valid ? pos[a] : P4{0, 0, 0, 1};
@@ -1247,7 +1257,7 @@ __global__ __launch_bounds__(64 * L) __attribute__((amdgpu_waves_per_eu(4))) voi
           lst, A.capw * L, me.part, cnt, count_range(cnt), CHU, ld,
           [&](int loc, const Recs& r) { pair_st(loc, r, std::false_type{}); }, [] {});
   } else {
-    const bool any_st = sizeof(R) == 4 || XS != 0 || stress_tile();
+    const bool any_st = sizeof(R) == 4 || (XS & 7) != 0 || stress_tile();
     tw.start(lst, A.capw * L, cnt);
     for (int c0 = 0; c0 < tw.usize; c0 += CHU) {
       __syncthreads();
@@ -1361,6 +1371,8 @@ PassArgs make_args(sph_ctx* c, sph_state* st) {
   A.cap_sl = slot_capacity(c->cap, pass_lanes(c->p));
   A.nbr16s = c->nbr16s;
   A.cnt_s = c->nbr_count_s;
+  A.nbr16 = c->nbr16;
+  A.cnt_sl = c->nbr_count_sl;
   A.tile_st = c->tile_st;
   A.star = c->stars ? st->star : nullptr;
   A.stars = c->stars;
@@ -1437,6 +1449,8 @@ static DensOut dens_out(sph_ctx* c, sph_state* st) {
   return O;
 }
 
+bool exact_lists_written(const sph_ctx* c) { return wide_skin(c->p, c->n); }
+
 sph_status launch_density(sph_ctx* c, sph_state* st) {
   PassArgs A = make_args(c, st);
   DensOut O = dens_out(c, st);
@@ -1454,8 +1468,17 @@ sph_status launch_density(sph_ctx* c, sph_state* st) {
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<float, KER, PER, L, 1, false>), g, b, 0, c->stream, A, c->pos4, O,
                            nullptr, c->nbr_count, nullptr);
       else
+      {
+        if constexpr (M == 1) {
+          if (exact_lists_written(c)) {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, 1, true>), g, b, 0, c->stream, A, c->pos4, O,
+                               c->nbr16, c->nbr_count, c->nbr_count_sl);
+            return;
+          }
+        }
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_density<double, KER, PER, L, M, false>), g, b, 0, c->stream, A, c->pos4, O,
                            nullptr, c->nbr_count, nullptr);
+      }
     });
   });
   HIP_TRY(hipGetLastError());
@@ -1541,11 +1564,14 @@ sph_status launch_stress(sph_ctx* c, sph_state* st) {
       constexpr int L = decltype(LL)::value, M = decltype(MM)::value;
       const dim3 b(64 * L);
       if (c->p.precision == SPH_FP32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<float, KER, PER, L, 1>), g, b, 0, c->stream, A, c->pos4f, c->fvf,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<float, KER, PER, L, 1, false>), g, b, 0, c->stream, A, c->pos4f, c->fvf,
                            c->faf, st->S, c->mu, st->dSdt, c->sdot);
+      else if (exact_lists_written(c))
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<double, KER, PER, L, 1, true>), g, b, 0, c->stream, A, c->pos4,
+                           c->fv, c->fa, st->S, c->mu, st->dSdt, c->sdot);
       else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<double, KER, PER, L, M>), g, b, 0, c->stream, A, c->pos4, c->fv,
-                           c->fa, st->S, c->mu, st->dSdt, c->sdot);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stress<double, KER, PER, L, M, false>), g, b, 0, c->stream, A, c->pos4,
+                           c->fv, c->fa, st->S, c->mu, st->dSdt, c->sdot);
     });
   });
   HIP_TRY(hipGetLastError());
@@ -1572,12 +1598,18 @@ sph_status launch_forces(sph_ctx* c, sph_state* st) {
         if (c->p.precision == SPH_FP32)
           hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<float, KER, PER, L, 1, X>), g, b, 0, c->stream, A, c->pos4f,
                              c->fvf, c->faf, c->sigf, c->tovf, c->sdot, O);
+        else if (exact_lists_written(c))
+          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<double, KER, PER, L, 1, X | kXEL>), g, b, 0, c->stream, A, c->pos4,
+                             c->fv, c->fa, c->sig, c->tovf, c->sdot, O);
         else
           hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<double, KER, PER, L, M, X>), g, b, 0, c->stream, A, c->pos4,
                              c->fv, c->fa, c->sig, c->tovf, c->sdot, O);
       };
       if (xs == kXGP) launch(std::integral_constant<int, kXGP>{});
       else if (xs == kXDD) launch(std::integral_constant<int, kXDD>{});
+      else if (exact_lists_written(c) && c->p.skin > kSkinSC)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<double, KER, PER, L, 1, kXSC | kXEL>), g, b, 0, c->stream, A, c->pos4,
+                           c->fv, c->fa, c->sig, c->tovf, c->sdot, O);
       else if (c->stress_heavy && c->p.precision == SPH_FP32)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forces<float, KER, PER, L, 1, kXSL>), g, b, 0, c->stream, A, c->pos4f,
                            c->fvf, c->faf, c->sigf, c->tovf, c->sdot, O);
