@@ -42,7 +42,9 @@ FORCE_FLOP = {"pair": 73, "particle": 110}
 DENS_BYTES = {"FP64": 52, "FP32": 52, "candidate": 2}
 FORCE_BYTES = {"FP64": 176, "FP32": 136, "candidate": 2}
 PEAK = {"FP64": 78.6e12, "FP32": 157.3e12}     # published MI355X vector peaks, FLOP/s
-KERNEL_SOURCES = ("paper_2107_07315_amd/csrc/sph_pairs.hip", "paper_2107_07315_amd/csrc/sph_internal.h")
+# what the passes' bytes depend on: their code and that of the list builds (tile cuts, union order, list lengths)
+KERNEL_SOURCES = tuple("paper_2107_07315_amd/csrc/" + f for f in (
+    "sph_pairs.hip", "sph_internal.h", "sph_cells.hip", "sph_cellgrid.hip", "sph_build.h", "sph_listout.h"))
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pair_passes_2M_traffic.json")
 
 
