@@ -29,3 +29,25 @@ def test_shell_lists_keep_the_grids_order(n, solid, lanes):
     assert a[3] == b[3]
     for x, y in zip(a[:3], b[:3]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("cell_div", [2, 4])
+def test_cell_size_leaves_the_fp64_sets(cell_div):
+    # where an FP64 build has cells (shells, wide skins), finer ones leave the exact sets
+    from paper_2107_07315_amd import sph
+    w = W.crust_shell(5000)
+    star = W.star(3000, seed=3)
+    for v, skin in ((w, 0.08), (star, 0.6)):
+        out = []
+        for div in (1, cell_div):
+            ctx = sph.Context(v.params, capacity=v.n, skin=skin, cell_div=div)
+            st = sph.DeviceState(v.arrays)
+            ctx.evaluate(st)
+            ctx.sph_sync()
+            off, ids = ctx.sph_export_neighbours(v.n)
+            order = st.numpy(["id"])["id"]
+            rows = np.repeat(order, np.diff(off)).astype(np.int64)
+            out.append((np.sort(rows * v.n + order[ids]), ids))
+            ctx.close()
+        assert np.array_equal(out[0][0], out[1][0])
+        assert not np.array_equal(out[0][1], out[1][1])   # in another order: the cells did change
